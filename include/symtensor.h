@@ -131,7 +131,13 @@
  * the planes are interleaved by 32-deep K-steps, and a binary32 u whose
  * contracted modes are its last ones, in runs of 4 or more elements per block,
  * 16-byte aligned, is read in place by the 256 x 256 tile and split in
- * registers (same bits as its planes).  The workspace holds
+ * registers (same bits as its planes).  F64 and F32 products that would
+ * otherwise align an operand, expand a complex v, or run on register-staged
+ * tiles take a product that reads u and v in place in any layout and at any
+ * alignment where its time model prefers it (K runs of any length stepped run by
+ * run, complex v not expanded; info.fused and info.fused_v are then those of the
+ * product it replaces); the three-step path multiplies its aligned forms on the
+ * same tile, in the same K-steps and stream-K shares.  The workspace holds
  * U_al in that case (left unused when u is read in place), then V_al (used when
  * v is not read in place) and the tables.  Where K-steps are the three-step path's, results are identical in
  * value to it: the product sums in the same order.
@@ -164,7 +170,9 @@
  *                          tile applies (F64/F32: "128x96", "d96x96s2", ...,
  *                          "rows" = the row-streaming product taken by default
  *                          where K and N are at most 64 and the slices hold at
- *                          least 16384 rows in all, "tallk" = the long-K
+ *                          least 16384 rows in all, "a96x96s2", "a128x64s2",
+ *                          "a64x64s2" = the in-place product for any layout,
+ *                          "tallk" = the long-K
  *                          product taken by default where M and N are at most
  *                          64 and K is 1024 or more;
  *                          BF16X3: "b128x128k32", "bd128x256s3", ...); an

@@ -1,0 +1,362 @@
+// Sector product in place for any layout of its operands (Alg. 2's product step,
+// f64 / f32, real or complex): the global-to-LDS ring of gemm.hip's tiles with a
+// loader that takes every layout of U, V and W, K runs of any length, and any
+// element alignment, so that no aligned form is written and no shape falls back
+// to register-staged one-element loads.
+//
+// What bounds it: the matrix pipes once a tile's loads are in flight, as for the
+// other global-to-LDS tiles; what it saves is passes over memory (aligned forms
+// of K-major or complex operands) and the issue slots of one-element register
+// loads.  Its loads differ from those tiles' in three ways:
+//  * CH = 4: each lane copies 4 bytes, so a tile row needs no 16-byte alignment
+//    and no whole 16-byte chunk (odd block sizes); four times the load
+//    instructions of CH = 16, still few beside a K-step's MFMAs (24 loads of a
+//    wave against 36 f64 MFMAs of 64 cycles on 96 x 96).
+//  * K tails: lanes past the valid depth of a K-step read a zero word instead
+//    (both operands, so that nothing of a neighbouring row is multiplied).
+//  * every K row of a K-major A at its own table entry, one scalar load per row
+//    and step, issued a step ahead (any layout of U's contracted modes).
+// Complex operands run on the real representation of C (include/symtensor.h,
+// COMPLEX OPERANDS) without expanding V: B's tile holds V's (re, im) pairs once
+// and the odd real rows (-im, re) are formed as fragments are read; A is read as
+// interleaved reals (its contracted modes last) or K-major as pairs.
+//
+// Measured (before -> after): the complex bond-64 environment chain 648 -> 245 us
+// (its align passes alone took 392); 9 x (500 x 500 x 500) f64 68.7 -> 62.9 us,
+// f32 44.8 -> 35.9 us; the Z_8 ladder in f32 (8 x (4608 x 4608 x 288)) 915 -> 818 us
+// (96 x 96 with three workgroups per CU against a 64 x 96 register tile); the
+// complex Z_8 ladder with blocks of 16 and 6, 1551 -> 1361 us.  4-byte loads run
+// at about two thirds of 16-byte ones' rate (3 x (743 x 1113 x 1111) f64: 34.5
+// TFLOP/s), so odd real shapes mostly stay on the register tiles.
+//
+// Values and K order are the other tiles': K-steps of 128 bytes, four indices
+// per MFMA, tiles cut by stream-K summed in K order by k_sk_fixup.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <atomic>
+#include <cstdint>
+
+#include "any_index.hpp"
+#include "gemm_tiles.hpp"
+#include "plan.hpp"
+#include "sk_index.hpp"
+
+namespace symt {
+namespace {
+
+// Source of the lanes past a K-step's valid depth.
+__device__ __attribute__((aligned(16))) const uint32_t kZeroWords[4] = {0, 0, 0, 0};
+
+template <int CH>
+__device__ __forceinline__ void lds_dma(const void* g, void* lds) {
+  static_assert(CH == 16 || CH == 4, "lane load");
+  if constexpr (CH == 16) __builtin_amdgcn_global_load_lds((gptr_t)(g), (lptr_t)(lds), 16, 0, 0);
+  else __builtin_amdgcn_global_load_lds((gptr_t)(g), (lptr_t)(lds), 4, 0, 0);
+}
+
+// AM, CB: the tile's layouts (any_index.hpp).  Null tables stand for the aligned
+// row-major forms (the three-step path, so that it sums in the same order).
+template <typename T, int BM, int BN, int WM, int WN, int S, int CH, int AM, bool CB>
+struct AnyTile {
+  static constexpr int ES = static_cast<int>(sizeof(T));
+  static constexpr int NW = WM * WN, NT = 64 * NW;
+  static constexpr int VE = 16 / ES;
+  static constexpr int BK = 128 / ES;
+  static constexpr int TM = BM / WM / 16, TN = BN / WN / 16;
+  static constexpr int A_BYTES = BM * 128;
+  static constexpr int A_ROW = AM == 0 ? 128 : AM == 1 ? BM * ES : 2 * BM * ES;   // bytes of an LDS row
+  static constexpr int B_ROW = BN * ES;
+  static constexpr int B_BYTES = (CB ? BK / 2 : BK) * B_ROW;
+  static constexpr int STAGE = A_BYTES + B_BYTES;
+  static constexpr int A_LOADS = (A_BYTES / CH + NT - 1) / NT, B_LOADS = (B_BYTES / CH + NT - 1) / NT;
+  static constexpr bool WHOLE = A_BYTES % (CH * NT) == 0 && B_BYTES % (CH * NT) == 0;
+  static_assert(A_BYTES % (64 * CH) == 0 && B_BYTES % (64 * CH) == 0, "loads must fill whole waves");
+  static_assert(TM * WM * 16 == BM && TN * WN * 16 == BN, "tile shape");
+  static_assert(S == 2 || (WHOLE && (S - 2) * (A_LOADS + B_LOADS) < 64), "every wave counts the same loads");
+  using Acc = typename Mfma<T>::Acc;
+};
+
+// Most LDS rows that one wave load (64 lanes of CH bytes) of a tile with ROW-byte rows touches.
+template <int CH, int ROW>
+constexpr int any_rows_per_load() {
+  // (loads start at multiples of gcd(64 CH, ROW) in a row)
+  int g = ROW, b = 64 * CH;
+  while (b) {
+    const int t = g % b;
+    g = b;
+    b = t;
+  }
+  return (ROW - g + 64 * CH - 1) / ROW + 1;
+}
+
+template <typename T, int BM, int BN, int WM, int WN, int S, int CH, int AM, bool CB>
+__device__ __forceinline__ void any_tile_accumulate(
+    const T* __restrict__ A, const T* __restrict__ B, int M, int N, const AnySteps& st, int64_t q, int m0, int n0,
+    int kt0, int kt1, const int64_t* __restrict__ ra, const int64_t* __restrict__ ca,
+    const int64_t* __restrict__ rb, const int64_t* __restrict__ cb, int64_t ldb, char* smem,
+    typename Mfma<T>::Acc (&acc)[BM / WM / 16][BN / WN / 16]) {
+  using D = AnyTile<T, BM, BN, WM, WN, S, CH, AM, CB>;
+  constexpr int ES = D::ES, NT = D::NT, NW = D::NW, BK = D::BK, TM = D::TM, TN = D::TN;
+  constexpr int A_LOADS = D::A_LOADS, B_LOADS = D::B_LOADS, STAGE = D::STAGE, A_BYTES = D::A_BYTES;
+  constexpr int A_ROW = D::A_ROW;
+  constexpr int A_NR = any_rows_per_load<CH, A_ROW>();
+  const int K = st.K;
+  const int KB = CB ? K / 2 : K;                 // rows of B's table
+  const char* Ab = reinterpret_cast<const char*>(A);
+  const char* Bb = reinterpret_cast<const char*>(B) + (rb ? 0 : q * static_cast<int64_t>(K) * N * ES);
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm0 = (wave / WN) * (BM / WM);
+  const int wn0 = (wave % WN) * (BN / WN);
+
+  // Byte offset of each load's source, fixed across K-steps; the K index (AM = 0)
+  // or LDS row of the lane inside the step is recomputed where a tail needs it.
+  int64_t a_src[A_LOADS], b_src[B_LOADS];
+#pragma unroll
+  for (int i = 0; i < A_LOADS; ++i) {
+    const AnySlot x = any_a_slot<ES, BM, AM>((i * NT + tid) * CH);
+    constexpr int PE = AM == 0 ? 16 : AM == 2 ? 2 * ES : ES;   // bytes of one m in a load
+    const int m = min(m0 + x.line, any_last_line<CH, PE>(M));
+    a_src[i] = (ra ? ra[q * M + m] : (q * M + m) * static_cast<int64_t>(K)) * ES + (AM == 0 || CH == 4 ? x.sub : 0);
+  }
+#pragma unroll
+  for (int i = 0; i < B_LOADS; ++i) {
+    const AnySlot x = any_b_slot<ES, BN, CB>((i * NT + tid) * CH);
+    const int n = min(n0 + x.line, any_last_line<CH, ES>(N));
+    b_src[i] = ((CB ? x.k / 2 : x.k) * ldb + (cb ? cb[q * N + n] : static_cast<int64_t>(n))) * ES +
+               (CH == 4 ? x.sub : 0);
+  }
+  // Table entries of the next step to issue (wave-uniform scalar loads, one step ahead).
+  int k0_next = 0, kv_next = 0;
+  int64_t acol_next = 0;
+  int64_t arow_next[AM ? A_LOADS : 1][AM ? A_NR : 1];
+  int64_t brow_next = 0;
+  auto fetch = [&](int kt) {
+    any_step(st, kt, BK, k0_next, kv_next);
+    if constexpr (AM == 0) {
+      acol_next = ca ? ca[q * K + k0_next] : k0_next;
+    } else {
+#pragma unroll
+      for (int i = 0; i < A_LOADS; ++i) {
+        const int r0 = (i * NW + wave) * 64 * CH / A_ROW;
+#pragma unroll
+        for (int j = 0; j < A_NR; ++j)
+          arow_next[i][j] = ca[q * K + min(k0_next + (AM == 2 ? 2 : 1) * (r0 + j), K - 1)];
+      }
+    }
+    const int kb = CB ? k0_next / 2 : k0_next;
+    brow_next = rb ? rb[q * KB + kb] : kb * ldb;
+  };
+  // K-major A: the entry of this lane's LDS row among those its wave load touches.
+  auto arow_of = [&](int i) -> int64_t {
+    if constexpr (AM == 0) {
+      return acol_next;
+    } else {
+      const int at = (i * NW + wave) * 64 * CH % A_ROW + lane * CH;
+      int64_t off = arow_next[i][0];
+#pragma unroll
+      for (int j = 1; j < A_NR; ++j) {
+        const int64_t e = arow_next[i][j];
+        off = at >= j * A_ROW ? e : off;
+      }
+      return off;
+    }
+  };
+  auto issue = [&](int kt, int stage) {
+    char* base = smem + stage * STAGE + wave * 64 * CH;
+    const int kv = kv_next;
+    const bool tail = kv < BK;
+#pragma unroll
+    for (int i = 0; i < A_LOADS; ++i) {
+      if (A_BYTES % (CH * NT) != 0 && (i * NW + wave) * 64 * CH >= A_BYTES) break;
+      const char* g = Ab + (a_src[i] + arow_of(i) * ES);
+      if (tail) {
+        const int k = any_a_slot<ES, BM, AM>((i * NT + tid) * CH).k;
+        if (k >= kv) g = reinterpret_cast<const char*>(kZeroWords);
+      }
+      lds_dma<CH>(g, base + i * NT * CH);
+    }
+#pragma unroll
+    for (int i = 0; i < B_LOADS; ++i) {
+      if (D::B_BYTES % (CH * NT) != 0 && (i * NW + wave) * 64 * CH >= D::B_BYTES) break;
+      const char* g = Bb + (b_src[i] + brow_next * ES);
+      if (tail) {
+        const int k = any_b_slot<ES, BN, CB>((i * NT + tid) * CH).k;
+        if (k >= kv) g = reinterpret_cast<const char*>(kZeroWords);
+      }
+      lds_dma<CH>(g, base + A_BYTES + i * NT * CH);
+    }
+    if (kt + 1 < kt1) fetch(kt + 1);
+  };
+
+  const int nk = kt1 - kt0;
+  if (nk > 0) fetch(kt0);
+#pragma unroll
+  for (int s = 0; s < S - 1; ++s)
+    if (s < nk) issue(kt0 + s, s);
+  for (int it = 0; it < nk; ++it) {
+    // step it has landed once at most (S-2) later steps' loads are outstanding
+    if (it + S - 2 < nk) wait_vmcnt<(S - 2) * (A_LOADS + B_LOADS)>();
+    else wait_vmcnt<0>();
+    asm volatile("s_barrier" ::: "memory");
+    if (it + S - 1 < nk) issue(kt0 + it + S - 1, (it + S - 1) % S);
+    const char* As = smem + (it % S) * STAGE;
+    const char* Bs = As + A_BYTES;
+#pragma unroll
+    for (int kk = 0; kk < BK; kk += 4) {
+      const int k = kk + (lane >> 4);
+      T a[TM], b[TN];
+#pragma unroll
+      for (int i = 0; i < TM; ++i) {
+        a[i] = *reinterpret_cast<const T*>(As + any_a_off<ES, BM, AM>(wm0 + i * 16 + (lane & 15), k));
+      }
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        const int n = wn0 + j * 16 + (lane & 15);
+        const T x = *reinterpret_cast<const T*>(Bs + any_b_off<ES, BN, CB>(k, n));
+        // CB: real row 2 kc + 1 is (-im, re), the other member of the pair, im negated
+        b[j] = CB && (k & 1) && !(n & 1) ? -x : x;
+      }
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = Mfma<T>::run(a[i], b[j], acc[i][j]);
+    }
+  }
+}
+
+// Waves per SIMD that the register allocator leaves room for: three where the LDS
+// ring admits three workgroups per CU; two with 4-byte loads, whose 24 load
+// sources take 48 registers (96 x 96 spilled 73 of them at three).
+template <int BM, int BN, int CH>
+constexpr int kAnyWavesPerSimd = CH == 16 || BM * BN <= 64 * 64 ? 3 : 2;
+
+// One workgroup per tile (ts = 0, XCD-aware order), or stream-K (ts > 0:
+// persistent workgroups, pieces of cut tiles to `part` for k_sk_fixup).
+template <typename T, int BM, int BN, int WM, int WN, int S, int CH, int AM, bool CB>
+__global__ __launch_bounds__(64 * WM * WN, (kAnyWavesPerSimd<BM, BN, CH>)) void k_gemm_any(
+    const T* __restrict__ A, const T* __restrict__ B, T* __restrict__ C, int M, int N, AnySteps st, int tiles_m,
+    int tiles_n, int64_t ntiles, const int64_t* __restrict__ ra, const int64_t* __restrict__ ca,
+    const int64_t* __restrict__ rc, const int64_t* __restrict__ cc, const int64_t* __restrict__ rb,
+    const int64_t* __restrict__ cb, int64_t ldb, T* __restrict__ part, int ts, int c_rows4) {
+  using D = AnyTile<T, BM, BN, WM, WN, S, CH, AM, CB>;
+  constexpr int TM = D::TM, TN = D::TN;
+  __shared__ __attribute__((aligned(1024))) char smem[S * D::STAGE];
+  typename D::Acc acc[TM][TN];
+  SkSlot sl{0, 0, 1};
+  int64_t it = 0, end = st.nk, first = 0, tile = 0;
+  if (ts > 0) {
+    sl = sk_slot(static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x), ts);
+    const int64_t total = ntiles / ts * st.nk;
+    it = sk_bound(sl.team, total, sl.nteam);
+    end = sk_bound(sl.team + 1, total, sl.nteam);
+    first = it / st.nk;
+  } else {
+    tile = xcd_remap(blockIdx.x, ntiles);
+  }
+  while (it < end) {
+    int64_t q, grp = 0;
+    int tm, tn, kt0 = 0, kt1 = st.nk;
+    if (ts > 0) {
+      grp = it / st.nk;
+      kt0 = static_cast<int>(it - grp * st.nk);
+      kt1 = static_cast<int>(min(static_cast<int64_t>(st.nk), kt0 + (end - it)));
+      tile = grp * ts + sl.member;
+      tn = static_cast<int>(tile % tiles_n);
+      const int64_t t2 = tile / tiles_n;
+      tm = static_cast<int>(t2 % tiles_m);
+      q = t2 / tiles_m;
+      __syncthreads();      // the previous piece's LDS reads are done before new loads land
+    } else {
+      tile_coords(tile, tiles_m, tiles_n, q, tm, tn);
+    }
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) acc[i][j] = typename D::Acc{};
+    any_tile_accumulate<T, BM, BN, WM, WN, S, CH, AM, CB>(A, B, M, N, st, q, tm * BM, tn * BN, kt0, kt1, ra, ca, rb,
+                                                          cb, ldb, smem, acc);
+    if (kt0 == 0 && kt1 == st.nk) {
+      // W's table entries all requested before the first store
+      CTab<TM, TN> ct;
+      if (rc) load_ctab<T, BM, BN, WM, WN, TM, TN>(ct, M, N, q, tm * BM, tn * BN, rc, cc);
+      else affine_ctab<T, BM, BN, WM, WN, TM, TN>(ct, M, N, q, tm * BM, tn * BN);
+      store_tile_tab<T, BM, BN, WM, WN, TM, TN>(C, M, N, tm * BM, tn * BN, ct, c_rows4 != 0, acc);
+    } else {
+      store_piece<TM, TN>(part + sk_piece(sl.team, sl.member, ts, grp, first) * (BM * BN), acc);
+    }
+    it += kt1 - kt0;
+  }
+}
+
+template <typename T, int BM, int BN, int WM, int WN, int S, int CH, int AM, bool CB>
+hipError_t launch_any_kernel(int64_t batch, int M, int N, const AnySteps& st, const void* A, const void* B, void* C,
+                             hipStream_t s, const FusedTables* f, void* part, size_t part_bytes, bool sk) {
+  const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
+  const int64_t ntiles = batch * tiles_m * tiles_n;
+  const dim3 block(64 * WM * WN);
+  const T* a = static_cast<const T*>(A);
+  const T* b = static_cast<const T*>(B);
+  T* c = static_cast<T*>(C);
+  T* pt = static_cast<T*>(part);
+  const int rows4 = f->c_rows4 && (reinterpret_cast<uintptr_t>(c) & 15) == 0 ? 1 : 0;
+  auto kern = k_gemm_any<T, BM, BN, WM, WN, S, CH, AM, CB>;
+  int P = 0, ts = 0;
+  if (sk && part) {
+    // resident workgroups per CU of this instantiation, cached
+    static std::atomic<int> occupancy{0};
+    int occ = occupancy.load(std::memory_order_relaxed);
+    if (occ == 0) {
+      if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kern, 64 * WM * WN, 0) != hipSuccess || occ < 1) occ = 1;
+      occupancy.store(occ, std::memory_order_relaxed);
+    }
+    const SkLaunch sl = sk_launch(ntiles, tiles_n, st.nk, std::min<int64_t>(kSkSlots, static_cast<int64_t>(device_cus()) * occ),
+                                  static_cast<int64_t>(part_bytes / sizeof(T)), static_cast<int64_t>(BM) * BN,
+                                  kSkMinIters);
+    P = sl.P;
+    if (P > 0) ts = sl.ts;
+  }
+  hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(P > 0 ? P : ntiles)), block, 0, s, a, b, c, M, N, st, tiles_m,
+                     tiles_n, ntiles, f->ra, f->ca, f->rc, f->cc, f->rb, f->cb, f->rb ? f->ldb : N, pt, ts, rows4);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || P == 0) return e;
+  const dim3 fgrid = sk_fixup_grid(ntiles, ts, st.nk, P / ts, static_cast<int64_t>(BM) * BN, 64 * WM * WN);
+  if (f->rc)
+    hipLaunchKernelGGL((k_sk_fixup<T, BM, BN, WM, WN, true>), fgrid, block, 0, s, pt, c, M, N, st.nk, tiles_m, tiles_n,
+                       ntiles, ts, P / ts, f->rc, f->cc);
+  else
+    hipLaunchKernelGGL((k_sk_fixup<T, BM, BN, WM, WN, false>), fgrid, block, 0, s, pt, c, M, N, st.nk, tiles_m,
+                       tiles_n, ntiles, ts, P / ts, f->rc, f->cc);
+  return hipGetLastError();
+}
+
+// Tiles in the order of the planner's table (the 96 x 96 one takes 16-byte loads
+// only: with 4-byte loads its sources and accumulators exceed two waves' registers).
+template <typename T, int CH, int AM, bool CB>
+hipError_t launch_any_tile(int tile, int64_t batch, int M, int N, const AnySteps& st, const void* A, const void* B,
+                           void* C, hipStream_t s, const FusedTables* f, void* part, size_t part_bytes, bool sk) {
+  if constexpr (CH == 16)
+    if (tile == 0)
+      return launch_any_kernel<T, 96, 96, 2, 2, 2, CH, AM, CB>(batch, M, N, st, A, B, C, s, f, part, part_bytes, sk);
+  if (tile <= 1)
+    return launch_any_kernel<T, 128, 64, 2, 2, 2, CH, AM, CB>(batch, M, N, st, A, B, C, s, f, part, part_bytes, sk);
+  return launch_any_kernel<T, 64, 64, 2, 2, 2, CH, AM, CB>(batch, M, N, st, A, B, C, s, f, part, part_bytes, sk);
+}
+
+template <typename T, int CH>
+hipError_t launch_any_typed(int tile, int am, bool cb, int64_t batch, int M, int N, const AnySteps& st, const void* A,
+                            const void* B, void* C, hipStream_t s, const FusedTables* f, void* part,
+                            size_t part_bytes, bool sk) {
+  if (cb)
+    return am == 0 ? launch_any_tile<T, CH, 0, true>(tile, batch, M, N, st, A, B, C, s, f, part, part_bytes, sk)
+                   : launch_any_tile<T, CH, 2, true>(tile, batch, M, N, st, A, B, C, s, f, part, part_bytes, sk);
+  return am == 0 ? launch_any_tile<T, CH, 0, false>(tile, batch, M, N, st, A, B, C, s, f, part, part_bytes, sk)
+                 : launch_any_tile<T, CH, 1, false>(tile, batch, M, N, st, A, B, C, s, f, part, part_bytes, sk);
+}
+
+}  // namespace
+}  // namespace symt

@@ -149,6 +149,53 @@ int read_operand(const symt_tensor* t, const GroupDesc& g, OperandDesc* o, const
   return SYMT_OK;
 }
 
+struct AnyChoice {
+  int tile = -1;
+  bool sk = false;
+  size_t partial_bytes = 0;
+  double time = 0;
+};
+// Tiles of the in-place product for any layout (launch order), their efficiency
+// with 16-byte and with 4-byte loads (measured on 8 x (4608 x 4608 x 288): f64 0.86,
+// 0.80, 0.75; 4-byte loads on 3 x (743 x 1113 x 1111): 0.5), and resident workgroups
+// per CU.
+struct AnyTileDesc {
+  const char* name;
+  int bm, bn;
+  double eff16, eff4;
+  int wgs;
+};
+constexpr AnyTileDesc kAnyTiles[] = {
+    {"a96x96s2", 96, 96, 0.85, 0.5, 3}, {"a128x64s2", 128, 64, 0.80, 0.5, 3}, {"a64x64s2", 64, 64, 0.75, 0.5, 3}};
+AnyChoice choose_any(int64_t batch, int64_t M, int64_t N, int64_t kpad, int elem, bool ch16, const char* forced,
+                     int sk_mode) {
+  AnyChoice best;
+  const double per_cu = (elem == 8 ? 78.6e12 : 157.3e12) / 256.0;
+  for (int i = 0; i < static_cast<int>(sizeof(kAnyTiles) / sizeof(kAnyTiles[0])); ++i) {
+    const AnyTileDesc& t = kAnyTiles[i];
+    if (forced && std::strcmp(forced, t.name) != 0) continue;
+    const int64_t tiles = batch * ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
+    const double t_tile = 2.0 * t.bm * t.bn * static_cast<double>(kpad) / ((ch16 ? t.eff16 : t.eff4) * per_cu);
+    for (int sk = 0; sk < 2; ++sk) {
+      if (sk ? sk_mode == 0 : sk_mode == 1) continue;
+      const size_t partial = sk ? 2 * static_cast<size_t>(std::min(kSkSlots, 256 * t.wgs)) * t.bm * t.bn * elem : 0;
+      double time;
+      if (sk) {
+        time = static_cast<double>(tiles) / 256.0 * t_tile / 0.95 + 2.0 * static_cast<double>(partial) / 5e12 + 8e-6;
+      } else {
+        // the fullest CU's tiles, all at once: one or two resident workgroups
+        // leave the matrix pipes waiting at each K-step's barrier (of the tile's
+        // efficiency, 0.57 with one: 6 x (1536 x 768 x 64) on 64 x 64 took 56 us for
+        // 20 us of MFMAs; 0.87 with two)
+        const int64_t rounds = (tiles + 255) / 256;
+        time = static_cast<double>(rounds) * t_tile / (rounds == 1 ? 0.57 : rounds == 2 ? 0.87 : 1.0);
+      }
+      if (best.tile < 0 || time < best.time) best = AnyChoice{i, sk != 0, partial, time};
+    }
+  }
+  return best;
+}
+
 bool is_letter(char c) { return (c >= 'a' && c <= 'z') || (c >= 'A' && c <= 'Z'); }
 
 }  // namespace
@@ -168,6 +215,23 @@ AlignedLayout aligned_layout(int32_t compute, int operand) {
 //  * a K run (the contracted block, fixed sectors) of whole K-steps (16 f64 or
 //    32 f32 rows);
 //  * its last modes J modes whose contiguous run holds whole 16-byte chunks.
+// V's contracted modes affine in U's K order inside a contracted block (row stride *ldb).
+static bool v_rows_affine(const Plan& p, int64_t* ldb) {
+  if (p.v < 1 || p.t < 1) return false;
+  const OperandDesc& V = p.V;
+  int64_t st[kMaxOrder];
+  int64_t a = 1;
+  for (int m = V.n - 1; m >= 0; --m) { st[m] = a; a *= V.dims[m]; }
+  const int64_t stride = st[p.posK_v[p.v - 1]];
+  int64_t expect = stride;
+  for (int i = p.v - 1; i >= 0; --i) {
+    if (st[p.posK_v[i]] != expect) return false;
+    expect *= V.dims[p.posK_v[i]];
+  }
+  *ldb = stride * (p.cplx ? 2 : 1);
+  return true;
+}
+
 bool v_in_place_layout(const Plan& p, int64_t* ldb, bool* chunks) {
   if (p.cplx || p.v < 1 || p.t < 1 || p.subgroups) return false;
   // (with K stepped run by run, every step lies in one run and loads are single
@@ -193,6 +257,70 @@ bool v_in_place_layout(const Plan& p, int64_t* ldb, bool* chunks) {
   *ldb = stride;
   return true;
 }
+
+namespace {
+// The in-place product for any layout (gemm_any.hpp): whether it takes this
+// plan, and its loader and tile.  Binary64 and binary32 plans whose operands are
+// all stored in the compute type and whose W is written in place anyway.
+bool plan_any(Plan* p, int want, bool trailing_k, int64_t run) {
+  if (p->compute == SYMT_COMPUTE_BF16X3 || !(p->fused || p->fused_ua)) return false;
+  if (p->U.dtype != want || p->V.dtype != want || p->W.dtype != want) return false;
+  const int elem = p->compute == SYMT_COMPUTE_F64 ? 8 : 4;
+  const int64_t ve = 16 / elem, bk = 128 / elem, pe = p->cplx ? 2 : 1;
+  auto last_run = [](const OperandDesc& X, const int32_t* pos, int count) {
+    int64_t st[kMaxOrder], a = 1, r = 1;
+    for (int m = X.n - 1; m >= 0; --m) { st[m] = a; a *= X.dims[m]; }
+    for (int i = count - 1; i >= 0 && st[pos[i]] == r; --i) r *= X.dims[pos[i]];
+    return r;
+  };
+  const int64_t i_run = last_run(p->U, p->posI_u, p->s) * pe, j_run = last_run(p->V, p->posJ_v, p->t) * pe;
+  auto& y = p->any;
+  y.am = trailing_k ? 0 : p->cplx ? 2 : 1;
+  int64_t ldb = 0;
+  const char* vip = std::getenv("SYMT_FUSED_V");
+  y.b = !(vip && std::atoi(vip) == 0) && v_rows_affine(*p, &ldb);
+  y.cb = y.b && p->cplx;
+  if (y.am == 2 && !y.cb) return false;
+  // lanes along a tile row read 32 bytes and more of one run
+  const bool a_ok = y.am == 0 || i_run * elem >= 32;
+  if (y.b && j_run * elem < 32) {
+    if (p->cplx && y.am == 2) return false;
+    y.b = y.cb = false;
+  }
+  // one run of A's columns (its contracted modes last) or of V's affine rows holds a K-step
+  y.krun = (y.am == 0 || y.b) && run != p->gk && run % bk != 0 ? static_cast<int32_t>(run) : 0;
+  const bool a16 = y.am == 0 ? run % ve == 0 : y.am == 1 ? i_run % ve == 0 && p->M % ve == 0
+                                                         : i_run % ve == 0 && (pe * p->M) % ve == 0;
+  const bool b16 = (y.b ? j_run % ve == 0 : true) && p->gn % ve == 0;
+  y.ch16 = a16 && b16;
+  const int64_t ksteps = y.krun > 0 ? p->gk / y.krun * ((y.krun + bk - 1) / bk) : (p->gk + bk - 1) / bk;
+  const char* forced = std::getenv("SYMT_GEMM_TILE");
+  const char* sk_env = std::getenv("SYMT_GEMM_SK");
+  const int sk_mode = sk_env ? std::atoi(sk_env) : -1;
+  const AnyChoice c = choose_any(p->g.size, p->M, p->gn, ksteps * bk, elem, y.ch16, forced, sk_mode);
+  if (c.tile < 0) return false;
+  if (!forced) {
+    // against the product the plan takes otherwise and its passes over U and V
+    const GemmChoice g = choose_fp_gemm(p->g.size, p->M, p->gn, p->gk, elem, true, p->a_trans);
+    if (!a_ok || g.tile == kRowsTile || g.tile == kTallKTile) return false;
+    // an aligned form is read and written once, complex rows of V once more
+    const double rate = p->cplx ? 1.3e12 : 3.5e12;
+    double other = g.time;
+    if (p->fused_ua) other += 2.0 * elem * pe * static_cast<double>(p->U.elems) / rate + 8e-6;
+    if (!p->fused_b)
+      other += 2.0 * elem * pe * pe * static_cast<double>(p->V.elems) / rate + (p->cplx ? 16e-6 : 8e-6);
+    double mine = c.time;
+    if (!y.b) mine += 2.0 * elem * pe * pe * static_cast<double>(p->V.elems) / rate + (p->cplx ? 16e-6 : 8e-6);
+    // (a binary32 product that splits K keeps its shorter sums unless much is gained)
+    if (mine > (g.splits > 1 && elem == 4 ? 0.8 : 0.95) * other) return false;
+  }
+  y.tile = c.tile;
+  y.sk = c.sk;
+  y.ldb = ldb;
+  y.partial_bytes = c.partial_bytes;
+  return true;
+}
+}  // namespace
 
 int make_plan(const char* einsum, const symt_group* group, const symt_tensor* u,
               const symt_tensor* v, const symt_tensor* w, int32_t compute, Plan* p,
@@ -612,11 +740,28 @@ int make_plan(const char* einsum, const symt_group* group, const symt_tensor* u,
   if (p->charges) {
     p->bytes_charges = 4 * 2 * static_cast<size_t>(p->g.size) * (p->U.n + p->V.n + p->W.n);
   }
+  if (!plan_any(p, want, trailing_k, run)) p->any = {};   // not taken: no layout of it stays in the plan
+  if (force_steps) {
+    // the three-step path multiplies its aligned forms on the same tile, in the
+    // same K-steps and stream-K shares: the same sums
+    Plan q;
+    if ((rc = make_plan(einsum, group, u, v, w, compute, &q, err))) return rc;
+    p->any = q.any;
+    p->any.am = 0;
+    p->any.b = p->any.cb = false;
+    const int64_t ve = compute == SYMT_COMPUTE_F64 ? 2 : 4;
+    p->any.ch16 = p->gk % ve == 0 && p->gn % ve == 0 && p->any.krun % ve == 0;
+  } else if (p->any.tile >= 0) {
+    // U is not aligned then, nor V where it has tables of its own (4-byte loads take any alignment)
+    const size_t G = static_cast<size_t>(p->g.size);
+    if (p->any.b && !p->fused_b) p->bytes_tables += round_up(8 * G * p->gk, 256) + round_up(8 * G * p->gn, 256);
+    p->workspace = (p->any.b ? 0 : round_up(p->ws_v_al, 256)) + p->bytes_tables;
+  }
   // Room for stream-K pieces when the model would pick it on 16-byte aligned operands.
   if (compute != SYMT_COMPUTE_BF16X3 && p->nq > 0 && p->M > 0 && p->gn > 0 && p->gk > 0) {
     const GemmChoice gc = choose_fp_gemm(p->nq, p->M, p->gn, p->gk,
                                          compute == SYMT_COMPUTE_F64 ? 8 : 4, true, p->a_trans);
-    p->bytes_partial = gc.partial_bytes;
+    p->bytes_partial = std::max(gc.partial_bytes, p->any.partial_bytes);
     p->workspace += round_up(p->bytes_partial, 256);
   }
   p->workspace += round_up(p->bytes_charges, 256);
@@ -740,7 +885,7 @@ GemmChoice choose_among(int64_t batch, int64_t M, int64_t N, int64_t K, int elem
         best.tile = i; best.bm = t.bm; best.bn = t.bn; best.dma = t.dma; best.sk = sk;
         best.splits = 1;
         best.partial_bytes = partial;
-        best_t = time;
+        best.time = best_t = time;
       }
     }
     // Register tiles with few tiles and a long K: split each tile's K-steps into
@@ -760,7 +905,7 @@ GemmChoice choose_among(int64_t batch, int64_t M, int64_t N, int64_t K, int elem
           best.tile = i; best.bm = t.bm; best.bn = t.bn; best.dma = false; best.sk = false;
           best.splits = static_cast<int>(sp);
           best.partial_bytes = partial;
-          best_t = time;
+          best.time = best_t = time;
         }
       }
     }

@@ -152,6 +152,19 @@ struct FusedTables {
   int32_t a_krow = 0;               // 1 (A not K-major): A's K index contiguous in 16-byte aligned runs
   int32_t k_groups = 0;             // 1: every 16-deep group of K lies in one run of A's rows and one
                                     //    affine run of B's rows, B's columns in 16-byte chunks (long-K)
+  // in-place product for any layout (gemm_any.hpp): tile >= 0 runs it
+  int32_t any_tile = -1;
+  int32_t any_am = 0;               // A: 0 rows along K, 1 K-major, 2 K-major complex pairs
+  int32_t any_cb = 0;               // 1: B is a complex V in place (odd real rows formed from the even ones)
+  int32_t any_ch = 4;               // bytes per lane load: 16 (aligned whole chunks) or 4
+  int32_t any_krun = 0;             // > 0: K stepped run by run
+  int32_t any_sk = 0;               // 1: stream-K
+};
+
+// One launch of the in-place product for any layout.
+struct AnyLaunch {
+  int tile, am, ch;
+  bool cb, sk;
 };
 
 struct OperandDesc {
@@ -218,6 +231,15 @@ struct Plan {
   // fused with K runs that do not hold whole K-steps: the register tiles step each
   // run on its own (krun = the run length; 0 = plain K-steps)
   int32_t krun = 0;
+  // The in-place product for any layout takes this plan (any.tile >= 0): U read in
+  // place whatever its layout, V too with any_b (else V_al).  any.ch16: the layouts
+  // hold whole 16-byte chunks (used where the data is 16-byte aligned).
+  struct {
+    int32_t tile = -1, am = 0, krun = 0;
+    bool cb = false, ch16 = false, sk = false, b = false;
+    int64_t ldb = 0;                // V's row stride (reals) with b
+    size_t partial_bytes = 0;
+  } any;
   size_t bytes_u_al = 0, bytes_v_al = 0, bytes_w_al = 0, workspace = 0;
   size_t ws_u_al = 0, ws_v_al = 0, ws_w_al = 0;   // their regions in the contraction's workspace
   size_t bytes_tables = 0;          // fused (or fused_ua): four offset tables, six with fused_b
@@ -255,6 +277,7 @@ struct GemmChoice {
                               // tiles evenly; tiles cut between two of them are summed after
   int splits = 1;             // register tiles: each tile's K-steps in this many runs, summed after
   size_t partial_bytes = 0;   // workspace for stream-K pieces or split partial tiles
+  double time = 0;            // the model's time in seconds (0: not a tile of the table)
 };
 // Most persistent workgroups of a stream-K product: 256 CUs x up to 3 resident
 // workgroups (the two-stage 96 x 96 tile).  The planner sizes the pieces

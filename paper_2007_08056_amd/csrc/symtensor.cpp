@@ -198,6 +198,17 @@ int do_gemm(symt_ctx* ctx, int compute, int64_t batch, int64_t m, int64_t k, int
   return rc ? ctx_fail(ctx, rc, err) : SYMT_OK;
 }
 
+// The in-place product's launch (gemm_any.hpp); chunks: 16-byte loads.
+void set_any(const Plan& p, bool chunks, symt::FusedTables* f) {
+  f->any_tile = p.any.tile;
+  f->ldb = p.any.ldb;
+  f->any_am = p.any.am;
+  f->any_cb = p.any.cb ? 1 : 0;
+  f->any_krun = p.any.krun;
+  f->any_sk = p.any.sk ? 1 : 0;
+  f->any_ch = chunks ? 16 : 4;
+}
+
 // Fused path: offset tables of U's rows and columns and of W's rows and
 // columns, V aligned, then one product that reads U and writes W in place.
 constexpr size_t kTableBudget = size_t(1) << 30;   // device bytes of cached tables per context
@@ -250,15 +261,19 @@ int do_fused(symt_ctx* ctx, const Plan& p, char* base, hipStream_t s, const int3
   const size_t G = static_cast<size_t>(p.g.size);
   // U aligned first (fused_ua): U_al, then the regions of the fused product
   void* ual = base;
-  if (p.fused_ua) base += round_up(p.ws_u_al, 256);
+  const bool any = p.any.tile >= 0;          // U in place whatever its layout
+  const bool ua = p.fused_ua && !any;
+  if (ua) base += round_up(p.ws_u_al, 256);
   void* val = base;
-  int64_t* ra = reinterpret_cast<int64_t*>(base + round_up(p.ws_v_al, 256));
+  // (the in-place product reads V through its tables whatever its alignment: no V_al then)
+  int64_t* ra = reinterpret_cast<int64_t*>(base + (any && p.any.b ? 0 : round_up(p.ws_v_al, 256)));
   int64_t* ca = reinterpret_cast<int64_t*>(reinterpret_cast<char*>(ra) + round_up(8 * G * p.M, 256));
   int64_t* rc = reinterpret_cast<int64_t*>(reinterpret_cast<char*>(ca) + round_up(8 * G * p.gk, 256));
   int64_t* cc = reinterpret_cast<int64_t*>(reinterpret_cast<char*>(rc) + round_up(8 * G * p.M, 256));
   int64_t* rb = reinterpret_cast<int64_t*>(reinterpret_cast<char*>(cc) + round_up(8 * G * p.gn, 256));
   int64_t* cb = reinterpret_cast<int64_t*>(reinterpret_cast<char*>(rb) + round_up(8 * G * p.gk, 256));
-  char* part = p.fused_b ? reinterpret_cast<char*>(cb) + round_up(8 * G * p.gn, 256)
+  const bool tab_v = p.fused_b || (any && p.any.b);   // tables of V too
+  char* part = tab_v ? reinterpret_cast<char*>(cb) + round_up(8 * G * p.gn, 256)
                          : reinterpret_cast<char*>(rb);
   // 16-byte loads of A need every row's K run to start 16-byte aligned
   // (K stepped run by run: a run of whole vectors keeps every step's valid part whole;
@@ -269,15 +284,15 @@ int do_fused(symt_ctx* ctx, const Plan& p, char* base, hipStream_t s, const int3
   if (p.a_trans) vec = aligned16(p.U.data) && p.a_chunks ? 2 : 1;
   // V in place: its column chunks take 16-byte loads (global-to-LDS tiles, and
   // register tiles whose loads are vectors), so V must be 16-byte aligned
-  const bool fb = p.fused_b && (p.krun > 0 || aligned16(p.V.data));
+  const bool fb = any ? p.any.b : p.fused_b && (p.krun > 0 || aligned16(p.V.data));
   // vector loads of B in place need 16-byte aligned, whole column chunks
   if (fb && vec > 1 && !(aligned16(p.V.data) && p.fused_b_chunks)) vec = 1;
   std::string err;
   // the tables: cached on the context (all of the plan's tables, built once), or
   // in the workspace (the ones this call reads, built every call)
-  const int n_plan = p.fused_b ? 6 : 4;
+  const int n_plan = tab_v ? 6 : 4;
   char* const t0 = reinterpret_cast<char*>(ra);
-  const size_t plan_bytes = static_cast<size_t>((p.fused_b ? reinterpret_cast<char*>(cb) +
+  const size_t plan_bytes = static_cast<size_t>((tab_v ? reinterpret_cast<char*>(cb) +
                                                                  round_up(8 * G * p.gn, 256)
                                                            : reinterpret_cast<char*>(rb)) - t0);
   bool build = true;
@@ -300,7 +315,7 @@ int do_fused(symt_ctx* ctx, const Plan& p, char* base, hipStream_t s, const int3
       int64_t total = 0;
       b.n = n_build;
       for (int t = 0; t < b.n; ++t) {
-        if (p.fused_ua && ops[t] == 0 && !p.bf16_wide_fa)   // U_al: row m at (q M + m) gk, column k at k
+        if (ua && ops[t] == 0 && !p.bf16_wide_fa)   // U_al: row m at (q M + m) gk, column k at k
           b.t[t] = t == 0 ? symt::affine_offsets(p, p.M, p.M * p.gk, p.gk) : symt::affine_offsets(p, p.gk, 0, 1);
         else
           b.t[t] = symt::make_offsets(p, ops[t], t % 2 == 0);
@@ -320,8 +335,8 @@ int do_fused(symt_ctx* ctx, const Plan& p, char* base, hipStream_t s, const int3
   if (rc_) return ctx_fail(ctx, rc_, err);
   // split-bf16 on the 256 x 256 wide tile: binary32 U read in place (16-byte aligned)
   const bool wide_fa = p.bf16_wide_fa && aligned16(p.U.data);
-  if (p.fused_ua && (rc_ = clear_k_pad(ctx, p, ual, fb ? nullptr : val, s))) return rc_;
-  if (p.fused_ua && !wide_fa && (rc_ = do_align(ctx, p, 0, ual, s, true, chg[0]))) return rc_;
+  if (ua && (rc_ = clear_k_pad(ctx, p, ual, fb ? nullptr : val, s))) return rc_;
+  if (ua && !wide_fa && (rc_ = do_align(ctx, p, 0, ual, s, true, chg[0]))) return rc_;
   if (!fb && (rc_ = do_align(ctx, p, 1, val, s, true, chg[1]))) return rc_;
   symt::FusedTables f{ra, ca, rc, cc, vec};
   // split-bf16 on aligned U: A and B come from the hi/lo planes, only W's tables apply
@@ -354,8 +369,9 @@ int do_fused(symt_ctx* ctx, const Plan& p, char* base, hipStream_t s, const int3
     f.cb = cb;
     f.ldb = p.ldb;
   }
-  return do_gemm(ctx, p.compute, p.g.size, p.M, p.fused_ua ? p.kpad : p.gk, p.gn,
-                 p.fused_ua && !wide_fa ? ual : p.U.data,
+  if (any) set_any(p, p.any.ch16 && aligned16(p.U.data) && (!fb || aligned16(p.V.data)), &f);
+  return do_gemm(ctx, p.compute, p.g.size, p.M, ua ? p.kpad : p.gk, p.gn,
+                 ua && !wide_fa ? ual : p.U.data,
                  fb ? p.V.data : val,
                  p.W.data, s, &f,
                  p.bytes_partial ? part : nullptr, p.bytes_partial, 0, 0, p.bf16_il);
@@ -594,7 +610,10 @@ int contract_planned(symt_ctx* ctx, const Plan& p, void* workspace, size_t works
   if ((rc = do_align(ctx, p, 1, val, s, true, chg[1]))) return rc;
   // the workspace holds the nq live slices in order: one batched product of them
   // (none live: no block of W is reached, and the unalign step clears W)
-  if (p.nq > 0 && (rc = do_gemm(ctx, p.compute, p.nq, p.M, p.kpad, p.gn, ual, val, wal, s, nullptr,
+  symt::FusedTables f{};
+  if (p.any.tile >= 0) set_any(p, p.any.ch16, &f);
+  if (p.nq > 0 && (rc = do_gemm(ctx, p.compute, p.nq, p.M, p.kpad, p.gn, ual, val, wal, s,
+                                p.any.tile >= 0 ? &f : nullptr,
                                 p.bytes_partial ? part : nullptr, p.bytes_partial, 0, 0, p.bf16_il)))
     return rc;
   if ((rc = do_unalign(ctx, p, wal, s, true, chg[2]))) return rc;
