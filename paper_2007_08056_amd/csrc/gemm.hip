@@ -1259,9 +1259,9 @@ hipError_t launch_fp_tile(int idx, int vec, int64_t batch, int M, int N, int K, 
 
 }  // namespace
 
-// Row-streaming product for K and N at most 64 (gemm_rows.hip).
+// Row-streaming product for K and N (swap: K and M) at most 64 (gemm_rows.hip).
 hipError_t launch_gemm_rows(bool f64, int64_t batch, int M, int N, int K, const void* A, const void* B, void* C,
-                            hipStream_t s, const FusedTables* f);
+                            hipStream_t s, const FusedTables* f, bool swap);
 // Long-K product for M and N at most 64 (gemm_tallk.hip).
 hipError_t launch_gemm_tallk(bool f64, int64_t batch, int M, int N, int K, const void* A, const void* B, void* C,
                              hipStream_t s, const FusedTables* f, void* part, int ranges);
@@ -1381,7 +1381,7 @@ int launch_sector_gemm(int compute, int64_t batch, int64_t m, int64_t k, int64_t
       return SYMT_OK;
     }
     if ((!gc.sk && gc.splits <= 1) || (reinterpret_cast<uintptr_t>(part) & 15) != 0) part = nullptr;
-    e = gc.tile == kRowsTile ? launch_gemm_rows(f64, batch, M, N, K, A, B, C, stream, fused)
+    e = gc.tile == kRowsTile ? launch_gemm_rows(f64, batch, M, N, K, A, B, C, stream, fused, rows_swapped(M, N))
         : f64 ? launch_fp_tile<double>(gc.tile, vec, batch, M, N, K, A, B, C, stream, fused, part, part_bytes,
                                      gc.splits)
             : launch_fp_tile<float>(gc.tile, vec, batch, M, N, K, A, B, C, stream, fused, part, part_bytes,

@@ -694,6 +694,9 @@ int make_plan(const char* einsum, const symt_group* group, const symt_tensor* u,
     for (int i = p->s - 1; i >= 0 && st[p->posI_w[i]] == r_run; --i) r_run *= p->W.dims[p->posI_w[i]];
     p->w_col_run = w_run;
     p->w_row_run = r_run;
+    a = 1;
+    for (int m = p->V.n - 1; m >= 0; --m) { st[m] = a; a *= p->V.dims[m]; }
+    for (int i = p->t - 1; i >= 0 && st[p->posJ_v[i]] == p->v_col_run; --i) p->v_col_run *= p->V.dims[p->posJ_v[i]];
   }
   p->fused_ua = !p->fused && !force_steps && !p->subgroups && p->nq == p->g.size &&
                 (!w || p->W.dtype == (p->cplx ? want : w_want) ||
@@ -854,6 +857,19 @@ GemmChoice choose_among(int64_t batch, int64_t M, int64_t N, int64_t K, int elem
     best.tile = kRowsTile;
     best.bm = 32;
     best.bn = static_cast<int>(N);
+    return best;
+  }
+  // the same with the long side along N (a small matrix times a large tensor): the
+  // transposed product (every operand's tables serve in the other role).  From 16384
+  // rows in all (4 x (32 x 32 x 4160) f64 15.4 -> 12.4 us), binary32 with K past 32
+  // from 49152: its blocks of 64 rows are too few before that (4 x (57 x 57 x 6560):
+  // 14.3 us on register tiles, 15.3 here; at 4 x (57 x 57 x 16640) 18.1 and 16.8).
+  const int64_t rows_min = elem == 4 && K > 32 ? 49152 : 16384;
+  if (K >= 1 && K <= 64 && rows_swapped(M, N) && M >= 1 && batch >= 1 && batch <= 65535 &&
+      (rows_forced || (!forced && batch * N >= rows_min))) {
+    best.tile = kRowsTile;
+    best.bm = static_cast<int>(M);
+    best.bn = 32;
     return best;
   }
   double best_t = 0;

@@ -152,6 +152,10 @@ struct FusedTables {
   int32_t a_krow = 0;               // 1 (A not K-major): A's K index contiguous in 16-byte aligned runs
   int32_t k_groups = 0;             // 1: every 16-deep group of K lies in one run of A's rows and one
                                     //    affine run of B's rows, B's columns in 16-byte chunks (long-K)
+  // contiguous runs along V's and W's columns (in reals), and whether W's lanes go along them
+  // (row-streaming product with its rows along N)
+  int64_t v_col_run = 1, w_col_run = 1;
+  int32_t c_cols = 0;
   // in-place product for any layout (gemm_any.hpp): tile >= 0 runs it
   int32_t any_tile = -1;
   int32_t any_am = 0;               // A: 0 rows along K, 1 K-major, 2 K-major complex pairs
@@ -227,6 +231,7 @@ struct Plan {
   // W's contiguous runs at its end: of its output modes from V (columns of the
   // product) and of those from U (rows); one of them is 1
   int64_t w_col_run = 1, w_row_run = 1;
+  int64_t v_col_run = 1;            // V's contiguous run of its output modes
   int64_t u_k_run = 1;              // U's contiguous run of its contracted index (in elements)
   // fused with K runs that do not hold whole K-steps: the register tiles step each
   // run on its own (krun = the run length; 0 = plain K-steps)
@@ -285,8 +290,10 @@ struct GemmChoice {
 // launch runs no more workgroups than that buffer holds.
 constexpr int kSkSlots = 768;
 // GemmChoice::tile of the row-streaming product (K and N at most 64, many rows):
-// past the tile table.
+// past the tile table.  The product's long side is M, or N where M is at most 64
+// (rows_swapped).
 constexpr int kRowsTile = 64;
+inline bool rows_swapped(int64_t M, int64_t N) { return N > 64 && M <= 64; }
 // GemmChoice::tile of the long-K product with M and N at most 64 (GemmChoice::
 // splits = its K ranges per slice, partial_bytes = their partial outputs).
 constexpr int kTallKTile = 65;

@@ -349,6 +349,10 @@ int do_fused(symt_ctx* ctx, const Plan& p, char* base, hipStream_t s, const int3
   // W written in place with its rows contiguous (and not its columns): the
   // row-streaming product stores lanes along rows
   f.c_trans = !p.cplx && p.w_row_run >= 16 && p.w_col_run < 8 ? 1 : 0;
+  // columns contiguous in V and W (real operands): the row-streaming product along N
+  f.c_cols = !p.cplx && p.w_col_run >= 16 ? 1 : 0;
+  f.v_col_run = p.cplx ? 1 : p.v_col_run;
+  f.w_col_run = p.cplx ? 1 : p.w_col_run;
   // U's K index contiguous (U_al, or runs of 16 and more in U): the long-K
   // product loads A along K
   f.a_klanes = p.fused_ua || p.u_k_run >= 16 ? 1 : 0;
