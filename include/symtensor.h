@@ -337,6 +337,21 @@ int symtensor_contract(symt_ctx* ctx, const char* einsum, const symt_group* grou
                        const symt_tensor* u, const symt_tensor* v, const symt_tensor* w,
                        int32_t compute, void* workspace, size_t workspace_bytes, void* stream);
 
+/* A contraction planned once and run many times: symtensor_prepare validates and
+ * plans it as symtensor_contract would (operand `data` pointers are not read;
+ * the tuning variables are read here), and symtensor_contract_prepared runs it on
+ * the given operands with symtensor_contract's results, checks and errors (the
+ * workspace is info.workspace_bytes of symtensor_plan).  The handle belongs to
+ * the context it was made on, keeps that plan's offset tables alive (counted in
+ * the context's 1 GiB), and is given back with symtensor_release (NULL is a
+ * no-op) before the context is destroyed. */
+typedef struct symt_prepared symt_prepared;
+int symtensor_prepare(symt_ctx* ctx, const char* einsum, const symt_group* group, const symt_tensor* u,
+                      const symt_tensor* v, const symt_tensor* w, int32_t compute, symt_prepared** out);
+int symtensor_contract_prepared(const symt_prepared* handle, const void* u, const void* v, void* w, void* workspace,
+                                size_t workspace_bytes, void* stream);
+int symtensor_release(symt_prepared* handle);
+
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same
  * contraction as symtensor_contract, with the same arguments, results and

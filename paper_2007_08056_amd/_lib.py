@@ -8,6 +8,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import sys
 from ctypes import POINTER, c_char, c_char_p, c_double, c_int, c_int32, c_int64, c_size_t, c_void_p
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -38,6 +39,7 @@ EXPORTED = (
     "symtensor_contract", "symtensor_align", "symtensor_unalign", "symtensor_sector_gemm",
     "symtensor_sector_gemm_workspace_size", "symtensor_set_timing", "symtensor_read_timing",
     "symtensor_status_string", "symtensor_last_error", "symtensor_contract_static",
+    "symtensor_prepare", "symtensor_contract_prepared", "symtensor_release",
 )
 SYMT_STATIC_WORKSPACE_BYTES = 128 << 20
 
@@ -84,6 +86,11 @@ def _load():
                                        c_int32, c_void_p, c_size_t, c_void_p]
     lib.symtensor_contract_static.argtypes = [c_void_p, c_char_p, p_group, p_tensor, p_tensor, p_tensor,
                                               c_int32, c_void_p]
+    lib.symtensor_prepare.argtypes = [c_void_p, c_char_p, p_group, p_tensor, p_tensor, p_tensor, c_int32,
+                                      POINTER(c_void_p)]
+    lib.symtensor_contract_prepared.argtypes = [c_void_p, c_void_p, c_void_p, c_void_p, c_void_p, c_size_t,
+                                                c_void_p]
+    lib.symtensor_release.argtypes = [c_void_p]
     lib.symtensor_align.argtypes = [c_void_p, c_char_p, p_group, p_tensor, p_tensor, p_tensor,
                                     c_int32, c_int32, c_void_p, c_size_t, c_void_p]
     lib.symtensor_unalign.argtypes = [c_void_p, c_char_p, p_group, p_tensor, p_tensor, p_tensor,
@@ -165,6 +172,29 @@ def context(device: int):
         ctx = h
         _CTX[device] = ctx
     return ctx
+
+
+class Prepared:
+    """A contraction planned on one device's context (symtensor_prepare): run it with data pointers."""
+
+    def __init__(self, device: int, einsum: str, group: SymtGroup, u: TensorDesc, v: TensorDesc, w: TensorDesc,
+                 compute: int):
+        self.ctx = context(device)
+        h = c_void_p()
+        check(LIB.symtensor_prepare(self.ctx, einsum.encode(), ctypes.byref(group), u.ref, v.ref, w.ref, int(compute),
+                                    ctypes.byref(h)), self.ctx)
+        self.handle = h.value
+
+    def run(self, u: int, v: int, w: int, workspace: int, workspace_bytes: int, stream: int):
+        code = LIB.symtensor_contract_prepared(self.handle, u, v, w, workspace, workspace_bytes, stream)
+        if code:
+            raise SymtError(code, last_error(self.ctx))
+
+    def __del__(self):
+        handle, self.handle = getattr(self, "handle", None), None
+        # (at interpreter exit the HIP runtime may be gone: the process returns the memory)
+        if handle and LIB is not None and not sys.is_finalizing():
+            LIB.symtensor_release(handle)
 
 
 def plan(einsum: str, group: SymtGroup, u: TensorDesc, v: TensorDesc, w: TensorDesc | None,

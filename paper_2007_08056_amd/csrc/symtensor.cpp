@@ -3,6 +3,7 @@
 // product, unalign W).  Declarations and contracts are in include/symtensor.h.
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <cstdint>
 #include <cstdlib>
 #include <cstring>
@@ -41,15 +42,19 @@ using symt::Plan;
 // wait for that build (an event) instead of rebuilding.
 struct TableCache {
   std::mutex mu;
+  std::shared_ptr<std::atomic<size_t>> held;   // the context's count of cached table bytes
   void* dev = nullptr;
-  size_t bytes = 0;
+  size_t bytes = 0;                            // counted in `held` while dev is set
   hipEvent_t ready = nullptr;
   bool built = false;
   bool done = false;       // the build has completed: no wait needed
   bool refused = false;    // no device memory (or over the context's budget): use the workspace
   ~TableCache() {
     if (ready) (void)hipEventDestroy(ready);
-    if (dev) (void)hipFree(dev);
+    if (dev) {
+      (void)hipFree(dev);
+      *held -= bytes;
+    }
   }
 };
 
@@ -68,7 +73,15 @@ struct symt_ctx {
   // planning input except the data pointers (see plan_key), with their tables.
   std::mutex plan_mu;
   std::unordered_map<std::string, CachedPlan> plans;
-  size_t table_bytes = 0;  // device bytes held by cached tables (under plan_mu)
+  // device bytes held by cached tables (prepared contractions may outlive the plan cache)
+  std::shared_ptr<std::atomic<size_t>> table_bytes = std::make_shared<std::atomic<size_t>>(0);
+};
+
+// A planned contraction kept by the caller (symtensor_prepare).
+struct symt_prepared {
+  symt_ctx* ctx;
+  Plan plan;
+  std::shared_ptr<TableCache> tables;
 };
 
 namespace {
@@ -226,20 +239,17 @@ void* cached_tables(symt_ctx* ctx, TableCache* tc, size_t bytes, hipStream_t s, 
     return nullptr;
   }
   if (!tc->dev && !tc->refused) {
-    bool room;
-    {
-      std::lock_guard<std::mutex> lock(ctx->plan_mu);
-      room = ctx->table_bytes + bytes <= kTableBudget;
-      if (room) ctx->table_bytes += bytes;
-    }
+    const bool room = ctx->table_bytes->fetch_add(bytes) + bytes <= kTableBudget;
     if (!room || hipMalloc(&tc->dev, bytes) != hipSuccess ||
         hipEventCreateWithFlags(&tc->ready, hipEventDisableTiming) != hipSuccess) {
       (void)hipGetLastError();
       if (tc->dev) (void)hipFree(tc->dev);
       tc->dev = nullptr;
       tc->refused = true;
+      *ctx->table_bytes -= bytes;
       return nullptr;
     }
+    tc->held = ctx->table_bytes;
     tc->bytes = bytes;
   }
   if (!tc->dev || tc->bytes != bytes) return nullptr;
@@ -464,7 +474,6 @@ int plan_for(symt_ctx* ctx, const char* einsum, const symt_group* group, const s
       // (a call still holding a plan's tables keeps them alive until it returns;
       // freeing device memory waits for the device)
       ctx->plans.clear();
-      ctx->table_bytes = 0;
     }
     auto tc = std::make_shared<TableCache>();
     ctx->plans.emplace(std::move(key), CachedPlan{*p, tc});
@@ -637,6 +646,43 @@ int symtensor_contract(symt_ctx* ctx, const char* einsum, const symt_group* grou
   int rc = plan_for(ctx, einsum, group, u, v, w, compute, &p, &tables);
   if (rc) return rc;
   return contract_planned(ctx, p, workspace, workspace_bytes, stream, tables.get());
+}
+
+int symtensor_prepare(symt_ctx* ctx, const char* einsum, const symt_group* group, const symt_tensor* u,
+                      const symt_tensor* v, const symt_tensor* w, int32_t compute, symt_prepared** out) {
+  if (!ctx) return ctx_fail(nullptr, SYMT_EINVAL, "context is NULL");
+  if (!out) return ctx_fail(ctx, SYMT_EINVAL, "out is NULL");
+  *out = nullptr;
+  if (!w) return ctx_fail(ctx, SYMT_EINVAL, "output descriptor is NULL");
+  try {
+    auto h = std::make_unique<symt_prepared>();
+    h->ctx = ctx;
+    const int rc = plan_for(ctx, einsum, group, u, v, w, compute, &h->plan, &h->tables);
+    if (rc) return rc;
+    *out = h.release();
+    return SYMT_OK;
+  } catch (const std::exception& e) {
+    return ctx_fail(ctx, SYMT_EUNSUPPORTED, e.what());
+  }
+}
+
+int symtensor_contract_prepared(const symt_prepared* h, const void* u, const void* v, void* w, void* workspace,
+                                size_t workspace_bytes, void* stream) {
+  if (!h) return ctx_fail(nullptr, SYMT_EINVAL, "prepared contraction is NULL");
+  try {
+    Plan p = h->plan;
+    p.U.data = const_cast<void*>(u);
+    p.V.data = const_cast<void*>(v);
+    p.W.data = w;
+    return contract_planned(h->ctx, p, workspace, workspace_bytes, stream, h->tables.get());
+  } catch (const std::exception& e) {
+    return ctx_fail(h->ctx, SYMT_EUNSUPPORTED, e.what());
+  }
+}
+
+int symtensor_release(symt_prepared* h) {
+  delete h;
+  return SYMT_OK;
 }
 
 int symtensor_contract_static(symt_ctx* ctx, const char* einsum, const symt_group* group,

@@ -99,7 +99,7 @@ class SymTensor:
 
     def key(self):
         """Every descriptor field but the data pointer (a planning cache key)."""
-        return (self.signs, self.charge, self.dims, self.data.dtype, self.mode_charges, self.sectors)
+        return (self.signs, self.charge, self.data.shape, self.data.dtype, self.mode_charges, self.sectors)
 
     def table(self, m):
         G = group_size(self.group)
@@ -113,47 +113,96 @@ def _check_dense(t: torch.Tensor):
         raise ValueError("operand data must be contiguous")
 
 
+# (the raw handle: a torch.cuda.Stream object costs microseconds per call)
 def _stream(device) -> int:
-    return torch.cuda.current_stream(device).cuda_stream
+    return torch._C._cuda_getCurrentRawStream(device.index or 0)
 
 
 def _code(compute: str, steps: bool) -> int:
     return L.COMPUTE[compute] | (L.SYMT_FLAG_STEPS if steps else 0)
 
 
-# Planned contractions: key -> (group, descriptors of u, v, w, plan info).  The
-# descriptors are reused with their data pointers replaced on every call, so a
-# contraction is planned once per key here (and once per key in the library's
-# context, which caches its own plans).
+# Planned contractions, one _Planned per key (subscripts, compute mode and every
+# descriptor field): planned once here and once in the library's context, however
+# often they run.
 _PLANS: dict = {}
+# what einsum derives from its operands' fields (_Einsum), by the same fields
+_EINSUMS: dict = {}
 _MAX_PLANS = 1024
 
 
-# Tuning variables the library's planner reads (include/symtensor.h): part of every key.
-_TUNING_VARS = ("SYMT_FUSED_V", "SYMT_GEMM_TILE", "SYMT_GEMM_SK")
+# Tuning variables the library's planner reads (include/symtensor.h): a planned
+# contraction keeps one plan for each combination of their values.
+_TUNING_VARS = ("SYMT_FUSED_V", "SYMT_GEMM_TILE", "SYMT_GEMM_SK", "SYMT_BF16_IL", "SYMT_BF16_FA")
 
 
-def _planned(subscripts, u, v, w, code):
-    key = (subscripts, u.group, u.key(), v.key(), w.key() if w is not None else None, code,
-           tuple(os.environ.get(k) for k in _TUNING_VARS))
-    ent = _PLANS.get(key)
-    if ent is None:
+def _tuning():
+    # (os.environ.get encodes and decodes every name and value: the mapping's bytes suffice)
+    return tuple(map(_ENV_GET, _ENV_KEYS))
+
+
+try:
+    _ENV_GET = os.environ._data.get
+    _ENV_KEYS = tuple(os.environ.encodekey(k) for k in _TUNING_VARS)
+except AttributeError:
+    _ENV_GET, _ENV_KEYS = os.environ.get, _TUNING_VARS
+
+
+class _Planned:
+    """One contraction's descriptors, its plan info per tuning, and its prepared handle per device and tuning."""
+
+    def __init__(self, subscripts, u, v, w, code):
         if u.group != v.group:
             raise ValueError("operands use different groups")
-        g = L.make_group(u.group)
-        du, dv = u.desc(), v.desc()
-        dw = w.desc() if w is not None else None
-        info = L.plan(subscripts, g, du, dv, dw, code)
+        self.subscripts, self.code = subscripts, code
+        self.group = L.make_group(u.group)
+        # (the descriptors' data pointers are not read by planning)
+        self.du, self.dv = u.desc(), v.desc()
+        self.dw = w.desc() if w is not None else None
+        self.infos = {}
+        self.handles = {}
+
+    def info(self, tuning):
+        info = self.infos.get(tuning)
+        if info is None:
+            info = self.infos[tuning] = L.plan(self.subscripts, self.group, self.du, self.dv, self.dw, self.code)
+        return info
+
+    def run(self, ud, vd, wd, workspace=None):
+        """wd <- the contraction of ud and vd (operands on one device, contiguous, of the planned shapes)."""
+        tuning = _tuning()
+        dev = ud.device
+        index = dev.index or 0
+        got = self.handles.get((index, tuning))
+        if got is None:
+            need = self.info(tuning).workspace_bytes
+            got = self.handles[index, tuning] = (
+                L.Prepared(index, self.subscripts, self.group, self.du, self.dv, self.dw, self.code), need)
+        handle, need = got
+        if workspace is None or workspace.numel() < need:
+            workspace = torch.empty(need or 1, dtype=torch.uint8, device=dev)
+        handle.run(ud.data_ptr(), vd.data_ptr(), wd.data_ptr(), workspace.data_ptr(), workspace.numel(),
+                   torch._C._cuda_getCurrentRawStream(index))
+
+
+def _planned(subscripts, u, v, w, code) -> _Planned:
+    key = (subscripts, u.group, u.key(), v.key(), w.key() if w is not None else None, code)
+    ent = _PLANS.get(key)
+    if ent is None:
+        ent = _Planned(subscripts, u, v, w, code)
+        ent.info(_tuning())                      # (an invalid contraction raises here and is not kept)
         if len(_PLANS) >= _MAX_PLANS:
+            # (einsum's entries hold planned contractions too: both go, or their tables stay)
             _PLANS.clear()
-        ent = _PLANS[key] = (g, du, dv, dw, info)
+            _EINSUMS.clear()
+        _PLANS[key] = ent
     return ent
 
 
 def plan(subscripts: str, u: SymTensor, v: SymTensor, compute: str = "f64", w: SymTensor | None = None,
          steps: bool = False):
     """Shapes, flops, workspace and derived output rule of a contraction (host only)."""
-    return _planned(subscripts, u, v, w, _code(compute, steps))[4]
+    return _planned(subscripts, u, v, w, _code(compute, steps)).info(_tuning())
 
 
 def derived_charges(subscripts: str, u: SymTensor, v: SymTensor):
@@ -202,17 +251,7 @@ def contract_into(subscripts: str, u: SymTensor, v: SymTensor, w: SymTensor, com
     """
     for t in (u.data, v.data, w.data):
         _check_dense(t)
-    dev = u.data.device
-    code = _code(compute, steps)
-    g, du, dv, dw, info = _planned(subscripts, u, v, w, code)
-    for d, t in ((du, u.data), (dv, v.data), (dw, w.data)):
-        d.set_data(t.data_ptr() if t.numel() else None)
-    if workspace is None or workspace.numel() < info.workspace_bytes:
-        workspace = torch.empty(max(1, info.workspace_bytes), dtype=torch.uint8, device=dev)
-    ctx = L.context(dev.index or 0)
-    L.check(L.LIB.symtensor_contract(ctx, subscripts.encode(), ctypes.byref(g), du.ref, dv.ref,
-                                     dw.ref, code, ctypes.c_void_p(workspace.data_ptr()),
-                                     workspace.numel(), ctypes.c_void_p(_stream(dev))), ctx)
+    _planned(subscripts, u, v, w, _code(compute, steps)).run(u.data, v.data, w.data, workspace)
     return w
 
 
@@ -222,38 +261,86 @@ def _swap(subscripts):
     return tu, tv, tw
 
 
+def _wrap(data, signs, charge, group, mode_charges, sectors) -> SymTensor:
+    """A SymTensor of already checked fields (no second validation)."""
+    t = SymTensor.__new__(SymTensor)
+    t.data, t.signs, t.charge, t.group, t.mode_charges, t.sectors = data, signs, charge, group, mode_charges, sectors
+    return t
+
+
+class _Einsum:
+    """What einsum derives once per key: the output's label and shape, the planned contraction and, when a
+    backward pass first asks for them, its two gradient contractions."""
+
+    def __init__(self, subscripts, u, v, compute):
+        info = plan(subscripts, u, v, compute)
+        tu, tv, tw = _swap(subscripts)
+        dims = [u.dims[tu.index(m)] if m in tu else v.dims[tv.index(m)] for m in tw]
+        G = group_size(u.group)
+        ws = derived_sectors(subscripts, u, v)
+        self.shape = tuple(list((ws or (G,) * len(tw))[: len(tw) - 1]) + dims)
+        wc = derived_charges(subscripts, u, v)
+        self.subscripts, self.compute = subscripts, compute
+        self.meta_u = (u.signs, u.charge, u.group, u.mode_charges, u.sectors)
+        self.meta_v = (v.signs, v.charge, v.group, v.mode_charges, v.sectors)
+        self.meta_w = (info.w_signs.decode(), info.w_charge, u.group, wc, ws)
+        # the output as a descriptor: a tensor of its shape that holds nothing
+        w = _wrap(torch.empty(self.shape, dtype=u.data.dtype, device="meta"), *self.meta_w)
+        self.forward = _planned(subscripts, u, v, w, _code(compute, False))
+        self.grad_u = self.grad_v = None
+
+    def contract(self, ud, vd):
+        _check_dense(ud)
+        _check_dense(vd)
+        wd = torch.empty(self.shape, dtype=ud.dtype, device=ud.device)
+        self.forward.run(ud, vd, wd)
+        return wd
+
+    def gradient(self, operand, gw, other, out):
+        """out <- the gradient contraction of operand 0 (u) or 1 (v)."""
+        for t in (gw, other, out):
+            _check_dense(t)
+        call = self.grad_v if operand else self.grad_u
+        if call is None:
+            tu, tv, tw = _swap(self.subscripts)
+            dw, x = _wrap(gw, *self.meta_w), _wrap(out, *(self.meta_v if operand else self.meta_u))
+            y = _wrap(other, *(self.meta_u if operand else self.meta_v))
+            code = _code(self.compute, False)
+            if operand:
+                call = self.grad_v = _planned(f"{tu},{tw}->{tv}", y, dw, x, code)
+            else:
+                call = self.grad_u = _planned(f"{tw},{tv}->{tu}", dw, y, x, code)
+        if operand:
+            call.run(other, gw, out)
+        else:
+            call.run(gw, other, out)
+        return out
+
+
 class _Contract(torch.autograd.Function):
     @staticmethod
-    def forward(ctx, subscripts, meta_u, meta_v, meta_w, compute, ud, vd):
-        u = SymTensor(ud, *meta_u)
-        v = SymTensor(vd, *meta_v)
-        w = SymTensor(torch.empty(meta_w[5], dtype=ud.dtype, device=ud.device), *meta_w[:5])
-        contract_into(subscripts, u, v, w, compute)
+    def forward(ctx, call, ud, vd):
+        wd = call.contract(ud, vd)
         ctx.save_for_backward(ud, vd)
-        ctx.meta = (subscripts, meta_u, meta_v, meta_w, compute)
-        return w.data
+        ctx.call = call
+        return wd
 
     @staticmethod
     def backward(ctx, gw):
-        subscripts, meta_u, meta_v, meta_w, compute = ctx.meta
+        call = ctx.call
         ud, vd = ctx.saved_tensors
-        tu, tv, tw = _swap(subscripts)
-        dW = SymTensor(gw.contiguous().to(ud.dtype), *meta_w[:5])
+        gw = gw.contiguous().to(ud.dtype)
         # complex operands: gradients with respect to the conjugate (Wirtinger),
         # so the other factor enters conjugated
         conj = (lambda t: t.conj().resolve_conj()) if ud.is_complex() else (lambda t: t)
         gu = gv = None
-        if ctx.needs_input_grad[5]:
+        if ctx.needs_input_grad[1]:
             # dU[I,K] = sum_J dW[I,J] V[K,J]; the derived rule of (dW, V) is U's.
-            out = SymTensor(torch.empty_like(ud), *meta_u)
-            contract_into(f"{tw},{tv}->{tu}", dW, SymTensor(conj(vd), *meta_v), out, compute)
-            gu = out.data
-        if ctx.needs_input_grad[6]:
+            gu = call.gradient(0, gw, conj(vd), torch.empty_like(ud))
+        if ctx.needs_input_grad[2]:
             # dV[K,J] = sum_I U[I,K] dW[I,J]; the derived rule of (U, dW) is V's up to a global sign.
-            out = SymTensor(torch.empty_like(vd), *meta_v)
-            contract_into(f"{tu},{tw}->{tv}", SymTensor(conj(ud), *meta_u), dW, out, compute)
-            gv = out.data
-        return None, None, None, None, None, gu, gv
+            gv = call.gradient(1, gw, conj(ud), torch.empty_like(vd))
+        return None, gu, gv
 
 
 def einsum(subscripts: str, u: SymTensor, v: SymTensor, compute: str = "f64") -> SymTensor:
@@ -262,18 +349,16 @@ def einsum(subscripts: str, u: SymTensor, v: SymTensor, compute: str = "f64") ->
         raise ValueError("operands use different groups")
     if compute not in L.COMPUTE:
         raise ValueError(f"compute must be one of {list(L.COMPUTE)}")
-    info = plan(subscripts, u, v, compute)
-    tu, tv, tw = _swap(subscripts)
-    dims = [u.dims[tu.index(m)] if m in tu else v.dims[tv.index(m)] for m in tw]
-    G = group_size(u.group)
-    ws = derived_sectors(subscripts, u, v)
-    shape = tuple(list((ws or (G,) * len(tw))[: len(tw) - 1]) + dims)
-    meta_u = (u.signs, u.charge, u.group, u.mode_charges, u.sectors)
-    meta_v = (v.signs, v.charge, v.group, v.mode_charges, v.sectors)
-    wc = derived_charges(subscripts, u, v)
-    meta_w = (info.w_signs.decode(), info.w_charge, u.group, wc, ws, shape)
-    wd = _Contract.apply(subscripts, meta_u, meta_v, meta_w, compute, u.data, v.data)
-    return SymTensor(wd, meta_w[0], meta_w[1], u.group, wc, ws)
+    ud, vd = u.data, v.data
+    key = (subscripts, compute, u.group, u.signs, u.charge, ud.shape, ud.dtype, u.mode_charges, u.sectors, v.signs,
+           v.charge, vd.shape, vd.dtype, v.mode_charges, v.sectors)
+    call = _EINSUMS.get(key)
+    if call is None:
+        call = _Einsum(subscripts, u, v, compute)
+        if len(_EINSUMS) >= _MAX_PLANS:
+            _EINSUMS.clear()
+        _EINSUMS[key] = call
+    return _wrap(_Contract.apply(call, ud, vd), *call.meta_w)
 
 
 # ---------------------------------------------------------------------------
