@@ -136,7 +136,8 @@
  * tiles take a product that reads u and v in place in any layout and at any
  * alignment where its time model prefers it (K runs of any length stepped run by
  * run, complex v not expanded; info.fused and info.fused_v are then those of the
- * product it replaces); the three-step path multiplies its aligned forms on the
+ * product it replaces), and so do BF16X3 products of real binary32 operands (w of
+ * either real type), which then split both in registers; the three-step path multiplies its aligned forms on the
  * same tile, in the same K-steps and stream-K shares.  The workspace holds
  * U_al in that case (left unused when u is read in place), then V_al (used when
  * v is not read in place) and the tables.  Where K-steps are the three-step path's, results are identical in
@@ -171,7 +172,8 @@
  *                          "rows" = the row-streaming product taken by default
  *                          where K and N are at most 64 and the slices hold at
  *                          least 16384 rows in all, "a96x96s2", "a128x64s2",
- *                          "a64x64s2" = the in-place product for any layout,
+ *                          "a64x64s2" = the in-place product for any layout
+ *                          (BF16X3: "a128x128s2" and the last two),
  *                          "tallk" = the long-K
  *                          product taken by default where M and N are at most
  *                          64 and K is 1024 or more;

@@ -37,12 +37,21 @@ __host__ __device__ inline void any_step(const AnySteps& st, int kt, int bk, int
 // 16-byte chunk swizzle of LDS row k of a [k][columns] tile (row bytes ROW), so
 // that the rows one fragment read touches (4 of them; 2 of complex rows) fall on
 // distinct banks.  A row holds a multiple of 8 chunks and the swizzle stays in it.
-template <int ES, int ROW, bool PAIRS>
+// Q4: the fragments of a 32-deep split-bf16 MFMA, whose four lane groups read K
+// indices 4 apart (any_k_bf16) instead of neighbours.
+template <int ES, int ROW, bool PAIRS, bool Q4 = false>
 __host__ __device__ inline int any_swz(int k) {
-  if constexpr (PAIRS) return ROW % 256 == 0 ? (k & 1) << (ES == 8 ? 3 : 2) : 0;
+  static_assert(!Q4 || (ES == 4 && !PAIRS && ROW % 256 == 0), "split-bf16 rows");
+  if constexpr (Q4) return ((k >> 2) & 3) << 2;
+  else if constexpr (PAIRS) return ROW % 256 == 0 ? (k & 1) << (ES == 8 ? 3 : 2) : 0;
   else if constexpr (ES == 8) return ROW % 256 == 0 ? (k & 1) << 3 : 0;
   else return ROW % 256 == 0 ? (k & 3) << 2 : ((k >> 1) & 1) << 2;
 }
+
+// K index (of a 32-deep step) of element j of lane group g's split-bf16 fragment: a
+// permutation of the step, the same for A and B, so that a row-major A still reads
+// 16-byte chunks (j 0-3 and 4-7) and rows of [k][columns] fall on distinct banks.
+__host__ __device__ inline int any_k_bf16(int g, int j) { return 16 * (j >> 2) + 4 * g + (j & 3); }
 
 // The element behind byte p of A's LDS tile: row m and first K index k of the
 // step it belongs to (AM = 2: an even k, the pair), and its byte `sub` past the
@@ -50,7 +59,7 @@ __host__ __device__ inline int any_swz(int k) {
 struct AnySlot {
   int line, k, sub;   // line: m of A, n of B
 };
-template <int ES, int BM, int AM>
+template <int ES, int BM, int AM, bool Q4 = false>
 __host__ __device__ inline AnySlot any_a_slot(int p) {
   constexpr int ROW = AM == 0 ? 128 : AM == 1 ? BM * ES : 2 * BM * ES;
   const int r = p / ROW, b = p % ROW;
@@ -59,36 +68,36 @@ __host__ __device__ inline AnySlot any_a_slot(int p) {
     return AnySlot{r, src / ES, src};
   } else {
     constexpr int PE = AM == 2 ? 2 * ES : ES;
-    const int src = (((b >> 4) ^ any_swz<ES, ROW, AM == 2>(r)) << 4) | (b & 15);
+    const int src = (((b >> 4) ^ any_swz<ES, ROW, AM == 2, Q4>(r)) << 4) | (b & 15);
     return AnySlot{src / PE, AM == 2 ? 2 * r : r, src % PE};
   }
 }
-template <int ES, int BN, bool CB>
+template <int ES, int BN, bool CB, bool Q4 = false>
 __host__ __device__ inline AnySlot any_b_slot(int p) {
   constexpr int ROW = BN * ES;
   const int r = p / ROW, b = p % ROW;
-  const int src = (((b >> 4) ^ any_swz<ES, ROW, CB>(r)) << 4) | (b & 15);
+  const int src = (((b >> 4) ^ any_swz<ES, ROW, CB, Q4>(r)) << 4) | (b & 15);
   return AnySlot{src / ES, CB ? 2 * r : r, src % ES};
 }
 
 // Byte of A's LDS tile that holds element (m, k) of the step, and of B's that
 // holds (k, n) (CB: of V's element, before the sign of the odd real rows).
-template <int ES, int BM, int AM>
+template <int ES, int BM, int AM, bool Q4 = false>
 __host__ __device__ inline int any_a_off(int m, int k) {
   if constexpr (AM == 0) {
     constexpr int VE = 16 / ES;
     return m * 128 + (((k / VE) ^ ((m >> 1) & 7)) << 4) + (k % VE) * ES;
   } else if constexpr (AM == 1) {
-    return k * BM * ES + ((((m * ES) >> 4) ^ any_swz<ES, BM * ES, false>(k)) << 4) + ((m * ES) & 15);
+    return k * BM * ES + ((((m * ES) >> 4) ^ any_swz<ES, BM * ES, false, Q4>(k)) << 4) + ((m * ES) & 15);
   } else {
     const int kc = k >> 1, mb = m * 2 * ES;
     return kc * 2 * BM * ES + (((mb >> 4) ^ any_swz<ES, 2 * BM * ES, true>(kc)) << 4) + (mb & 15) + (k & 1) * ES;
   }
 }
-template <int ES, int BN, bool CB>
+template <int ES, int BN, bool CB, bool Q4 = false>
 __host__ __device__ inline int any_b_off(int k, int n) {
   const int r = CB ? k >> 1 : k, nb = (CB ? n ^ (k & 1) : n) * ES;
-  return r * BN * ES + (((nb >> 4) ^ any_swz<ES, BN * ES, CB>(r)) << 4) + (nb & 15);
+  return r * BN * ES + (((nb >> 4) ^ any_swz<ES, BN * ES, CB, Q4>(r)) << 4) + (nb & 15);
 }
 
 // Lines (rows m of A, columns n of B) past the end are clamped: the last start of

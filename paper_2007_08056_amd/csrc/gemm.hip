@@ -1271,6 +1271,8 @@ hipError_t launch_gemm_any_f64(const AnyLaunch& l, int64_t batch, int M, int N, 
                                void* C, hipStream_t s, const FusedTables* f, void* part, size_t part_bytes);
 hipError_t launch_gemm_any_f32(const AnyLaunch& l, int64_t batch, int M, int N, int K, const void* A, const void* B,
                                void* C, hipStream_t s, const FusedTables* f, void* part, size_t part_bytes);
+hipError_t launch_gemm_any_bf16x3(const AnyLaunch& l, int64_t batch, int M, int N, int K, const void* A, const void* B,
+                                  void* C, hipStream_t s, const FusedTables* f, void* part, size_t part_bytes);
 
 // Wide split-bf16 tiles with one binary32 accumulator (gemm_bf16x3.hip).
 hipError_t launch_bf16x3_wide(int variant, int64_t batch, int M, int N, int K, const void* A, const void* B,
@@ -1292,7 +1294,13 @@ int launch_sector_gemm(int compute, int64_t batch, int64_t m, int64_t k, int64_t
   }
   const int M = static_cast<int>(m), N = static_cast<int>(n), K = static_cast<int>(k);
   hipError_t e = hipSuccess;
-  if (compute == SYMT_COMPUTE_BF16X3) {
+  if (fused && fused->any_tile >= 0) {
+    const AnyLaunch l{fused->any_tile, fused->any_am, fused->any_ch, fused->any_cb != 0, fused->any_sk != 0};
+    const auto launch = compute == SYMT_COMPUTE_F64   ? launch_gemm_any_f64
+                        : compute == SYMT_COMPUTE_F32 ? launch_gemm_any_f32
+                                                      : launch_gemm_any_bf16x3;
+    e = launch(l, batch, M, N, K, A, B, C, stream, fused, part, part_bytes);
+  } else if (compute == SYMT_COMPUTE_BF16X3) {
     if (K % 8 != 0) {
       if (err) *err = "split-bf16 product needs the contracted extent to be a multiple of 8";
       return SYMT_EUNSUPPORTED;
@@ -1351,11 +1359,6 @@ int launch_sector_gemm(int compute, int64_t batch, int64_t m, int64_t k, int64_t
       e = launch_bf16x3<128, 96, 32, 2, 2>(batch, M, N, K, A, B, C, stream, pa, pb, wrc, wcc, wcb);
     else
       e = launch_bf16x3<128, 128, 32, 2, 2>(batch, M, N, K, A, B, C, stream, pa, pb, wrc, wcc, wcb);
-  } else if (fused && fused->any_tile >= 0) {
-    const AnyLaunch l{fused->any_tile, fused->any_am, fused->any_ch, fused->any_cb != 0, fused->any_sk != 0};
-    e = compute == SYMT_COMPUTE_F64
-            ? launch_gemm_any_f64(l, batch, M, N, K, A, B, C, stream, fused, part, part_bytes)
-            : launch_gemm_any_f32(l, batch, M, N, K, A, B, C, stream, fused, part, part_bytes);
   } else {
     const bool f64 = compute == SYMT_COMPUTE_F64;
     const int vw = f64 ? 2 : 4;

@@ -29,6 +29,18 @@
 // at about two thirds of 16-byte ones' rate (3 x (743 x 1113 x 1111) f64: 34.5
 // TFLOP/s), so odd real shapes mostly stay on the register tiles.
 //
+// BF (binary32 operands): the split-bf16 product.  A fragment's eight values are
+// split into hi and lo in registers as they are read (24 VALU operations against
+// 3 MFMAs per tile of 16 x 16), so no operand goes to bf16 planes first; two
+// binary32 accumulators (hi hi, and the cross terms) as the other tiles of that
+// product, pieces of cut tiles in binary64.  It is bound by those splits and the
+// eight LDS reads of each B fragment (0.2 to 0.3 of a third of the bf16 peak), so
+// large products with whole 32-deep K-steps stay on planes, whose tiles reach 0.9;
+// what it saves is the planes' write and reads (12 bytes per element), three or
+// four launches, and the single pass over a long K that those tiles make.
+// Before -> after: 5 x (120 x 320 x 90) 41 -> 17 us, 8 x (3200 x 3200 x 128)
+// 358 -> 142, 4 x (1156 x 1156 x 36) 118 -> 39, 6 x (16 x 186624 x 18) 5307 -> 203.
+//
 // Values and K order are the other tiles': K-steps of 128 bytes, four indices
 // per MFMA, tiles cut by stream-K summed in K order by k_sk_fixup.
 #pragma once
@@ -38,6 +50,7 @@
 #include <algorithm>
 #include <atomic>
 #include <cstdint>
+#include <type_traits>
 
 #include "any_index.hpp"
 #include "gemm_tiles.hpp"
@@ -79,6 +92,16 @@ struct AnyTile {
   using Acc = typename Mfma<T>::Acc;
 };
 
+// A tile's sums: one accumulator per 16 x 16 block, two in the split-bf16 product.
+template <typename T, int TM, int TN, bool BF>
+struct AnyAcc {
+  typename Mfma<T>::Acc v[TM][TN];
+};
+template <int TM, int TN>
+struct AnyAcc<float, TM, TN, true> {
+  f4 v[TM][TN], x[TM][TN];
+};
+
 // Most LDS rows that one wave load (64 lanes of CH bytes) of a tile with ROW-byte rows touches.
 template <int CH, int ROW>
 constexpr int any_rows_per_load() {
@@ -92,12 +115,12 @@ constexpr int any_rows_per_load() {
   return (ROW - g + 64 * CH - 1) / ROW + 1;
 }
 
-template <typename T, int BM, int BN, int WM, int WN, int S, int CH, int AM, bool CB>
+template <typename T, int BM, int BN, int WM, int WN, int S, int CH, int AM, bool CB, bool BF>
 __device__ __forceinline__ void any_tile_accumulate(
     const T* __restrict__ A, const T* __restrict__ B, int M, int N, const AnySteps& st, int64_t q, int m0, int n0,
     int kt0, int kt1, const int64_t* __restrict__ ra, const int64_t* __restrict__ ca,
     const int64_t* __restrict__ rb, const int64_t* __restrict__ cb, int64_t ldb, char* smem,
-    typename Mfma<T>::Acc (&acc)[BM / WM / 16][BN / WN / 16]) {
+    AnyAcc<T, BM / WM / 16, BN / WN / 16, BF>& acc) {
   using D = AnyTile<T, BM, BN, WM, WN, S, CH, AM, CB>;
   constexpr int ES = D::ES, NT = D::NT, NW = D::NW, BK = D::BK, TM = D::TM, TN = D::TN;
   constexpr int A_LOADS = D::A_LOADS, B_LOADS = D::B_LOADS, STAGE = D::STAGE, A_BYTES = D::A_BYTES;
@@ -118,14 +141,14 @@ __device__ __forceinline__ void any_tile_accumulate(
   int64_t a_src[A_LOADS], b_src[B_LOADS];
 #pragma unroll
   for (int i = 0; i < A_LOADS; ++i) {
-    const AnySlot x = any_a_slot<ES, BM, AM>((i * NT + tid) * CH);
+    const AnySlot x = any_a_slot<ES, BM, AM, BF && AM != 0>((i * NT + tid) * CH);
     constexpr int PE = AM == 0 ? 16 : AM == 2 ? 2 * ES : ES;   // bytes of one m in a load
     const int m = min(m0 + x.line, any_last_line<CH, PE>(M));
     a_src[i] = (ra ? ra[q * M + m] : (q * M + m) * static_cast<int64_t>(K)) * ES + (AM == 0 || CH == 4 ? x.sub : 0);
   }
 #pragma unroll
   for (int i = 0; i < B_LOADS; ++i) {
-    const AnySlot x = any_b_slot<ES, BN, CB>((i * NT + tid) * CH);
+    const AnySlot x = any_b_slot<ES, BN, CB, BF>((i * NT + tid) * CH);
     const int n = min(n0 + x.line, any_last_line<CH, ES>(N));
     b_src[i] = ((CB ? x.k / 2 : x.k) * ldb + (cb ? cb[q * N + n] : static_cast<int64_t>(n))) * ES +
                (CH == 4 ? x.sub : 0);
@@ -175,7 +198,7 @@ __device__ __forceinline__ void any_tile_accumulate(
       if (A_BYTES % (CH * NT) != 0 && (i * NW + wave) * 64 * CH >= A_BYTES) break;
       const char* g = Ab + (a_src[i] + arow_of(i) * ES);
       if (tail) {
-        const int k = any_a_slot<ES, BM, AM>((i * NT + tid) * CH).k;
+        const int k = any_a_slot<ES, BM, AM, BF && AM != 0>((i * NT + tid) * CH).k;
         if (k >= kv) g = reinterpret_cast<const char*>(kZeroWords);
       }
       lds_dma<CH>(g, base + i * NT * CH);
@@ -185,7 +208,7 @@ __device__ __forceinline__ void any_tile_accumulate(
       if (D::B_BYTES % (CH * NT) != 0 && (i * NW + wave) * 64 * CH >= D::B_BYTES) break;
       const char* g = Bb + (b_src[i] + brow_next * ES);
       if (tail) {
-        const int k = any_b_slot<ES, BN, CB>((i * NT + tid) * CH).k;
+        const int k = any_b_slot<ES, BN, CB, BF>((i * NT + tid) * CH).k;
         if (k >= kv) g = reinterpret_cast<const char*>(kZeroWords);
       }
       lds_dma<CH>(g, base + A_BYTES + i * NT * CH);
@@ -206,25 +229,65 @@ __device__ __forceinline__ void any_tile_accumulate(
     if (it + S - 1 < nk) issue(kt0 + it + S - 1, (it + S - 1) % S);
     const char* As = smem + (it % S) * STAGE;
     const char* Bs = As + A_BYTES;
-#pragma unroll
-    for (int kk = 0; kk < BK; kk += 4) {
-      const int k = kk + (lane >> 4);
-      T a[TM], b[TN];
+    if constexpr (BF) {
+      const int g = lane >> 4;
+      bf8 ah[TM], al[TM];
 #pragma unroll
       for (int i = 0; i < TM; ++i) {
-        a[i] = *reinterpret_cast<const T*>(As + any_a_off<ES, BM, AM>(wm0 + i * 16 + (lane & 15), k));
+        const int m = wm0 + i * 16 + (lane & 15);
+        fv4 x[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          if constexpr (AM == 0) {
+            x[h] = *reinterpret_cast<const fv4*>(As + any_a_off<ES, BM, AM>(m, any_k_bf16(g, 4 * h)));
+          } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              x[h][e] = *reinterpret_cast<const T*>(As + any_a_off<ES, BM, AM, true>(m, any_k_bf16(g, 4 * h + e)));
+          }
+        }
+        split8(x[0], x[1], ah[i], al[i]);
       }
 #pragma unroll
       for (int j = 0; j < TN; ++j) {
         const int n = wn0 + j * 16 + (lane & 15);
-        const T x = *reinterpret_cast<const T*>(Bs + any_b_off<ES, BN, CB>(k, n));
-        // CB: real row 2 kc + 1 is (-im, re), the other member of the pair, im negated
-        b[j] = CB && (k & 1) && !(n & 1) ? -x : x;
+        fv4 x[2];
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          x[e >> 2][e & 3] = *reinterpret_cast<const T*>(Bs + any_b_off<ES, BN, CB, true>(any_k_bf16(g, e), n));
+        bf8 bh, bl;
+        split8(x[0], x[1], bh, bl);
+        // (the two updates of each cross accumulator are TM products apart)
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+          acc.v[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[i], bh, acc.v[i][j], 0, 0, 0);
+          acc.x[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[i], bl, acc.x[i][j], 0, 0, 0);
+        }
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+          acc.x[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al[i], bh, acc.x[i][j], 0, 0, 0);
       }
+    } else {
 #pragma unroll
-      for (int i = 0; i < TM; ++i)
+      for (int kk = 0; kk < BK; kk += 4) {
+        const int k = kk + (lane >> 4);
+        T a[TM], b[TN];
 #pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = Mfma<T>::run(a[i], b[j], acc[i][j]);
+        for (int i = 0; i < TM; ++i) {
+          a[i] = *reinterpret_cast<const T*>(As + any_a_off<ES, BM, AM>(wm0 + i * 16 + (lane & 15), k));
+        }
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+          const int n = wn0 + j * 16 + (lane & 15);
+          const T x = *reinterpret_cast<const T*>(Bs + any_b_off<ES, BN, CB>(k, n));
+          // CB: real row 2 kc + 1 is (-im, re), the other member of the pair, im negated
+          b[j] = CB && (k & 1) && !(n & 1) ? -x : x;
+        }
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j) acc.v[i][j] = Mfma<T>::run(a[i], b[j], acc.v[i][j]);
+      }
     }
   }
 }
@@ -232,21 +295,65 @@ __device__ __forceinline__ void any_tile_accumulate(
 // Waves per SIMD that the register allocator leaves room for: three where the LDS
 // ring admits three workgroups per CU; two with 4-byte loads, whose 24 load
 // sources take 48 registers (96 x 96 spilled 73 of them at three).
-template <int BM, int BN, int CH>
-constexpr int kAnyWavesPerSimd = CH == 16 || BM * BN <= 64 * 64 ? 3 : 2;
+template <int BM, int BN, int CH, bool BF = false>
+constexpr int kAnyWavesPerSimd = BM * BN <= 64 * 64 || (CH == 16 && !BF) ? 3 : 2;
+
+// Split-bf16 sums to W (binary64 sums of the two accumulators, rounded to TC) and to a piece.
+template <typename TC, int BM, int BN, int WM, int WN, int TM, int TN>
+__device__ __forceinline__ void store_any_bf16(TC* __restrict__ C, int M, int N, int m0, int n0,
+                                               const CTab<TM, TN>& t, bool rows4,
+                                               const AnyAcc<float, TM, TN, true>& acc) {
+  const int lane = threadIdx.x & 63;
+  const int wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int j = 0; j < TN; ++j) {
+    const int col = n0 + (wave % WN) * (BN / WN) + j * 16 + (lane & 15);
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      const int row0 = m0 + (wave / WN) * (BM / WM) + i * 16 + Mfma<float>::row(lane, 0);
+      TC v[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        v[r] = static_cast<TC>(static_cast<double>(acc.v[i][j][r]) + static_cast<double>(acc.x[i][j][r]));
+      if constexpr (sizeof(TC) == 4) {
+        if (rows4 && row0 + 3 < M) {
+          if (col < N) *reinterpret_cast<f4*>(C + t.row[i][0] + t.col[j]) = f4{v[0], v[1], v[2], v[3]};
+          continue;
+        }
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (row0 + r < M && col < N) C[t.row[i][r] + t.col[j]] = v[r];
+    }
+  }
+}
+template <int TM, int TN>
+__device__ __forceinline__ void store_any_piece(double* __restrict__ piece, const AnyAcc<float, TM, TN, true>& acc) {
+  const int lane = threadIdx.x & 63;
+  double* pw = piece + (threadIdx.x >> 6) * (TM * TN * 4 * 64) + lane;
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        pw[((i * TN + j) * 4 + r) * 64] = static_cast<double>(acc.v[i][j][r]) + static_cast<double>(acc.x[i][j][r]);
+}
 
 // One workgroup per tile (ts = 0, XCD-aware order), or stream-K (ts > 0:
 // persistent workgroups, pieces of cut tiles to `part` for k_sk_fixup).
-template <typename T, int BM, int BN, int WM, int WN, int S, int CH, int AM, bool CB>
-__global__ __launch_bounds__(64 * WM * WN, (kAnyWavesPerSimd<BM, BN, CH>)) void k_gemm_any(
-    const T* __restrict__ A, const T* __restrict__ B, T* __restrict__ C, int M, int N, AnySteps st, int tiles_m,
+template <typename T, int BM, int BN, int WM, int WN, int S, int CH, int AM, bool CB, bool BF = false,
+          typename TC = T>
+__global__ __launch_bounds__(64 * WM * WN, (kAnyWavesPerSimd<BM, BN, CH, BF>)) void k_gemm_any(
+    const T* __restrict__ A, const T* __restrict__ B, TC* __restrict__ C, int M, int N, AnySteps st, int tiles_m,
     int tiles_n, int64_t ntiles, const int64_t* __restrict__ ra, const int64_t* __restrict__ ca,
     const int64_t* __restrict__ rc, const int64_t* __restrict__ cc, const int64_t* __restrict__ rb,
-    const int64_t* __restrict__ cb, int64_t ldb, T* __restrict__ part, int ts, int c_rows4) {
+    const int64_t* __restrict__ cb, int64_t ldb,
+    typename std::conditional<BF, double, T>::type* __restrict__ part, int ts, int c_rows4) {
   using D = AnyTile<T, BM, BN, WM, WN, S, CH, AM, CB>;
   constexpr int TM = D::TM, TN = D::TN;
   __shared__ __attribute__((aligned(1024))) char smem[S * D::STAGE];
-  typename D::Acc acc[TM][TN];
+  AnyAcc<T, TM, TN, BF> acc;
   SkSlot sl{0, 0, 1};
   int64_t it = 0, end = st.nk, first = 0, tile = 0;
   if (ts > 0) {
@@ -277,23 +384,32 @@ __global__ __launch_bounds__(64 * WM * WN, (kAnyWavesPerSimd<BM, BN, CH>)) void 
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int j = 0; j < TN; ++j) acc[i][j] = typename D::Acc{};
-    any_tile_accumulate<T, BM, BN, WM, WN, S, CH, AM, CB>(A, B, M, N, st, q, tm * BM, tn * BN, kt0, kt1, ra, ca, rb,
-                                                          cb, ldb, smem, acc);
+      for (int j = 0; j < TN; ++j) {
+        acc.v[i][j] = typename D::Acc{};
+        if constexpr (BF) acc.x[i][j] = typename D::Acc{};
+      }
+    any_tile_accumulate<T, BM, BN, WM, WN, S, CH, AM, CB, BF>(A, B, M, N, st, q, tm * BM, tn * BN, kt0, kt1, ra, ca,
+                                                              rb, cb, ldb, smem, acc);
     if (kt0 == 0 && kt1 == st.nk) {
       // W's table entries all requested before the first store
       CTab<TM, TN> ct;
       if (rc) load_ctab<T, BM, BN, WM, WN, TM, TN>(ct, M, N, q, tm * BM, tn * BN, rc, cc);
       else affine_ctab<T, BM, BN, WM, WN, TM, TN>(ct, M, N, q, tm * BM, tn * BN);
-      store_tile_tab<T, BM, BN, WM, WN, TM, TN>(C, M, N, tm * BM, tn * BN, ct, c_rows4 != 0, acc);
+      if constexpr (BF)
+        store_any_bf16<TC, BM, BN, WM, WN, TM, TN>(C, M, N, tm * BM, tn * BN, ct, c_rows4 != 0, acc);
+      else
+        store_tile_tab<T, BM, BN, WM, WN, TM, TN>(C, M, N, tm * BM, tn * BN, ct, c_rows4 != 0, acc.v);
     } else {
-      store_piece<TM, TN>(part + sk_piece(sl.team, sl.member, ts, grp, first) * (BM * BN), acc);
+      auto* piece = part + sk_piece(sl.team, sl.member, ts, grp, first) * (BM * BN);
+      if constexpr (BF) store_any_piece<TM, TN>(piece, acc);
+      else store_piece<TM, TN>(piece, acc.v);
     }
     it += kt1 - kt0;
   }
 }
 
-template <typename T, int BM, int BN, int WM, int WN, int S, int CH, int AM, bool CB>
+template <typename T, int BM, int BN, int WM, int WN, int S, int CH, int AM, bool CB, bool BF = false,
+          typename TC = T>
 hipError_t launch_any_kernel(int64_t batch, int M, int N, const AnySteps& st, const void* A, const void* B, void* C,
                              hipStream_t s, const FusedTables* f, void* part, size_t part_bytes, bool sk) {
   const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
@@ -301,10 +417,11 @@ hipError_t launch_any_kernel(int64_t batch, int M, int N, const AnySteps& st, co
   const dim3 block(64 * WM * WN);
   const T* a = static_cast<const T*>(A);
   const T* b = static_cast<const T*>(B);
-  T* c = static_cast<T*>(C);
-  T* pt = static_cast<T*>(part);
+  using TP = typename std::conditional<BF, double, T>::type;
+  TC* c = static_cast<TC*>(C);
+  TP* pt = static_cast<TP*>(part);
   const int rows4 = f->c_rows4 && (reinterpret_cast<uintptr_t>(c) & 15) == 0 ? 1 : 0;
-  auto kern = k_gemm_any<T, BM, BN, WM, WN, S, CH, AM, CB>;
+  auto kern = k_gemm_any<T, BM, BN, WM, WN, S, CH, AM, CB, BF, TC>;
   int P = 0, ts = 0;
   if (sk && part) {
     // resident workgroups per CU of this instantiation, cached
@@ -315,7 +432,7 @@ hipError_t launch_any_kernel(int64_t batch, int M, int N, const AnySteps& st, co
       occupancy.store(occ, std::memory_order_relaxed);
     }
     const SkLaunch sl = sk_launch(ntiles, tiles_n, st.nk, std::min<int64_t>(kSkSlots, static_cast<int64_t>(device_cus()) * occ),
-                                  static_cast<int64_t>(part_bytes / sizeof(T)), static_cast<int64_t>(BM) * BN,
+                                  static_cast<int64_t>(part_bytes / sizeof(TP)), static_cast<int64_t>(BM) * BN,
                                   kSkMinIters);
     P = sl.P;
     if (P > 0) ts = sl.ts;
@@ -326,10 +443,10 @@ hipError_t launch_any_kernel(int64_t batch, int M, int N, const AnySteps& st, co
   if (e != hipSuccess || P == 0) return e;
   const dim3 fgrid = sk_fixup_grid(ntiles, ts, st.nk, P / ts, static_cast<int64_t>(BM) * BN, 64 * WM * WN);
   if (f->rc)
-    hipLaunchKernelGGL((k_sk_fixup<T, BM, BN, WM, WN, true>), fgrid, block, 0, s, pt, c, M, N, st.nk, tiles_m, tiles_n,
+    hipLaunchKernelGGL((k_sk_fixup<T, BM, BN, WM, WN, true, TP, TC>), fgrid, block, 0, s, pt, c, M, N, st.nk, tiles_m, tiles_n,
                        ntiles, ts, P / ts, f->rc, f->cc);
   else
-    hipLaunchKernelGGL((k_sk_fixup<T, BM, BN, WM, WN, false>), fgrid, block, 0, s, pt, c, M, N, st.nk, tiles_m,
+    hipLaunchKernelGGL((k_sk_fixup<T, BM, BN, WM, WN, false, TP, TC>), fgrid, block, 0, s, pt, c, M, N, st.nk, tiles_m,
                        tiles_n, ntiles, ts, P / ts, f->rc, f->cc);
   return hipGetLastError();
 }

@@ -13,6 +13,25 @@ namespace {
 typedef double d4 __attribute__((ext_vector_type(4)));
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
+typedef float fv4 __attribute__((ext_vector_type(4)));
+typedef float fv8 __attribute__((ext_vector_type(8)));
+typedef uint32_t uv4 __attribute__((ext_vector_type(4)));
+
+// bf16_split of eight binary32 values at once: hi = bf16(x), lo = bf16(x - hi),
+// each by the hardware conversion that bf16_rne is (paired, round to nearest even): the
+// products that split in registers give the bits of the transforms' planes.
+__device__ __forceinline__ void split8(fv4 x0, fv4 x1, bf8& hi, bf8& lo) {
+  const fv8 x = {x0[0], x0[1], x0[2], x0[3], x1[0], x1[1], x1[2], x1[3]};
+  hi = __builtin_convertvector(x, bf8);
+  const uv4 hb = __builtin_bit_cast(uv4, hi);
+  fv8 hf;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    hf[2 * j] = __uint_as_float(hb[j] << 16);
+    hf[2 * j + 1] = __uint_as_float(hb[j] & 0xFFFF0000u);
+  }
+  lo = __builtin_convertvector(x - hf, bf8);
+}
 
 // Tile order of one-workgroup-per-tile launches: within each Q, groups of
 // kGroupM M-panels, column by column, so the workgroups in flight on an XCD

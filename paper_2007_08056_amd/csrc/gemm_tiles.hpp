@@ -133,9 +133,10 @@ __device__ __forceinline__ void store_piece(T* __restrict__ piece, const Acc (&a
 // tiles -- is summed by many workgroups); tiles covered whole by one team
 // return at once.  Each element's sum starts from zero and adds the pieces in
 // team order: the same arithmetic whatever `chunks` is.
-template <typename T, int BM, int BN, int WM, int WN, bool FC>
+// T: the product's type (accumulator rows); TP, TC: the pieces' and C's types.
+template <typename T, int BM, int BN, int WM, int WN, bool FC, typename TP = T, typename TC = T>
 __global__ __launch_bounds__(64 * WM * WN) void k_sk_fixup(
-    const T* __restrict__ part, T* __restrict__ C, int M, int N, int nk, int tiles_m, int tiles_n,
+    const TP* __restrict__ part, TC* __restrict__ C, int M, int N, int nk, int tiles_m, int tiles_n,
     int64_t ntiles, int ts, int nteam, const int64_t* __restrict__ rc, const int64_t* __restrict__ cc) {
   constexpr int TM = BM / WM / 16, TN = BN / WN / 16;
   constexpr int E = BM * BN;                      // elements of a tile (= of a piece)
@@ -167,7 +168,7 @@ __global__ __launch_bounds__(64 * WM * WN) void k_sk_fixup(
   const int64_t t2 = tile / tiles_n;
   const int tm = static_cast<int>(t2 % tiles_m);
   const int64_t q = t2 / tiles_m;
-  T* Cq = C + (FC ? 0 : q * static_cast<int64_t>(M) * N);
+  TC* Cq = C + (FC ? 0 : q * static_cast<int64_t>(M) * N);
   const int per = (E + chunks - 1) / chunks;
   const int e0 = static_cast<int>(blockIdx.y) * per;
   const int e1 = min(E, e0 + per);
@@ -192,11 +193,11 @@ __global__ __launch_bounds__(64 * WM * WN) void k_sk_fixup(
   constexpr int NT = 64 * WM * WN;
   constexpr int U = 4;                            // elements in flight per thread
   for (int e = e0 + static_cast<int>(threadIdx.x); e < e1; e += U * NT) {
-    T acc[U];
+    TP acc[U];
     int64_t dst[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      acc[u] = T(0);
+      acc[u] = TP(0);
       dst[u] = e + u * NT < e1 ? dest(e + u * NT) : -1;
     }
     if (listed) {
@@ -222,7 +223,7 @@ __global__ __launch_bounds__(64 * WM * WN) void k_sk_fixup(
     }
 #pragma unroll
     for (int u = 0; u < U; ++u)
-      if (dst[u] >= 0) Cq[dst[u]] = acc[u];
+      if (dst[u] >= 0) Cq[dst[u]] = static_cast<TC>(acc[u]);
   }
 }
 

@@ -196,6 +196,66 @@ AnyChoice choose_any(int64_t batch, int64_t M, int64_t N, int64_t kpad, int elem
   return best;
 }
 
+// The split-bf16 tiles of the in-place product.  Efficiencies (of a third of the
+// bf16 peak), rates and launch costs here and in bf16_planes_time are a fit to the
+// times of 130 contractions of 0.00002 to 300 GFLOP on each tile and on planes,
+// with 16- and 4-byte loads, stream-K and not (its own choice is 7% from the best
+// of them in the mean, planes alone 2.4 times).
+constexpr AnyTileDesc kAnyTilesBf16[] = {
+    {"a128x128s2", 128, 128, 0.31, 0, 2}, {"a128x64s2", 128, 64, 0.22, 0.17, 2}, {"a64x64s2", 64, 64, 0.19, 0.14, 3}};
+constexpr double kBf16PerCu = 2500e12 / 3 / 256;
+AnyChoice choose_any_bf16(int64_t batch, int64_t M, int64_t N, int64_t kpad, double bytes, bool ch16,
+                          const char* forced, int sk_mode) {
+  AnyChoice best;
+  const double mem = bytes / 1.9e12;
+  for (int i = 0; i < static_cast<int>(sizeof(kAnyTilesBf16) / sizeof(kAnyTilesBf16[0])); ++i) {
+    const AnyTileDesc& t = kAnyTilesBf16[i];
+    if (forced && std::strcmp(forced, t.name) != 0) continue;
+    if (!forced && !ch16 && t.eff4 == 0) continue;
+    const int64_t tiles = batch * ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
+    const double eff = ch16 || t.eff4 == 0 ? t.eff16 : t.eff4;
+    const double t_tile = 2.0 * t.bm * t.bn * static_cast<double>(kpad) / (eff * kBf16PerCu);
+    for (int sk = 0; sk < 2; ++sk) {
+      if (sk ? sk_mode == 0 : sk_mode == 1) continue;
+      // (pieces are binary64)
+      const size_t partial = sk ? 2 * static_cast<size_t>(std::min(kSkSlots, 256 * t.wgs)) * t.bm * t.bn * 8 : 0;
+      const int64_t rounds = (tiles + 255) / 256;
+      const double busy = sk ? static_cast<double>(tiles) / 256.0 * t_tile / 0.82
+                             : static_cast<double>(rounds) * t_tile / (rounds == 1 ? 0.57 : rounds == 2 ? 0.96 : 1.0);
+      const double time = std::max(busy, mem) + 0.2 * std::min(busy, mem) +
+                          (sk ? 0.7 * static_cast<double>(partial) / 5e12 + 15e-6 : 13e-6);
+      if (best.tile < 0 || time < best.time) best = AnyChoice{i, sk != 0, partial, time};
+    }
+  }
+  return best;
+}
+
+// The time of a split-bf16 plan on hi/lo planes: its passes over U, V and W (12
+// bytes read and written per element that goes to planes) and the tile the launcher takes.
+double bf16_planes_time(const Plan& p) {
+  const double rate = 2.9e12;
+  double t = 36e-6 + (12.0 * static_cast<double>(p.V.elems) + 8.0 * static_cast<double>(p.W.elems)) / rate;
+  if (!p.fused) t += 12.0 * static_cast<double>(p.U.elems) / rate + 4e-6;
+  if (!p.fused && !p.fused_ua) t += 24.0 * static_cast<double>(p.W.elems) / rate + 4e-6;
+  const int wide = p.kpad % 32 == 0 ? bf16x3_wide_tile(p.nq, p.M, p.gn) : -1;
+  int64_t bm = 128, bn = 128;
+  double eff = 0.39;
+  if (wide >= 0) {
+    bm = 256, bn = wide == 0 ? 256 : 128, eff = 0.93;
+  } else if (!bf16x3_register_tile(p.M, p.gn, p.kpad)) {
+    bn = 256, eff = 0.72;
+  } else if (p.gn <= 64) {
+    bn = 64, eff *= 0.5;
+  } else if (p.gn >= 1024 && p.M >= 1024) {
+    bn = 256;
+  } else if ((p.gn + 95) / 96 * 96 < (p.gn + 127) / 128 * 128) {
+    bn = 96, eff *= 0.75;
+  }
+  const int64_t tiles = p.nq * ((p.M + bm - 1) / bm) * ((p.gn + bn - 1) / bn);
+  return t + static_cast<double>((tiles + 255) / 256) * 2.0 * static_cast<double>(bm * bn) *
+                 static_cast<double>(p.kpad) / (eff * kBf16PerCu);
+}
+
 bool is_letter(char c) { return (c >= 'a' && c <= 'z') || (c >= 'A' && c <= 'Z'); }
 
 }  // namespace
@@ -261,10 +321,15 @@ bool v_in_place_layout(const Plan& p, int64_t* ldb, bool* chunks) {
 namespace {
 // The in-place product for any layout (gemm_any.hpp): whether it takes this
 // plan, and its loader and tile.  Binary64 and binary32 plans whose operands are
-// all stored in the compute type and whose W is written in place anyway.
+// all stored in the compute type and whose W is written in place anyway;
+// split-bf16 plans of real binary32 operands (W of either real type).
 bool plan_any(Plan* p, int want, bool trailing_k, int64_t run) {
-  if (p->compute == SYMT_COMPUTE_BF16X3 || !(p->fused || p->fused_ua)) return false;
-  if (p->U.dtype != want || p->V.dtype != want || p->W.dtype != want) return false;
+  const bool bf = p->compute == SYMT_COMPUTE_BF16X3;
+  if (p->U.dtype != want || p->V.dtype != want) return false;
+  if (bf ? p->cplx || p->subgroups || p->nq != p->g.size || p->M <= 0 || p->N <= 0 || p->Kd <= 0 || p->U.elems <= 0 ||
+               p->v < 1 || p->s < 1 || p->t < 1
+         : !(p->fused || p->fused_ua) || p->W.dtype != want)
+    return false;
   const int elem = p->compute == SYMT_COMPUTE_F64 ? 8 : 4;
   const int64_t ve = 16 / elem, bk = 128 / elem, pe = p->cplx ? 2 : 1;
   auto last_run = [](const OperandDesc& X, const int32_t* pos, int count) {
@@ -297,9 +362,18 @@ bool plan_any(Plan* p, int want, bool trailing_k, int64_t run) {
   const char* forced = std::getenv("SYMT_GEMM_TILE");
   const char* sk_env = std::getenv("SYMT_GEMM_SK");
   const int sk_mode = sk_env ? std::atoi(sk_env) : -1;
-  const AnyChoice c = choose_any(p->g.size, p->M, p->gn, ksteps * bk, elem, y.ch16, forced, sk_mode);
+  const AnyChoice c =
+      bf ? choose_any_bf16(p->g.size, p->M, p->gn, ksteps * bk,
+                           4.0 * static_cast<double>(p->U.elems + p->V.elems + p->W.elems), y.ch16, forced, sk_mode)
+         : choose_any(p->g.size, p->M, p->gn, ksteps * bk, elem, y.ch16, forced, sk_mode);
   if (c.tile < 0) return false;
-  if (!forced) {
+  if (bf && !forced) {
+    // against the product on hi/lo planes
+    const double valign = y.b ? 0 : 8.0 * static_cast<double>(p->V.elems) / 3.5e12 + 8e-6;
+    // (0.7: the model is least sure where planes run on global-to-LDS tiles)
+    const double keep = p->kpad % 32 == 0 && !bf16x3_register_tile(p->M, p->gn, p->kpad) ? 0.7 : 0.85;
+    if (!a_ok || c.time + valign > keep * bf16_planes_time(*p)) return false;
+  } else if (!forced) {
     // against the product the plan takes otherwise and its passes over U and V
     const GemmChoice g = choose_fp_gemm(p->g.size, p->M, p->gn, p->gk, elem, true, p->a_trans);
     if (!a_ok || g.tile == kRowsTile || g.tile == kTallKTile) return false;
@@ -757,6 +831,9 @@ int make_plan(const char* einsum, const symt_group* group, const symt_tensor* u,
   } else if (p->any.tile >= 0) {
     // U is not aligned then, nor V where it has tables of its own (4-byte loads take any alignment)
     const size_t G = static_cast<size_t>(p->g.size);
+    p->any_direct = true;
+    if (!p->fused && !p->fused_ua)
+      p->bytes_tables = round_up(8 * G * p->M, 256) * 2 + round_up(8 * G * p->gk, 256) + round_up(8 * G * p->gn, 256);
     if (p->any.b && !p->fused_b) p->bytes_tables += round_up(8 * G * p->gk, 256) + round_up(8 * G * p->gn, 256);
     p->workspace = (p->any.b ? 0 : round_up(p->ws_v_al, 256)) + p->bytes_tables;
   }
@@ -765,6 +842,9 @@ int make_plan(const char* einsum, const symt_group* group, const symt_tensor* u,
     const GemmChoice gc = choose_fp_gemm(p->nq, p->M, p->gn, p->gk,
                                          compute == SYMT_COMPUTE_F64 ? 8 : 4, true, p->a_trans);
     p->bytes_partial = std::max(gc.partial_bytes, p->any.partial_bytes);
+    p->workspace += round_up(p->bytes_partial, 256);
+  } else if (p->any.tile >= 0) {
+    p->bytes_partial = p->any.partial_bytes;
     p->workspace += round_up(p->bytes_partial, 256);
   }
   p->workspace += round_up(p->bytes_charges, 256);

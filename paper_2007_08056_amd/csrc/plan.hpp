@@ -245,6 +245,7 @@ struct Plan {
     int64_t ldb = 0;                // V's row stride (reals) with b
     size_t partial_bytes = 0;
   } any;
+  bool any_direct = false;          // any, on U's and W's standard forms (not the three-step path)
   size_t bytes_u_al = 0, bytes_v_al = 0, bytes_w_al = 0, workspace = 0;
   size_t ws_u_al = 0, ws_v_al = 0, ws_w_al = 0;   // their regions in the contraction's workspace
   size_t bytes_tables = 0;          // fused (or fused_ua): four offset tables, six with fused_b

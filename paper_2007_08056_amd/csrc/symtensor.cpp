@@ -188,6 +188,17 @@ int do_unalign(symt_ctx* ctx, const Plan& p, const void* wal, hipStream_t s, boo
   return rc ? ctx_fail(ctx, rc, err) : SYMT_OK;
 }
 
+// The plan whose transforms write the in-place product's aligned operands: a
+// split-bf16 one takes them as binary32 rows (it splits as it multiplies).
+const Plan& any_operands(const Plan& p, Plan* f32) {
+  if (p.any.tile < 0 || p.compute != SYMT_COMPUTE_BF16X3) return p;
+  *f32 = p;
+  f32->compute = SYMT_COMPUTE_F32;
+  f32->kpad = p.gk;
+  f32->bf16_il = false;
+  return *f32;
+}
+
 // Split-bf16 planes with K padded to a multiple of 8 (kpad): clear them before
 // the transforms fill their first gk columns, so the pad multiplies as zero.
 int clear_k_pad(symt_ctx* ctx, const Plan& p, void* ual, void* val, hipStream_t s) {
@@ -344,13 +355,14 @@ int do_fused(symt_ctx* ctx, const Plan& p, char* base, hipStream_t s, const int3
   if (tlock.owns_lock()) tlock.unlock();
   if (rc_) return ctx_fail(ctx, rc_, err);
   // split-bf16 on the 256 x 256 wide tile: binary32 U read in place (16-byte aligned)
-  const bool wide_fa = p.bf16_wide_fa && aligned16(p.U.data);
+  const bool wide_fa = p.bf16_wide_fa && !any && aligned16(p.U.data);
   if (ua && (rc_ = clear_k_pad(ctx, p, ual, fb ? nullptr : val, s))) return rc_;
   if (ua && !wide_fa && (rc_ = do_align(ctx, p, 0, ual, s, true, chg[0]))) return rc_;
-  if (!fb && (rc_ = do_align(ctx, p, 1, val, s, true, chg[1]))) return rc_;
+  Plan pf;
+  if (!fb && (rc_ = do_align(ctx, any_operands(p, &pf), 1, val, s, true, chg[1]))) return rc_;
   symt::FusedTables f{ra, ca, rc, cc, vec};
   // split-bf16 on aligned U: A and B come from the hi/lo planes, only W's tables apply
-  if (p.fused_ua && p.compute == SYMT_COMPUTE_BF16X3 && !wide_fa) f.ra = f.ca = nullptr;
+  if (ua && p.compute == SYMT_COMPUTE_BF16X3 && !wide_fa) f.ra = f.ca = nullptr;
   f.a_bytes = static_cast<int32_t>(p.fused_ua && !wide_fa ? (p.compute == SYMT_COMPUTE_F64 ? 8 : 4)
                                                             : elem_bytes(p.U.dtype));
   f.krun = p.krun;
@@ -613,20 +625,23 @@ int contract_planned(symt_ctx* ctx, const Plan& p, void* workspace, size_t works
     for (int op = 0; op < 3; ++op)
       if (!p.chg[op].empty()) chg[op] = dev + off[op];
   }
-  if (p.fused || p.fused_ua) return do_fused(ctx, p, base, s, chg, tables);
+  if (p.fused || p.fused_ua || p.any_direct) return do_fused(ctx, p, base, s, chg, tables);
   void* ual = base;
   void* val = base + symt::round_up(p.ws_u_al, 256);
   void* wal = base + symt::round_up(p.ws_u_al, 256) + symt::round_up(p.ws_v_al, 256);
   char* part = static_cast<char*>(wal) + symt::round_up(p.ws_w_al, 256);
-  if ((rc = clear_k_pad(ctx, p, ual, val, s))) return rc;
-  if ((rc = do_align(ctx, p, 0, ual, s, true, chg[0]))) return rc;
-  if ((rc = do_align(ctx, p, 1, val, s, true, chg[1]))) return rc;
+  const bool any = p.any.tile >= 0;
+  Plan pf;
+  const Plan& po = any_operands(p, &pf);
+  if (!any && (rc = clear_k_pad(ctx, p, ual, val, s))) return rc;
+  if ((rc = do_align(ctx, po, 0, ual, s, true, chg[0]))) return rc;
+  if ((rc = do_align(ctx, po, 1, val, s, true, chg[1]))) return rc;
   // the workspace holds the nq live slices in order: one batched product of them
   // (none live: no block of W is reached, and the unalign step clears W)
   symt::FusedTables f{};
-  if (p.any.tile >= 0) set_any(p, p.any.ch16, &f);
-  if (p.nq > 0 && (rc = do_gemm(ctx, p.compute, p.nq, p.M, p.kpad, p.gn, ual, val, wal, s,
-                                p.any.tile >= 0 ? &f : nullptr,
+  if (any) set_any(p, p.any.ch16, &f);
+  if (p.nq > 0 && (rc = do_gemm(ctx, p.compute, p.nq, p.M, any ? p.gk : p.kpad, p.gn, ual, val, wal, s,
+                                any ? &f : nullptr,
                                 p.bytes_partial ? part : nullptr, p.bytes_partial, 0, 0, p.bf16_il)))
     return rc;
   if ((rc = do_unalign(ctx, p, wal, s, true, chg[2]))) return rc;

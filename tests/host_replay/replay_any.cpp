@@ -17,7 +17,7 @@
 
 using namespace symt;
 
-static int64_t g_checks = 0, g_fail = 0, g_plans = 0, g_tails = 0, g_am[3] = {}, g_cb = 0, g_odd = 0;
+static int64_t g_checks = 0, g_fail = 0, g_plans = 0, g_tails = 0, g_am[3] = {}, g_cb = 0, g_odd = 0, g_bf = 0;
 static std::string g_case;
 #define CHECK(c, what, x, y)                                                                            \
   do {                                                                                                  \
@@ -46,7 +46,7 @@ static std::vector<int64_t> table(const OffsetParams& o, int G) {
 }
 
 // One tile shape on one plan: the first and last tile of every slice.
-template <int ES, int BM, int BN, int CH, int AM, bool CB>
+template <int ES, int BM, int BN, int CH, int AM, bool CB, bool BF = false>
 void replay_tile(const Plan& p, const std::vector<int64_t>& ra, const std::vector<int64_t>& ca,
                  const std::vector<int64_t>& rb, const std::vector<int64_t>& cb) {
   constexpr int BK = 128 / ES;
@@ -71,7 +71,7 @@ void replay_tile(const Plan& p, const std::vector<int64_t>& ra, const std::vecto
         g_tails += kv < BK;
         constexpr int PE = AM == 0 ? 16 : AM == 2 ? 2 * ES : ES;
         for (int at = 0; at < A_BYTES; at += CH) {
-          const AnySlot x = any_a_slot<ES, BM, AM>(at);
+          const AnySlot x = any_a_slot<ES, BM, AM, BF && AM != 0>(at);
           const int m = std::min(m0 + x.line, any_last_line<CH, PE>(M));
           const int64_t col = AM == 0 ? ca[q * K + k0] : ca[q * K + std::min(k0 + x.k, K - 1)];
           int64_t src = (ra[q * M + m] + col) * ES + (AM == 0 || CH == 4 ? x.sub : 0);
@@ -83,7 +83,7 @@ void replay_tile(const Plan& p, const std::vector<int64_t>& ra, const std::vecto
           for (int d = 0; d < CH / 4; ++d) la[at / 4 + d] = src < 0 ? -1 : src / 4 + d;
         }
         for (int at = 0; at < B_BYTES; at += CH) {
-          const AnySlot x = any_b_slot<ES, BN, CB>(at);
+          const AnySlot x = any_b_slot<ES, BN, CB, BF>(at);
           const int n = std::min(n0 + x.line, any_last_line<CH, ES>(N));
           const int kb = CB ? k0 / 2 : k0;
           const int64_t base = p.any.b ? rb[q * KB + kb] : q * static_cast<int64_t>(K) * N + kb * ldb;
@@ -98,7 +98,7 @@ void replay_tile(const Plan& p, const std::vector<int64_t>& ra, const std::vecto
         }
         for (int m = 0; m < BM && m0 + m < M; ++m)
           for (int k = 0; k < BK; ++k) {
-            const int off = any_a_off<ES, BM, AM>(m, k);
+            const int off = any_a_off<ES, BM, AM, BF && AM != 0>(m, k);
             CHECK(off >= 0 && off + ES <= A_BYTES && off % ES == 0, "A operand read outside its tile", off, m);
             for (int d = 0; d < ES / 4; ++d) {
               const int64_t want = k < kv ? (ra[q * M + m0 + m] + ca[q * K + k0 + k]) * (ES / 4) + d : -1;
@@ -107,7 +107,7 @@ void replay_tile(const Plan& p, const std::vector<int64_t>& ra, const std::vecto
           }
         for (int n = 0; n < BN && n0 + n < N; ++n)
           for (int k = 0; k < BK; ++k) {
-            const int off = any_b_off<ES, BN, CB>(k, n);
+            const int off = any_b_off<ES, BN, CB, BF>(k, n);
             CHECK(off >= 0 && off + ES <= B_BYTES && off % ES == 0, "B operand read outside its tile", off, n);
             int64_t el = -1;
             if (k < kv) {
@@ -143,6 +143,26 @@ void replay_layouts(const Plan& p, const std::vector<int64_t>& ra, const std::ve
   }
 }
 
+// The split-bf16 tiles; their fragments' K indices cover a step once, and a
+// row-major A's come as 16-byte chunks.
+template <int CH, int AM>
+void replay_bf16(const Plan& p, const std::vector<int64_t>& ra, const std::vector<int64_t>& ca,
+                 const std::vector<int64_t>& rb, const std::vector<int64_t>& cb) {
+  if (p.any.tile == 0) replay_tile<4, 128, 128, CH, AM, false, true>(p, ra, ca, rb, cb);
+  else if (p.any.tile == 1) replay_tile<4, 128, 64, CH, AM, false, true>(p, ra, ca, rb, cb);
+  else replay_tile<4, 64, 64, CH, AM, false, true>(p, ra, ca, rb, cb);
+  unsigned seen = 0;
+  for (int g = 0; g < 4; ++g)
+    for (int j = 0; j < 8; ++j) {
+      const int k = any_k_bf16(g, j);
+      seen |= 1u << k;
+      for (int m = 0; m < 16; ++m)
+        CHECK((any_a_off<4, 64, 0>)(m, k) - (any_a_off<4, 64, 0>)(m, any_k_bf16(g, j & 4)) == 4 * (j & 3) &&
+                  (any_a_off<4, 64, 0>)(m, any_k_bf16(g, j & 4)) % 16 == 0, "A fragment is not whole chunks", m, k);
+    }
+  CHECK(seen == ~0u, "fragments do not cover the step", seen, 0);
+}
+
 static void replay_plan(const Plan& p) {
   ++g_plans;
   ++g_am[p.any.am];
@@ -162,6 +182,15 @@ static void replay_plan(const Plan& p) {
   if (p.compute == SYMT_COMPUTE_F64) {
     if (p.any.ch16) replay_layouts<8, 16>(p, ra, ca, rb, cb);
     replay_layouts<8, 4>(p, ra, ca, rb, cb);
+  } else if (p.compute == SYMT_COMPUTE_BF16X3) {
+    ++g_bf;
+    if (p.any.am == 0) {
+      if (p.any.ch16) replay_bf16<16, 0>(p, ra, ca, rb, cb);
+      replay_bf16<4, 0>(p, ra, ca, rb, cb);
+    } else {
+      if (p.any.ch16) replay_bf16<16, 1>(p, ra, ca, rb, cb);
+      replay_bf16<4, 1>(p, ra, ca, rb, cb);
+    }
   } else {
     if (p.any.ch16) replay_layouts<4, 16>(p, ra, ca, rb, cb);
     replay_layouts<4, 4>(p, ra, ca, rb, cb);
@@ -175,7 +204,7 @@ static void replay_plan(const Plan& p) {
 static void check_workspace(const Plan& p) {
   CHECK(p.any.tile >= 0 || (!p.any.b && !p.any.cb && p.any.partial_bytes == 0), "layout of a product not taken",
         p.any.tile, p.any.b);
-  if (!(p.fused || p.fused_ua)) return;
+  if (!(p.fused || p.fused_ua || p.any_direct)) return;
   const size_t G = static_cast<size_t>(p.g.size);
   const bool any = p.any.tile >= 0;
   size_t need = p.fused_ua && !any ? round_up(p.ws_u_al, 256) : 0;
@@ -205,7 +234,7 @@ int main(int argc, char** argv) {
       d = r == 0 ? 1 + rng.below(40) : r == 1 ? 2 * (1 + rng.below(12)) : r == 2 ? 16 : 1 + rng.below(9);
     }
     const bool cplx = rng.below(3) == 0;
-    const int compute = rng.below(2);
+    const int compute = rng.below(cplx ? 2 : 3);   // (F64, F32, split-bf16 on binary32)
     const int dt = cplx ? (compute ? SYMT_C64 : SYMT_C128) : (compute ? SYMT_F32 : SYMT_F64);
     auto desc = [&](const std::string& term, std::string& sg, std::vector<int64_t>& dm, bool second) {
       for (char m : term) {
@@ -224,7 +253,7 @@ int main(int argc, char** argv) {
     std::vector<int64_t> du, dv;
     const symt_tensor u = desc(tu, su, du, false), vv = desc(tv, sv, dv, true);
     const std::string sub = tu + "," + tv + "->" + tw;
-    for (const char* tile : {"", "a96x96s2", "a128x64s2", "a64x64s2"}) {
+    for (const char* tile : {"", "a96x96s2", "a128x128s2", "a128x64s2", "a64x64s2"}) {
       if (*tile) setenv("SYMT_GEMM_TILE", tile, 1);
       else unsetenv("SYMT_GEMM_TILE");
       Plan p;
@@ -248,15 +277,15 @@ int main(int argc, char** argv) {
       g_case = sub + " " + tile;
       check_workspace(pw);
       if (pw.any.tile < 0 || pw.M * pw.gk > 400000 || pw.gk * pw.gn > 400000) continue;
-      g_case = sub + " " + tile + (compute ? " f32" : " f64") + (cplx ? " complex" : "");
+      g_case = sub + " " + tile + (compute == 2 ? " bf16x3" : compute ? " f32" : " f64") + (cplx ? " complex" : "");
       replay_plan(pw);
     }
   }
   unsetenv("SYMT_GEMM_TILE");
   std::printf("%lld checks, %lld plans (A along K %lld, K-major %lld, pairs %lld; complex V in place %lld; 4-byte "
-              "only %lld), %lld K-step tails, %lld failures\n",
+              "only %lld; split-bf16 %lld), %lld K-step tails, %lld failures\n",
               static_cast<long long>(g_checks), static_cast<long long>(g_plans), static_cast<long long>(g_am[0]),
               static_cast<long long>(g_am[1]), static_cast<long long>(g_am[2]), static_cast<long long>(g_cb),
-              static_cast<long long>(g_odd), static_cast<long long>(g_tails), static_cast<long long>(g_fail));
+              static_cast<long long>(g_odd), static_cast<long long>(g_bf), static_cast<long long>(g_tails), static_cast<long long>(g_fail));
   return g_fail ? 1 : 0;
 }

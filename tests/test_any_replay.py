@@ -37,6 +37,6 @@ def test_any_layout_product_replay(tmp_path):
     print(r.stdout)
     assert r.returncode == 0, r.stdout + r.stderr[-4000:]
     assert " 0 failures" in r.stdout
-    m = re.search(r"A along K (\d+), K-major (\d+), pairs (\d+); complex V in place (\d+); 4-byte only (\d+)\), "
-                  r"(\d+) K-step tails", r.stdout)
+    m = re.search(r"A along K (\d+), K-major (\d+), pairs (\d+); complex V in place (\d+); 4-byte only (\d+); "
+                  r"split-bf16 (\d+)\), (\d+) K-step tails", r.stdout)
     assert m and all(int(x) > 0 for x in m.groups()), r.stdout

@@ -82,3 +82,41 @@ def test_any_layout_product(P, case, dtype, tile, monkeypatch):
             outs.append(w.data)
         assert torch.equal(outs[0], outs[2])        # the loads' width does not change the sums
         assert torch.equal(outs[0], outs[1])        # nor does aligning the operands first
+
+
+@pytest.mark.parametrize("tile", ["a128x128s2", "a128x64s2", "a64x64s2"])
+@pytest.mark.parametrize("case", CASES)
+def test_any_layout_split_bf16_product(P, case, tile, monkeypatch):
+    """Split-bf16 on binary32 operands, split as the fragments are read: W in binary32
+    and in binary64 (the same sums), three steps and an odd U the same bits."""
+    sub, orders, cu, cv, du, dv = case
+    monkeypatch.setenv("SYMT_GEMM_TILE", tile)
+    rng = np.random.default_rng(seed("any-bf16", sub, orders))
+    g = O.Group(orders)
+    su = O.Sym.make(cu, int(rng.integers(g.size)), du, g)
+    sv = O.Sym.make(cv, int(rng.integers(g.size)), dv, g)
+    print(f"any split-bf16 {sub} G={orders} {tile}", file=sys.stderr, flush=True)
+
+    def draw(sym):
+        x = torch.from_numpy(rng.standard_normal(sym.reduced_shape())).to(DEV, torch.float32)
+        return P.SymTensor(x, sym.sign_string(), sym.charge, orders)
+    u, v = draw(su), draw(sv)
+    Ru, Rv = H.to_np(u.data).astype(np.float64), H.to_np(v.data).astype(np.float64)
+    ref, _ = O.contract_blocks(sub, Ru, su, Rv, sv)
+    absref, _ = O.contract_blocks(sub, np.abs(Ru), su, np.abs(Rv), sv)
+    fac = H.bound_factor("bf16x3", H.contracted_extent(sub, su))
+    buf = torch.zeros(u.data.numel() + 1, dtype=torch.float32, device=DEV)
+    buf[1:] = u.data.reshape(-1)
+    u_off = P.SymTensor(buf[1:].view(u.data.shape), u.signs, u.charge, u.group)
+    for sk in ("0", "1"):
+        monkeypatch.setenv("SYMT_GEMM_SK", sk)
+        outs = []
+        for uu, wt, steps in ((u, torch.float64, False), (u, torch.float64, True), (u_off, torch.float64, False),
+                              (u, torch.float32, False), (u, torch.float32, True)):
+            w = P.output_like(sub, u, v, dtype=wt)
+            w.data.fill_(float("nan"))
+            P.contract_into(sub, uu, v, w, "bf16x3", steps=steps)
+            outs.append(w.data)
+        assert np.all(np.abs(H.to_np(outs[0]) - ref) <= fac * absref + 1e-300)
+        assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
+        assert torch.equal(outs[3], outs[0].to(torch.float32)) and torch.equal(outs[3], outs[4])
