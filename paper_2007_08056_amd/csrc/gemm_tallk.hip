@@ -49,6 +49,9 @@ struct TkMfma<float> {
 
 constexpr int kTkWaves = 4;
 constexpr int kTkGroup = 16;     // K indices per group (four MFMA K-steps)
+// Shortest runs that the vector variant takes: of 256 indices at most one group
+// in 16 crosses a run's end.
+constexpr int64_t kTkRun = 256;
 
 // TM, TN: 16-row / 16-column tiles of the output (M <= 16 TM, N <= 16 TN).
 // kc: K indices per workgroup (a multiple of kTkGroup); gridDim.x ranges per Q.
@@ -384,6 +387,214 @@ __global__ __launch_bounds__(64 * kTkWaves) void k_gemm_tallk_dma(
   }
 }
 
+// Vector variant, for operands whose groups or columns do not come in whole
+// 16-byte chunks (odd block sizes) but whose K index runs contiguous in A and
+// affine in B for `run` indices and more: the same groups in the same order (the
+// same bits), loaded with 16-byte accesses at element alignment -- A along K, B
+// along its columns, the last chunk of a row clamped to N - VE -- into registers
+// one group ahead and through a wave-private LDS slab into the MFMA layout (rows
+// along K at a pitch of 16 + VE elements, B's at 80: operand reads of both fall
+// on distinct banks).  HBM bound: a group of 16 indices is 16 (M + N) elements for
+// 16 M N multiply-adds, and the one-element loads of the register variant above
+// issue 4 to 8 times the load instructions.  A group that crosses a run's end or
+// the range's end takes each element's (B: each row's) own table entry instead.
+// 4 x (57 x 2963088 x 57), 10.8 GB in f64: 4155 -> 2090 us (5.2 TB/s), f32 1590 -> 1190;
+// 4 x (45 x 1458000 x 45) 972 -> 784 and 617 -> 402 us.  Two groups in flight where
+// their registers fit, and one wave per SIMD for f64 outputs past 48 x 48 (two spill).
+template <typename T, int TM, int TN>
+struct TkSlab {
+  static constexpr int VE = 16 / static_cast<int>(sizeof(T)), GK = kTkGroup;
+  static constexpr int MP = 16 * TM, NP = 16 * TN;
+  static constexpr int LDA = GK + VE;
+  static constexpr int LDB = TN == 4 || TN == 2 ? NP + 16 : NP;   // rows 16 (mod 32) elements apart
+  static constexpr int ACH = GK / VE, BCH = NP / VE;               // chunks per row of A and of B
+  static constexpr int A_LOADS = MP * ACH / 64, B_LOADS = GK * BCH / 64;
+  static constexpr int ELEMS = MP * LDA + GK * LDB;
+  static_assert(A_LOADS * 64 == MP * ACH && B_LOADS * 64 == GK * BCH, "loads must fill whole waves");
+};
+
+template <typename T, int TM, int TN>
+__global__ __launch_bounds__(64 * kTkWaves, (sizeof(T) == 8 && TM * TN >= 12 ? 1 : 2)) void k_gemm_tallk_vec(
+    const T* __restrict__ A, const T* __restrict__ B, T* __restrict__ part, int M, int N, int K, int kc, int run, int rel,
+    const int64_t* __restrict__ ra, const int64_t* __restrict__ ca, const int64_t* __restrict__ rb,
+    const int64_t* __restrict__ cb, int64_t ldb) {
+  using D = TkSlab<T, TM, TN>;
+  using Acc = typename TkMfma<T>::Acc;
+  constexpr int VE = D::VE, GK = D::GK, LDA = D::LDA, LDB = D::LDB, A_LOADS = D::A_LOADS, B_LOADS = D::B_LOADS;
+  constexpr int NP = D::NP;
+  constexpr uint32_t ES = sizeof(T);
+  // groups in flight: two where their registers fit beside the accumulators
+  constexpr int PD = sizeof(T) == 4 || (TM + TN) * 16 + TM * TN * 8 <= 128 ? 2 : 1;
+  typedef T Vec __attribute__((ext_vector_type(VE)));
+  typedef Vec MemVec __attribute__((aligned(sizeof(T))));   // at element alignment
+  __shared__ __attribute__((aligned(16))) T smem[kTkWaves * D::ELEMS];
+  static_assert(D::MP * NP <= kTkWaves * D::ELEMS, "sum space");
+  const int64_t q = blockIdx.y;
+  const int x = blockIdx.x;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+  const int k_begin = x * kc;
+  const int k_end = min(K, k_begin + kc);
+  T* As = smem + wave * D::ELEMS;
+  T* Bs = As + D::MP * LDA;
+
+  // this lane's load sources, fixed across groups (rows past M and chunks past N clamped)
+  // in bytes past the group's first element of A and of B: from the entry of row 0
+  // (column 0) where the later ones lie above it (rel), else from the operand's start
+  const int64_t a_first = ra ? (rel & 1 ? ra[q * M] : 0) : q * M * static_cast<int64_t>(K);
+  const int64_t b_first = cb && (rel & 2) ? cb[q * N] : 0;
+  uint32_t a_src[A_LOADS], b_src[B_LOADS];
+#pragma unroll
+  for (int i = 0; i < A_LOADS; ++i) {
+    const int slot = i * 64 + lane, m = min(slot / D::ACH, M - 1);
+    a_src[i] = static_cast<uint32_t>((ra ? ra[q * M + m] - a_first : m * static_cast<int64_t>(K)) + slot % D::ACH * VE) * ES;
+  }
+#pragma unroll
+  for (int i = 0; i < B_LOADS; ++i) {
+    const int slot = i * 64 + lane, n = min(slot % D::BCH * VE, N - VE);
+    b_src[i] = static_cast<uint32_t>(slot / D::BCH * ldb + (cb ? cb[q * N + n] - b_first : n)) * ES;
+  }
+  // LDS column of this lane's operand columns: a clamped chunk holds columns N - VE and on
+  int b_at[TN];
+#pragma unroll
+  for (int j = 0; j < TN; ++j) {
+    const int n = 16 * j + (lane & 15), whole = N / VE * VE;
+    b_at[j] = n >= whole && n < N ? whole + n - (N - VE) : n;
+  }
+  Vec va[PD][A_LOADS], vb[PD][B_LOADS];
+  // a group's first entries (wave-uniform, fetched one group before its loads)
+  int64_t acol = 0, brow = 0;
+  auto entries = [&](int g) {
+    acol = ca ? ca[q * K + g] : static_cast<int64_t>(g);
+    brow = rb ? rb[q * K + g] : (q * K + g) * static_cast<int64_t>(N);
+  };
+  auto load = [&](int d) {
+    const T* at = A + a_first + acol;
+    const T* bt = B + b_first + brow;
+    const char* a = reinterpret_cast<const char*>(at);
+    const char* b = reinterpret_cast<const char*>(bt);
+#pragma unroll
+    for (int i = 0; i < A_LOADS; ++i) va[d][i] = *reinterpret_cast<const MemVec*>(a + a_src[i]);
+#pragma unroll
+    for (int i = 0; i < B_LOADS; ++i) vb[d][i] = *reinterpret_cast<const MemVec*>(b + b_src[i]);
+  };
+  auto to_lds = [&](int d) {
+#pragma unroll
+    for (int i = 0; i < A_LOADS; ++i) {
+      const int slot = i * 64 + lane;
+      *reinterpret_cast<Vec*>(As + slot / D::ACH * LDA + slot % D::ACH * VE) = va[d][i];
+    }
+#pragma unroll
+    for (int i = 0; i < B_LOADS; ++i) {
+      const int slot = i * 64 + lane;
+      *reinterpret_cast<Vec*>(Bs + slot / D::BCH * LDB + slot % D::BCH * VE) = vb[d][i];
+    }
+  };
+  // any other group: A element by element, B row by row, each through its own table
+  // entry (zeros past the range)
+  auto load_any = [&](int d, int g) {
+    const int k0 = g + lane % D::ACH * VE;
+    int64_t col[VE];
+#pragma unroll
+    for (int e = 0; e < VE; ++e)
+      col[e] = k0 + e < k_end ? (ca ? ca[q * K + k0 + e] : static_cast<int64_t>(k0 + e)) - lane % D::ACH * VE : -1;
+#pragma unroll
+    for (int i = 0; i < A_LOADS; ++i) {
+      const char* at = reinterpret_cast<const char*>(A + a_first) + a_src[i];
+#pragma unroll
+      for (int e = 0; e < VE; ++e)
+        va[d][i][e] = k0 + e < k_end ? *(reinterpret_cast<const T*>(at) + col[e]) : T(0);
+      __builtin_amdgcn_sched_barrier(0);   // (one load's addresses at a time in registers)
+    }
+#pragma unroll
+    for (int i = 0; i < B_LOADS; ++i) {
+      const int row = (i * 64 + lane) / D::BCH, k = g + row;
+      const int64_t off = k < k_end ? (rb ? rb[q * K + k] : (q * K + k) * static_cast<int64_t>(N)) - row * ldb : 0;
+      const char* bt = reinterpret_cast<const char*>(B + b_first + off) + b_src[i];
+      Vec x = {};
+      if (k < k_end) x = *reinterpret_cast<const MemVec*>(bt);
+      vb[d][i] = x;
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+
+  Acc acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] = Acc{};
+  const int gstep = kTkWaves * GK;
+  int g = k_begin + wave * GK;
+  // position of the next group to load in its run (run > gstep), and whether that
+  // group lies inside the run and the range
+  int at_run = g % run;
+  auto whole = [&](int gn) {
+    const bool ok = gn + GK <= k_end && at_run + GK <= run;
+    at_run += gstep;
+    if (at_run >= run) at_run -= run;
+    return ok;
+  };
+  auto fetch = [&](int d, int gn) {
+    if (gn >= k_end) return;
+    if (whole(gn)) load(d);
+    else load_any(d, gn);
+    if (gn + gstep < k_end) entries(gn + gstep);
+  };
+  if (g < k_end) entries(g);
+#pragma unroll
+  for (int d = 0; d < PD; ++d) fetch(d, g + d * gstep);
+  auto step = [&](int d) {
+    to_lds(d);
+    fetch(d, g + PD * gstep);
+#pragma unroll
+    for (int kk = 0; kk < GK; kk += 4) {
+      // (one K-step's operands at a time: the next group's loads hold their registers)
+      if constexpr (sizeof(T) == 8 && TM * TN >= 12) __builtin_amdgcn_sched_barrier(0);
+      const int k = kk + (lane >> 4);
+      T a[TM], b[TN];
+#pragma unroll
+      for (int i = 0; i < TM; ++i) a[i] = As[(16 * i + (lane & 15)) * LDA + k];
+#pragma unroll
+      for (int j = 0; j < TN; ++j) b[j] = Bs[k * LDB + b_at[j]];
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = TkMfma<T>::run(a[i], b[j], acc[i][j]);
+    }
+  };
+  while (g < k_end) {
+#pragma unroll
+    for (int d = 0; d < PD; ++d)
+      if (g < k_end) {
+        step(d);
+        g += gstep;
+      }
+  }
+  // the four waves' sums in wave order (over the slabs, once every wave is done
+  // with its own), then the workgroup's partial [m][n]
+  T* red = smem;
+  __syncthreads();
+  for (int w = 0; w < kTkWaves; ++w) {
+    if (wave == w) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int e = (16 * i + TkMfma<T>::row(lane, r)) * NP + 16 * j + (lane & 15);
+            red[e] = w == 0 ? acc[i][j][r] : red[e] + acc[i][j][r];
+          }
+    }
+    __syncthreads();
+  }
+  T* pw = part + (q * gridDim.x + x) * static_cast<int64_t>(M) * N;
+  for (int e = static_cast<int>(threadIdx.x); e < M * N; e += 64 * kTkWaves) {
+    const int m = e / N, n = e - (e / N) * N;
+    pw[e] = red[m * NP + n];
+  }
+}
+
 // C = the sum over ranges, in range order, of the partials (one thread per
 // output element; grid (elements / 256, Q)).
 template <typename T>
@@ -401,6 +612,32 @@ __global__ __launch_bounds__(256) void k_tallk_sum(const T* __restrict__ part, T
   const int m = e / N, n = e - (e / N) * N;
   const int64_t off = rc ? rc[q * M + m] + cc[q * N + n] : (q * M + m) * static_cast<int64_t>(N) + n;
   C[off] = acc;
+}
+
+// The vector variant's runs along K (0: it does not take these operands): B's
+// columns one run or whole chunks, and every offset inside a group below 4 GiB.
+struct VecRuns {
+  int run, rel;
+  int64_t ldb;
+};
+template <typename T>
+VecRuns vec_runs(const FusedTables* f, int M, int N, int K) {
+  constexpr int VE = 16 / static_cast<int>(sizeof(T));
+  constexpr int64_t most = (int64_t(1) << 31) / static_cast<int64_t>(sizeof(T));
+  VecRuns r{0, 3, N};
+  int64_t run = K, span = static_cast<int64_t>(M) * K;
+  if (f && (f->ra || f->rb)) {
+    run = f->k_run;
+    r.rel = f->vec_rel;
+    if (f->ra) span = f->a_span;
+    if (f->rb) {
+      r.ldb = f->ldb;
+      if (f->v_col_run < N && f->v_col_run % VE != 0) return r;
+      if (f->v_span > most) return r;
+    }
+  }
+  if (span <= most && r.ldb <= most / 32) r.run = static_cast<int>(std::min<int64_t>(run, INT32_MAX));
+  return r;
 }
 
 template <typename T, int TM, int TN>
@@ -425,6 +662,9 @@ hipError_t launch_mn(int64_t batch, int M, int N, int K, const T* A, const T* B,
   if (dma) {
     hipLaunchKernelGGL((k_gemm_tallk_dma<T, TM, TN>), grid, dim3(64 * kTkWaves), 0, s, A, B, part, M, N, K, kc,
                        ra, ca, rb, cb, f && f->rb ? f->ldb : static_cast<int64_t>(N));
+  } else if (const VecRuns r = vec_runs<T>(f, M, N, K); r.run >= kTkRun && N >= VE) {
+    hipLaunchKernelGGL((k_gemm_tallk_vec<T, TM, TN>), grid, dim3(64 * kTkWaves), 0, s, A, B, part, M, N, K, kc,
+                       r.run, r.rel, ra, ca, rb, cb, r.ldb);
   } else if (kl)
     hipLaunchKernelGGL((k_gemm_tallk<T, TM, TN, true>), grid, dim3(64 * kTkWaves), 0, s, A, B, part, M, N, K, kc,
                        ra, ca, rb, cb);

@@ -152,6 +152,11 @@ struct FusedTables {
   int32_t a_krow = 0;               // 1 (A not K-major): A's K index contiguous in 16-byte aligned runs
   int32_t k_groups = 0;             // 1: every 16-deep group of K lies in one run of A's rows and one
                                     //    affine run of B's rows, B's columns in 16-byte chunks (long-K)
+  // long-K product, vector variant: K indices contiguous in A and affine (stride ldb) in
+  // B; the extents that A's row and B's column entries span, from the first one's where
+  // all others lie above it (vec_rel: 1 A's, 2 B's), else from the operand's start
+  int64_t k_run = 1, a_span = 0, v_span = 0;
+  int32_t vec_rel = 0;
   // contiguous runs along V's and W's columns (in reals), and whether W's lanes go along them
   // (row-streaming product with its rows along N)
   int64_t v_col_run = 1, w_col_run = 1;

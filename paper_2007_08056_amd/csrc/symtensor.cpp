@@ -3,6 +3,7 @@
 // product, unalign W).  Declarations and contracts are in include/symtensor.h.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <atomic>
 #include <cstdint>
 #include <cstdlib>
@@ -379,6 +380,12 @@ int do_fused(symt_ctx* ctx, const Plan& p, char* base, hipStream_t s, const int3
   // product loads A along K
   f.a_klanes = p.fused_ua || p.u_k_run >= 16 ? 1 : 0;
   f.k_groups = symt::tallk_groups(p) ? 1 : 0;
+  // (V_al's rows are affine throughout, V's in each contracted block; U_al's run along K)
+  f.k_run = p.cplx || p.a_trans ? 1 : std::min(ua ? p.gk : p.u_k_run, fb ? p.nK : p.gk);
+  // (U_al's rows of a slice, and those of one block, follow its first row; V's columns likewise)
+  f.vec_rel = (ua || p.s == 1 ? 1 : 0) | (!fb || p.t == 1 ? 2 : 0);
+  f.a_span = ua ? p.M * p.gk : p.s == 1 ? p.nI * p.nK : p.U.elems;
+  f.v_span = !fb || p.t == 1 ? 0 : p.V.elems;
   // W's rows contiguous in runs of 4k elements: binary32 tiles store 4 rows per lane
   f.c_rows4 = !p.cplx && p.w_row_run % 4 == 0 ? 1 : 0;
   // K-major A without M chunks: 16-byte loads along U's trailing contracted run instead
