@@ -143,6 +143,12 @@
  * v is not read in place) and the tables.  Where K-steps are the three-step path's, results are identical in
  * value to it: the product sums in the same order.
  *
+ * Subgroup modes: where the last member of every sector group solves its delta
+ * for all stored sectors (its |G|/H divides the other members'), the contraction
+ * runs the same products over its live slices, through offset tables of those
+ * slices, after clearing w where it has blocks that no slice reaches
+ * (info.fused, fused_v and fused_w stay 0).
+ *
  * Execution and ownership.  Every device buffer the caller names (operand
  * data, workspace, aligned buffers) is allocated and owned by the caller.  A
  * context holds the HIP device, timing events, the last error and a cache of

@@ -293,7 +293,7 @@ static bool v_rows_affine(const Plan& p, int64_t* ldb) {
 }
 
 bool v_in_place_layout(const Plan& p, int64_t* ldb, bool* chunks) {
-  if (p.cplx || p.v < 1 || p.t < 1 || p.subgroups) return false;
+  if (p.cplx || p.v < 1 || p.t < 1 || (p.subgroups && !p.slices)) return false;
   // (with K stepped run by run, every step lies in one run and loads are single
   // elements: only the affine rows are needed)
   if (p.compute != SYMT_COMPUTE_F64 && p.compute != SYMT_COMPUTE_F32) return false;
@@ -326,10 +326,11 @@ namespace {
 bool plan_any(Plan* p, int want, bool trailing_k, int64_t run) {
   const bool bf = p->compute == SYMT_COMPUTE_BF16X3;
   if (p->U.dtype != want || p->V.dtype != want) return false;
-  if (bf ? p->cplx || p->subgroups || p->nq != p->g.size || p->M <= 0 || p->N <= 0 || p->Kd <= 0 || p->U.elems <= 0 ||
+  if (bf ? p->cplx || (!p->slices && (p->subgroups || p->nq != p->g.size)) || p->M <= 0 || p->N <= 0 || p->Kd <= 0 || p->U.elems <= 0 ||
                p->v < 1 || p->s < 1 || p->t < 1
          : !(p->fused || p->fused_ua) || p->W.dtype != want)
     return false;
+  const int64_t nb = p->slices ? p->nq : p->g.size;
   const int elem = p->compute == SYMT_COMPUTE_F64 ? 8 : 4;
   const int64_t ve = 16 / elem, bk = 128 / elem, pe = p->cplx ? 2 : 1;
   auto last_run = [](const OperandDesc& X, const int32_t* pos, int count) {
@@ -363,9 +364,9 @@ bool plan_any(Plan* p, int want, bool trailing_k, int64_t run) {
   const char* sk_env = std::getenv("SYMT_GEMM_SK");
   const int sk_mode = sk_env ? std::atoi(sk_env) : -1;
   const AnyChoice c =
-      bf ? choose_any_bf16(p->g.size, p->M, p->gn, ksteps * bk,
+      bf ? choose_any_bf16(nb, p->M, p->gn, ksteps * bk,
                            4.0 * static_cast<double>(p->U.elems + p->V.elems + p->W.elems), y.ch16, forced, sk_mode)
-         : choose_any(p->g.size, p->M, p->gn, ksteps * bk, elem, y.ch16, forced, sk_mode);
+         : choose_any(nb, p->M, p->gn, ksteps * bk, elem, y.ch16, forced, sk_mode);
   if (c.tile < 0) return false;
   if (bf && !forced) {
     // against the product on hi/lo planes
@@ -375,7 +376,7 @@ bool plan_any(Plan* p, int want, bool trailing_k, int64_t run) {
     if (!a_ok || c.time + valign > keep * bf16_planes_time(*p)) return false;
   } else if (!forced) {
     // against the product the plan takes otherwise and its passes over U and V
-    const GemmChoice g = choose_fp_gemm(p->g.size, p->M, p->gn, p->gk, elem, true, p->a_trans);
+    const GemmChoice g = choose_fp_gemm(nb, p->M, p->gn, p->gk, elem, true, p->a_trans);
     if (!a_ok || g.tile == kRowsTile || g.tile == kTallKTile) return false;
     // an aligned form is read and written once, complex rows of V once more
     const double rate = p->cplx ? 1.3e12 : 3.5e12;
@@ -396,9 +397,10 @@ bool plan_any(Plan* p, int want, bool trailing_k, int64_t run) {
 }
 }  // namespace
 
-int make_plan(const char* einsum, const symt_group* group, const symt_tensor* u,
-              const symt_tensor* v, const symt_tensor* w, int32_t compute, Plan* p,
-              std::string* err) {
+namespace {
+// slices: as a fused plan over the live slices (Plan::direct).
+int plan_contraction(const char* einsum, const symt_group* group, const symt_tensor* u, const symt_tensor* v,
+                     const symt_tensor* w, int32_t compute, bool slices, Plan* p, std::string* err) {
   if (!einsum || !p) return fail(err, SYMT_EINVAL, "einsum or plan is NULL");
   int rc = read_group(group, &p->g, err);
   if (rc) return rc;
@@ -677,6 +679,22 @@ int make_plan(const char* einsum, const symt_group* group, const symt_tensor* u,
   p->ws_w_al = p->bytes_w_al / G * nq;
   p->workspace = round_up(p->ws_u_al, 256) + round_up(p->ws_v_al, 256) + round_up(p->ws_w_al, 256);
 
+  // ---- fused over the live slices: every sector group's last member must solve its
+  // delta for all stored sectors (its coefficient's magnitude divides the others')
+  if (slices) {
+    auto solvable = [&](const OperandDesc& X, const int32_t* pos, int count) {
+      for (int i = 0; i + 1 < count; ++i)
+        if ((p->g.size / X.hs[pos[i]]) % (p->g.size / X.hs[pos[count - 1]]) != 0) return false;
+      return count > 0;
+    };
+    p->slices = !p->charges && p->nq > 0 && solvable(p->U, p->posI_u, p->s) &&
+                solvable(p->U, p->posK_u, p->v) && solvable(p->V, p->posJ_v, p->t);
+    int64_t stored = 1;
+    for (int m = 0; m + 1 < p->W.n; ++m) stored *= p->W.hs[m];
+    p->clear_w = p->nq * gs * gt != stored;
+  }
+  const int64_t nb = p->slices ? p->nq : p->g.size;
+
   // ---- fused product: A read from U's standard form along contiguous K runs
   // (U's last v modes are its contracted modes and their block holds whole
   // K-depths), C written straight into W's standard form.
@@ -718,7 +736,7 @@ int make_plan(const char* einsum, const symt_group* group, const symt_tensor* u,
   const bool stepped = !whole_aligned && compute != SYMT_COMPUTE_BF16X3 && !p->cplx && p->U.dtype == want &&
                        (!w || p->W.dtype == want) && p->nK <= INT32_MAX && p->nK > 0 &&
                        p->gk % p->nK == 0 &&
-                       !choose_fp_gemm(p->g.size, p->M, p->gn, p->gk, static_cast<int>(ea), true).dma;
+                       !choose_fp_gemm(nb, p->M, p->gn, p->gk, static_cast<int>(ea), true).dma;
   // U's contracted modes are not its last ones: A is loaded K-major straight from U
   // (row k of a K-step at its own column-table entry, M chunks along U's other
   // modes), as B is from V: on register tiles, and on the 128-row global-to-LDS
@@ -737,13 +755,14 @@ int make_plan(const char* einsum, const symt_group* group, const symt_tensor* u,
   // (where the model's global-to-LDS tile is a 96-row one, which cannot read
   // K-major A, a 128-row one replaces it only for a U large enough that aligning
   // it would cost more than the other tile: 64 MiB; else U is aligned first)
-  const GemmChoice g_any = choose_fp_gemm(p->g.size, p->M, p->gn, p->gk, static_cast<int>(ea), true);
-  const GemmChoice g_at = choose_fp_gemm(p->g.size, p->M, p->gn, p->gk, static_cast<int>(ea), true, true);
+  const GemmChoice g_any = choose_fp_gemm(nb, p->M, p->gn, p->gk, static_cast<int>(ea), true);
+  const GemmChoice g_at = choose_fp_gemm(nb, p->M, p->gn, p->gk, static_cast<int>(ea), true, true);
   const bool at_dma = g_at.dma && a_chunks &&
                       (g_at.tile == g_any.tile || static_cast<double>(ea) * p->U.elems >= 64.0 * (1 << 20));
   const bool at_ok = !trailing_k && compute != SYMT_COMPUTE_BF16X3 && p->U.dtype == want &&
                      (!w || p->W.dtype == want) && (!g_any.dma || at_dma);
-  p->fused = !force_steps && !p->subgroups && p->nq == p->g.size &&
+  const bool whole = slices ? p->slices : !p->subgroups && p->nq == p->g.size;
+  p->fused = !force_steps && whole &&
              (((fp_ok || bf_ok || stepped) && trailing_k) || at_ok) &&
              p->M > 0 && p->N > 0 && p->Kd > 0 && p->U.elems > 0;
   p->a_trans = p->fused && !trailing_k;
@@ -772,13 +791,13 @@ int make_plan(const char* einsum, const symt_group* group, const symt_tensor* u,
     for (int m = p->V.n - 1; m >= 0; --m) { st[m] = a; a *= p->V.dims[m]; }
     for (int i = p->t - 1; i >= 0 && st[p->posJ_v[i]] == p->v_col_run; --i) p->v_col_run *= p->V.dims[p->posJ_v[i]];
   }
-  p->fused_ua = !p->fused && !force_steps && !p->subgroups && p->nq == p->g.size &&
+  p->fused_ua = !p->fused && !force_steps && whole &&
                 (!w || p->W.dtype == (p->cplx ? want : w_want) ||
                  (compute == SYMT_COMPUTE_BF16X3 && p->W.dtype == SYMT_F32)) &&
                 p->M > 0 && p->N > 0 && p->Kd > 0 && p->U.elems > 0 &&
                 (compute != SYMT_COMPUTE_BF16X3 || (w_run >= 16 && !p->cplx));
   if (p->fused || p->fused_ua) {
-    const size_t G = static_cast<size_t>(p->g.size);
+    const size_t G = static_cast<size_t>(nb);
     p->bytes_tables = round_up(8 * G * p->M, 256) * 2 + round_up(8 * G * p->gk, 256) +
                       round_up(8 * G * p->gn, 256);
     p->workspace = (p->fused_ua ? round_up(p->ws_u_al, 256) : 0) + round_up(p->ws_v_al, 256) + p->bytes_tables;
@@ -791,7 +810,7 @@ int make_plan(const char* einsum, const symt_group* group, const symt_tensor* u,
   bool chunks = false;
   if (!vip_off && (p->fused || p->fused_ua) && !p->cplx && p->V.dtype == want &&
       v_in_place_layout(*p, &ldb, &chunks)) {
-    const size_t G = static_cast<size_t>(p->g.size);
+    const size_t G = static_cast<size_t>(nb);
     p->fused_b = true;
     p->fused_b_chunks = chunks;
     p->ldb = ldb;
@@ -823,14 +842,14 @@ int make_plan(const char* einsum, const symt_group* group, const symt_tensor* u,
     // same K-steps and stream-K shares: the same sums
     Plan q;
     if ((rc = make_plan(einsum, group, u, v, w, compute, &q, err))) return rc;
-    p->any = q.any;
+    p->any = q.direct ? q.direct->any : q.any;
     p->any.am = 0;
     p->any.b = p->any.cb = false;
     const int64_t ve = compute == SYMT_COMPUTE_F64 ? 2 : 4;
     p->any.ch16 = p->gk % ve == 0 && p->gn % ve == 0 && p->any.krun % ve == 0;
   } else if (p->any.tile >= 0) {
     // U is not aligned then, nor V where it has tables of its own (4-byte loads take any alignment)
-    const size_t G = static_cast<size_t>(p->g.size);
+    const size_t G = static_cast<size_t>(nb);
     p->any_direct = true;
     if (!p->fused && !p->fused_ua)
       p->bytes_tables = round_up(8 * G * p->M, 256) * 2 + round_up(8 * G * p->gk, 256) + round_up(8 * G * p->gn, 256);
@@ -848,7 +867,27 @@ int make_plan(const char* einsum, const symt_group* group, const symt_tensor* u,
     p->workspace += round_up(p->bytes_partial, 256);
   }
   p->workspace += round_up(p->bytes_charges, 256);
+  // Subgroup modes: in place over the live slices, for the passes over U, V and W
+  // that it saves (the Z_8 ladder with 4 sectors on its output modes, 4 x (2304 x
+  // 4608 x 288) f64: 570 -> 407 us, of which aligning took 148; Z_2 with
+  // one sector on its output modes, f32 blocks of 13 and 7: 75 -> 30).
+  if (p->subgroups && !force_steps && !slices) {
+    auto d = std::make_shared<Plan>();
+    if (plan_contraction(einsum, group, u, v, w, compute, true, d.get(), err) == SYMT_OK && d->slices &&
+        (d->fused || d->fused_ua || d->any_direct)) {
+      p->workspace_steps = p->workspace;
+      p->workspace = std::max(p->workspace, d->workspace);
+      p->direct = std::move(d);
+      p->any = {};
+    }
+  }
   return SYMT_OK;
+}
+}  // namespace
+
+int make_plan(const char* einsum, const symt_group* group, const symt_tensor* u, const symt_tensor* v,
+              const symt_tensor* w, int32_t compute, Plan* p, std::string* err) {
+  return plan_contraction(einsum, group, u, v, w, compute, false, p, err);
 }
 
 std::vector<int32_t> charge_tables_device(const Plan& p, int64_t offset[3]) {
@@ -1130,6 +1169,8 @@ OffsetParams make_offsets(const Plan& p, int operand, bool rows) {
     wsec[m] = w;
     w *= X.hs[m];
   }
+  o.q0 = p.slices ? p.q0 : 0;
+  o.q_step = p.slices ? p.q_step : 1;
   o.gpow = 1;
   for (int i = 0; i + 1 < o.grp.count; ++i) o.gpow *= o.grp.rad[i];
   o.n_inner = 1;

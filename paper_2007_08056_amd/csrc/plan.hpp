@@ -4,6 +4,7 @@
 
 #include <cstddef>
 #include <cstdint>
+#include <memory>
 #include <string>
 #include <vector>
 
@@ -109,6 +110,7 @@ struct OffsetParams {
   int64_t stride[kMaxOrder];        // their standard-form strides
   int64_t weight[kMaxOrder];        // standard-form offset of one unit of each mode's sector
   const int32_t* chg;               // device charge tables of the operand, or nullptr (identity)
+  int32_t q0, q_step;               // table row q' is auxiliary sector q0 + q_step q'
   // affine = 1: entry (q, i) = q * aff_q + i * aff_i (the tables of an aligned form)
   int32_t affine;
   int64_t aff_q, aff_i;
@@ -250,6 +252,14 @@ struct Plan {
     int64_t ldb = 0;                // V's row stride (reals) with b
     size_t partial_bytes = 0;
   } any;
+  // Subgroup modes (fewer live slices than |G|): the same contraction as a fused plan
+  // over its live slices, whose offset tables hold a slice each (slices).  Absent
+  // where a live slice's delta has stored sectors without a solution.  The three
+  // steps' plan keeps describing the contraction (info.fused = 0).
+  std::shared_ptr<const Plan> direct;
+  bool slices = false;
+  bool clear_w = false;             // slices: blocks of W that no slice reaches
+  size_t workspace_steps = 0;       // the three steps' share of `workspace` (with direct)
   bool any_direct = false;          // any, on U's and W's standard forms (not the three-step path)
   size_t bytes_u_al = 0, bytes_v_al = 0, bytes_w_al = 0, workspace = 0;
   size_t ws_u_al = 0, ws_v_al = 0, ws_w_al = 0;   // their regions in the contraction's workspace

@@ -280,7 +280,7 @@ void* cached_tables(symt_ctx* ctx, TableCache* tc, size_t bytes, hipStream_t s, 
 int do_fused(symt_ctx* ctx, const Plan& p, char* base, hipStream_t s, const int32_t* const chg[3],
              TableCache* tc = nullptr) {
   using symt::round_up;
-  const size_t G = static_cast<size_t>(p.g.size);
+  const size_t G = static_cast<size_t>(p.slices ? p.nq : p.g.size);   // rows of each table
   // U aligned first (fused_ua): U_al, then the regions of the fused product
   void* ual = base;
   const bool any = p.any.tile >= 0;          // U in place whatever its layout
@@ -357,6 +357,8 @@ int do_fused(symt_ctx* ctx, const Plan& p, char* base, hipStream_t s, const int3
   if (rc_) return ctx_fail(ctx, rc_, err);
   // split-bf16 on the 256 x 256 wide tile: binary32 U read in place (16-byte aligned)
   const bool wide_fa = p.bf16_wide_fa && !any && aligned16(p.U.data);
+  if (p.clear_w && (rc_ = symt::launch_zero(p.W.data, static_cast<size_t>(p.W.elems) * elem_bytes(p.W.dtype), s, &err)))
+    return ctx_fail(ctx, rc_, err);
   if (ua && (rc_ = clear_k_pad(ctx, p, ual, fb ? nullptr : val, s))) return rc_;
   if (ua && !wide_fa && (rc_ = do_align(ctx, p, 0, ual, s, true, chg[0]))) return rc_;
   Plan pf;
@@ -403,7 +405,7 @@ int do_fused(symt_ctx* ctx, const Plan& p, char* base, hipStream_t s, const int3
     f.ldb = p.ldb;
   }
   if (any) set_any(p, p.any.ch16 && aligned16(p.U.data) && (!fb || aligned16(p.V.data)), &f);
-  return do_gemm(ctx, p.compute, p.g.size, p.M, ua ? p.kpad : p.gk, p.gn,
+  return do_gemm(ctx, p.compute, static_cast<int64_t>(G), p.M, ua ? p.kpad : p.gk, p.gn,
                  ua && !wide_fa ? ual : p.U.data,
                  fb ? p.V.data : val,
                  p.W.data, s, &f,
@@ -632,6 +634,13 @@ int contract_planned(symt_ctx* ctx, const Plan& p, void* workspace, size_t works
     for (int op = 0; op < 3; ++op)
       if (!p.chg[op].empty()) chg[op] = dev + off[op];
   }
+  if (p.direct) {
+    Plan d = *p.direct;
+    d.U.data = p.U.data;
+    d.V.data = p.V.data;
+    d.W.data = p.W.data;
+    return do_fused(ctx, d, base, s, chg, tables);
+  }
   if (p.fused || p.fused_ua || p.any_direct) return do_fused(ctx, p, base, s, chg, tables);
   void* ual = base;
   void* val = base + symt::round_up(p.ws_u_al, 256);
@@ -720,6 +729,10 @@ int symtensor_contract_static(symt_ctx* ctx, const char* einsum, const symt_grou
   int rc = plan_for(ctx, einsum, group, u, v, w, compute, &p);
   if (rc) return rc;
   const size_t cap = SYMT_STATIC_WORKSPACE_BYTES;
+  if (p.workspace > cap && p.direct) {
+    p.direct.reset();
+    p.workspace = p.workspace_steps;
+  }
   if (p.workspace > cap && p.bytes_partial > 0) {
     // without the stream-K pieces (or split-K partial tiles) the product runs
     // one workgroup per tile; the pieces sit just before the charge tables

@@ -136,7 +136,7 @@ __host__ __device__ inline int64_t group_offset_t(const OffsetParams& p, int q, 
   const I digits = i / n_inner;
   I inner = i - digits * n_inner;
   int S[kMaxOrder];
-  (void)fill_sectors(p.g, p.grp, digits, q, S, p.chg);   // offset tables: no subgroup modes
+  (void)fill_sectors(p.g, p.grp, digits, q, S, p.chg);   // (a plan with tables has a solution everywhere)
   int64_t off = 0;
   for (int j = p.grp.count - 1; j >= 0; --j) {
     const I dim = static_cast<I>(p.dim[j]);
@@ -151,7 +151,7 @@ __host__ __device__ inline int64_t group_offset(const OffsetParams& p, int q, in
   return group_offset_t<int64_t>(p, q, i);
 }
 
-// Entry i of an offset table for auxiliary sector q, in reals: complex
+// Entry i of row q of an offset table (auxiliary sector q0 + q_step q), in reals: complex
 // operands double every offset, and their column tables hold (re, im) of each
 // column at 2c, 2c + 1.
 __host__ __device__ inline int64_t table_entry(const OffsetParams& p, int q, int64_t i) {
@@ -161,7 +161,7 @@ __host__ __device__ inline int64_t table_entry(const OffsetParams& p, int q, int
     comp = static_cast<int>(i & 1);
     i >>= 1;
   }
-  return p.scale * group_offset(p, q, i) + comp;
+  return p.scale * group_offset(p, p.q0 + p.q_step * q, i) + comp;
 }
 
 }  // namespace symt

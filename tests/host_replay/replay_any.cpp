@@ -17,7 +17,7 @@
 
 using namespace symt;
 
-static int64_t g_checks = 0, g_fail = 0, g_plans = 0, g_tails = 0, g_am[3] = {}, g_cb = 0, g_odd = 0, g_bf = 0;
+static int64_t g_checks = 0, g_fail = 0, g_plans = 0, g_tails = 0, g_am[3] = {}, g_cb = 0, g_odd = 0, g_bf = 0, g_direct = 0, g_clear = 0;
 static std::string g_case;
 #define CHECK(c, what, x, y)                                                                            \
   do {                                                                                                  \
@@ -205,7 +205,7 @@ static void check_workspace(const Plan& p) {
   CHECK(p.any.tile >= 0 || (!p.any.b && !p.any.cb && p.any.partial_bytes == 0), "layout of a product not taken",
         p.any.tile, p.any.b);
   if (!(p.fused || p.fused_ua || p.any_direct)) return;
-  const size_t G = static_cast<size_t>(p.g.size);
+  const size_t G = static_cast<size_t>(p.slices ? p.nq : p.g.size);
   const bool any = p.any.tile >= 0;
   size_t need = p.fused_ua && !any ? round_up(p.ws_u_al, 256) : 0;
   need += (any && p.any.b ? 0 : round_up(p.ws_v_al, 256)) + 2 * round_up(8 * G * p.M, 256) + round_up(8 * G * p.gk, 256) +
@@ -213,6 +213,37 @@ static void check_workspace(const Plan& p) {
   if (p.fused_b || (any && p.any.b)) need += round_up(8 * G * p.gk, 256) + round_up(8 * G * p.gn, 256);
   need += round_up(p.bytes_partial, 256) + round_up(p.bytes_charges, 256);
   CHECK(need <= p.workspace, "launch layout past the workspace", need, p.workspace);
+}
+
+// A subgroup contraction planned over its live slices: every block that the three
+// steps' transforms move lies where the offset tables put it, and W is cleared
+// exactly where some of its blocks are not reached.
+static void check_direct(const Plan& p) {
+  const Plan& d = *p.direct;
+  ++g_direct;
+  g_clear += d.clear_w;
+  CHECK(!p.fused && !p.fused_ua && p.any.tile < 0 && d.slices && d.nq == p.nq, "direct plan", p.fused, d.nq);
+  CHECK(p.workspace >= d.workspace && p.workspace >= p.workspace_steps, "workspace", p.workspace, d.workspace);
+  for (int op = 0; op < 3; ++op) {
+    const OffsetParams R = make_offsets(d, op, true), C = make_offsets(d, op, false);
+    const XformParams x = make_xform(d, op, true, 8, 8, false, true);
+    std::vector<int64_t> seen;
+    for (int64_t blk = 0; blk < x.nblocks; ++blk) {
+      int64_t sb = -1, ab = -1;
+      const bool ok = block_bases(x, blk, sb, ab);
+      CHECK(ok, "a live block without a solution", op, blk);
+      const int64_t cs = blk % x.gpow_col, rs = blk / x.gpow_col % x.gpow_row;
+      const int q = static_cast<int>(blk / x.gpow_col / x.gpow_row);
+      const int64_t at = table_entry(R, q, rs * R.n_inner) + table_entry(C, q, cs * C.n_inner * (d.cplx ? 2 : 1));
+      CHECK(at == sb, "table entry of a block", at, sb);
+      seen.push_back(sb);
+    }
+    std::sort(seen.begin(), seen.end());
+    CHECK(std::adjacent_find(seen.begin(), seen.end()) == seen.end(), "blocks not distinct", op, x.nblocks);
+    if (op == 2)
+      CHECK((static_cast<int64_t>(seen.size()) * x.blk_elems == d.W.elems * (d.cplx ? 2 : 1)) == !d.clear_w, "blocks not reached",
+            seen.size(), d.clear_w);
+  }
 }
 
 int main(int argc, char** argv) {
@@ -282,6 +313,52 @@ int main(int argc, char** argv) {
     }
   }
   unsetenv("SYMT_GEMM_TILE");
+  for (int c = 0; c < 4 * n; ++c) {
+    const int s = 1 + rng.below(3), t = 1 + rng.below(2), v = 1 + rng.below(2);
+    const std::string L = "abcdefgh", I = L.substr(0, s), K = L.substr(s, v), J = L.substr(s + v, t);
+    const std::string tu = rng.below(2) ? I + K : K + I, tv = rng.below(2) ? K + J : J + K, tw = rng.below(2) ? I + J : J + I;
+    const int G = (int[]){4, 6, 8, 9, 12}[rng.below(5)];
+    symt_group g{};
+    g.nfactors = 1;
+    g.order[0] = G;
+    const bool cplx = rng.below(3) == 0;
+    int32_t hs[8];
+    int64_t dim[8];
+    for (int m = 0; m < 8; ++m) {
+      do hs[m] = 1 + rng.below(G); while (G % hs[m] != 0);
+      if (rng.below(2)) hs[m] = G;
+      dim[m] = 1 + rng.below(5);
+    }
+    struct Op { std::string sg; std::vector<int64_t> d; std::vector<int32_t> h; };
+    auto desc = [&](const std::string& term, Op& o, bool second) {
+      for (char m : term) {
+        o.d.push_back(dim[m - 'a']);
+        o.h.push_back(hs[m - 'a']);
+        const bool neg = (m - 'a') % 2 == 1;
+        o.sg.push_back((second && K.find(m) != std::string::npos ? !neg : neg) ? '-' : '+');
+      }
+      symt_tensor x{};
+      x.nmodes = static_cast<int32_t>(term.size());
+      x.signs = o.sg.c_str();
+      x.charge = rng.below(G);
+      x.dims = o.d.data();
+      x.sectors = o.h.data();
+      x.dtype = cplx ? SYMT_C128 : SYMT_F64;
+      return x;
+    };
+    Op ou, ov;
+    const symt_tensor u = desc(tu, ou, false), vv = desc(tv, ov, true);
+    Plan p;
+    std::string err;
+    g_case = tu + "," + tv + "->" + tw + " sectors";
+    if (make_plan((tu + "," + tv + "->" + tw).c_str(), &g, &u, &vv, nullptr, SYMT_COMPUTE_F64, &p, &err) != SYMT_OK) continue;
+    check_workspace(p);
+    if (p.direct) {
+      check_workspace(*p.direct);
+      check_direct(p);
+    }
+  }
+  std::printf("%lld direct subgroup plans (%lld clear W)\n", static_cast<long long>(g_direct), static_cast<long long>(g_clear));
   std::printf("%lld checks, %lld plans (A along K %lld, K-major %lld, pairs %lld; complex V in place %lld; 4-byte "
               "only %lld; split-bf16 %lld), %lld K-step tails, %lld failures\n",
               static_cast<long long>(g_checks), static_cast<long long>(g_plans), static_cast<long long>(g_am[0]),

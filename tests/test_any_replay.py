@@ -40,3 +40,5 @@ def test_any_layout_product_replay(tmp_path):
     m = re.search(r"A along K (\d+), K-major (\d+), pairs (\d+); complex V in place (\d+); 4-byte only (\d+); "
                   r"split-bf16 (\d+)\), (\d+) K-step tails", r.stdout)
     assert m and all(int(x) > 0 for x in m.groups()), r.stdout
+    m = re.search(r"(\d+) direct subgroup plans \((\d+) clear W\)", r.stdout)
+    assert m and int(m.group(1)) > int(m.group(2)) > 0, r.stdout
