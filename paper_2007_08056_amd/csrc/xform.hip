@@ -16,7 +16,10 @@
 //     a 64 x 64 tile is read into LDS along index A (the source-fastest dims,
 //     merged until 64 elements) and written along index B (the
 //     destination-fastest of the rest), so in-block dims as small as 2 still
-//     fill the tile.
+//     fill the tile.  The tile keeps the source's type: latency bound (decode,
+//     loads and stores of one tile in turn), a binary32 tile of 17 KB admits
+//     twice the workgroups per CU of a binary64 one (V of the Z_8 ladder to bf16
+//     planes, 42 MB in blocks of 576 x 36: 75 -> 31 us).
 // Element conversions (f64 <-> f32, f32 -> bf16 hi/lo pair) are fused.
 #include <hip/hip_runtime.h>
 
@@ -173,7 +176,7 @@ template <typename Tin, int OUT>
 __global__ __launch_bounds__(256) void k_xform_transpose(const Tin* __restrict__ src,
                                                          void* __restrict__ dst,
                                                          const XformParams p) {
-  __shared__ double tile[64][65];
+  __shared__ Tin tile[64][65];
   __shared__ int64_t a_src[64], a_dst[64], b_src[64], b_dst[64];
   __shared__ int perm[64];                        // tr_write: A elements in destination order
   // (the launch has at most 2^31 - 1 workgroups: 32-bit workgroup arithmetic)
@@ -219,11 +222,11 @@ __global__ __launch_bounds__(256) void k_xform_transpose(const Tin* __restrict__
   if (x < na) {
     // all sixteen of this thread's loads go out before the first LDS write
     const int64_t sx = so + a_src[x];
-    double v[16];
+    Tin v[16];
 #pragma unroll
     for (int k = 0; k < 16; ++k) {
       const int j = y + 4 * k;
-      v[k] = live && j < nb ? static_cast<double>(src[sx + b_src[j]]) : 0.0;
+      v[k] = live && j < nb ? src[sx + b_src[j]] : Tin(0);
     }
 #pragma unroll
     for (int k = 0; k < 16; ++k)
@@ -236,14 +239,14 @@ __global__ __launch_bounds__(256) void k_xform_transpose(const Tin* __restrict__
       const int ae = perm[x];
       const int64_t da = dof + a_dst[ae];
       for (int j = y; j < nb; j += 4) {
-        double v[1] = {tile[j][ae]};
+        double v[1] = {static_cast<double>(tile[j][ae])};
         store_vec<OUT, 1>(dst, da + b_dst[j], p.plane, v, p.il);
       }
     }
   } else if (x < nb) {
     const int64_t dx = dof + b_dst[x];
     for (int j = y; j < na; j += 4) {
-      double v[1] = {tile[x][j]};
+      double v[1] = {static_cast<double>(tile[x][j])};
       store_vec<OUT, 1>(dst, dx + a_dst[j], p.plane, v, p.il);
     }
   }
