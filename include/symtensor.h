@@ -131,7 +131,10 @@
  * the planes are interleaved by 32-deep K-steps, and a binary32 u whose
  * contracted modes are its last ones, in runs of 4 or more elements per block,
  * 16-byte aligned, is read in place by the 256 x 256 tile and split in
- * registers (same bits as its planes).  F64 and F32 products that would
+ * registers (same bits as its planes).  Such a u also runs on 256-row tiles of 192
+ * to 288 columns under stream-K where those fit N and the time model prefers them
+ * (info stays that of the product they replace; the three-step path then multiplies
+ * on the same tiles; a u that is not 16-byte aligned takes the replaced product).  F64 and F32 products that would
  * otherwise align an operand, expand a complex v, or run on register-staged
  * tiles take a product that reads u and v in place in any layout and at any
  * alignment where its time model prefers it (K runs of any length stepped run by
@@ -183,7 +186,7 @@
  *                          "tallk" = the long-K
  *                          product taken by default where M and N are at most
  *                          64 and K is 1024 or more;
- *                          BF16X3: "b128x128k32", "bd128x256s3", ...); an
+ *                          BF16X3: "b128x128k32", "bd128x256s3", "bw256x288sk", ...); an
  *                          unknown or inapplicable name is ignored.
  *   SYMT_GEMM_SK=0 | 1     0 forbids stream-K and split K (the long-K product's
  *                          ranges included); 1 forces stream-K on

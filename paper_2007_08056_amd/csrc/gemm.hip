@@ -1279,6 +1279,9 @@ hipError_t launch_bf16x3_wide(int variant, int64_t batch, int M, int N, int K, c
                               void* C, hipStream_t s, int64_t pa, int64_t pb, const int64_t* rc,
                               const int64_t* cc, int c_bytes, bool il, const int64_t* ra, const int64_t* ca);
 
+hipError_t launch_bf16x3_wide_sk(int64_t batch, int M, int N, int K, const void* A, const void* B, void* C,
+                                 hipStream_t s, const FusedTables* f, void* part, size_t part_bytes);
+
 // plane_a / plane_b (split-bf16 only): elements from a hi plane to its lo
 // plane, 0 for the packed layout (batch * m * k, batch * n * k).  il
 // (split-bf16 only): both operands' planes interleaved by 32-deep K-steps, which
@@ -1300,6 +1303,8 @@ int launch_sector_gemm(int compute, int64_t batch, int64_t m, int64_t k, int64_t
                         : compute == SYMT_COMPUTE_F32 ? launch_gemm_any_f32
                                                       : launch_gemm_any_bf16x3;
     e = launch(l, batch, M, N, K, A, B, C, stream, fused, part, part_bytes);
+  } else if (compute == SYMT_COMPUTE_BF16X3 && fused && fused->wide_bn > 0) {
+    e = launch_bf16x3_wide_sk(batch, M, N, K, A, B, C, stream, fused, part, part_bytes);
   } else if (compute == SYMT_COMPUTE_BF16X3) {
     if (K % 8 != 0) {
       if (err) *err = "split-bf16 product needs the contracted extent to be a multiple of 8";

@@ -45,189 +45,246 @@
 
 #include "bf16_split.hpp"
 #include "gemm_common.hpp"
+#include "gemm_tiles.hpp"
 #include "plan.hpp"
 
 namespace symt {
 
 namespace {
 
-template <int BM, int BN, int WM, int WN, int S, bool FC, typename TC, bool IL, bool FA>
+// STEP: a K-step's three products are summed apart and added to the accumulator once,
+// so that it rounds as often as the hi-hi accumulator of the two-accumulator tiles: on
+// the ladders' products 4.436e-6 rms against 4.453e-6 (two accumulators) and 4.461e-6
+// (one, three additions a step), for 9% of the time (366 -> 400 us on 8 x (4608 x 4608
+// x 288)).
+// SK: stream-K (sk_index.hpp): persistent workgroups share the K-steps of all
+// tiles evenly, the accumulators of cut tiles go to `part` for k_sk_fixup.
+template <int BM, int BN, int WM, int WN, int S, bool FC, typename TC, bool IL, bool FA, bool SK = false,
+          bool STEP = false>
 __global__ __launch_bounds__(64 * WM * WN, 1) void k_bf16x3_wide(
     const uint16_t* __restrict__ Ahi, const uint16_t* __restrict__ Alo, const uint16_t* __restrict__ Bhi,
     const uint16_t* __restrict__ Blo, TC* __restrict__ C, int M, int N, int K, int tiles_m, int tiles_n,
     int64_t ntiles, const int64_t* __restrict__ rc, const int64_t* __restrict__ cc, int group_m,
-    const float* __restrict__ U, const int64_t* __restrict__ ra, const int64_t* __restrict__ ca) {
+    const float* __restrict__ U, const int64_t* __restrict__ ra, const int64_t* __restrict__ ca,
+    float* __restrict__ part, int ts) {
   constexpr int NT = 64 * WM * WN;
   constexpr int BK = 32;
   constexpr int TM = BM / WM / 16;
   constexpr int TN = BN / WN / 16;
   constexpr int A_LOADS = BM * 8 / NT;            // 16-byte chunks of both A planes per thread
-  constexpr int B_LOADS = BN * 8 / NT;
+  constexpr int B_LOADS = (BN * 8 + NT - 1) / NT;
+  constexpr bool B_EVEN = B_LOADS * NT == BN * 8; // else the last load is the first waves' alone
   constexpr int PA = BM * 64, PB = BN * 64;       // bytes per plane per stage
   constexpr int STAGE = 2 * PA + 2 * PB;
   static_assert(TM * WM * 16 == BM && TN * WN * 16 == BN, "tile shape");
-  static_assert(A_LOADS * NT == BM * 8 && B_LOADS * NT == BN * 8, "loads must divide evenly");
+  static_assert(A_LOADS * NT == BM * 8 && (B_EVEN || (S == 2 && IL && BN * 8 % 64 == 0)), "loads must fill whole waves");
   static_assert(S >= 2 && S * STAGE <= 160 * 1024, "LDS ring");
   static_assert(FC || std::is_same<TC, double>::value, "aligned W is binary64");
   static_assert(!FA || (IL && S == 2), "A in place: interleaved B planes and two stages");
   __shared__ __attribute__((aligned(1024))) char smem[S * STAGE];
 
-  const int64_t tile = xcd_remap(blockIdx.x, ntiles);
-  int64_t q;
-  int tm, tn;
-  tile_coords(tile, tiles_m, tiles_n, q, tm, tn, group_m);
-  const int m0 = tm * BM, n0 = tn * BN;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm0 = (wave / WN) * (BM / WM);
   const int wn0 = (wave % WN) * (BN / WN);
-  const int64_t offA = q * static_cast<int64_t>(M) * K * (IL ? 2 : 1);
-  const int64_t offB = q * static_cast<int64_t>(N) * K * (IL ? 2 : 1);
+  const int steps = K / BK;
+  SkSlot sl{0, 0, 1};
+  int64_t it = 0, end = 1, first = 0;
+  if constexpr (SK) {
+    sl = sk_slot(static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x), ts);
+    const int64_t total = ntiles / ts * steps;
+    it = sk_bound(sl.team, total, sl.nteam);
+    end = sk_bound(sl.team + 1, total, sl.nteam);
+    first = it / steps;
+  }
+  while (it < end) {
+    int64_t q, grp = 0;
+    int tm, tn, kt0 = 0, nk = steps;                // this workgroup's K-steps of the tile: nk from kt0
+    if constexpr (SK) {
+      grp = it / steps;
+      kt0 = static_cast<int>(it - grp * steps);
+      nk = static_cast<int>(min(static_cast<int64_t>(steps - kt0), end - it));
+      const int64_t tile = grp * ts + sl.member;
+      tn = static_cast<int>(tile % tiles_n);
+      const int64_t t2 = tile / tiles_n;
+      tm = static_cast<int>(t2 % tiles_m);
+      q = t2 / tiles_m;
+      __syncthreads();                              // the previous piece's LDS reads are done
+    } else {
+      tile_coords(xcd_remap(blockIdx.x, ntiles), tiles_m, tiles_n, q, tm, tn, group_m);
+    }
+    const int m0 = tm * BM, n0 = tn * BN;
+    const int64_t offA = q * static_cast<int64_t>(M) * K * (IL ? 2 : 1);
+    const int64_t offB = q * static_cast<int64_t>(N) * K * (IL ? 2 : 1);
 
-  // Load slot s = tid + i * NT covers [plane][row][chunk]; LDS position c of row
-  // r holds global chunk c ^ ((r >> 1) & 3).  IL: slot s covers [row][chunk of
-  // 8] and position c of row r holds chunk c ^ (r & 7) of the row's K-step
-  // (chunks 0-3 hi, 4-7 lo).
-  const uint16_t* a_src[A_LOADS];
-  // FA: U's row offset and the in-step K offset (4 x chunk) of each load slot,
-  // and the column offsets of the next K-step to issue
-  const float* a_row[A_LOADS];
-  int a_k[A_LOADS];
-  int64_t a_col[A_LOADS];
-#pragma unroll
-  for (int i = 0; i < A_LOADS; ++i) {
-    const int slot = tid + i * NT;
-    if constexpr (FA) {
-      const int r = slot >> 3;
-      a_row[i] = U + ra[q * M + min(m0 + r, M - 1)];
-      a_k[i] = ((slot & 7) ^ (r & 7)) * 4;
-    } else if constexpr (IL) {
-      const int r = slot >> 3;
-      a_src[i] = Ahi + offA + static_cast<int64_t>(min(m0 + r, M - 1)) * 2 * K + ((slot & 7) ^ (r & 7)) * 8;
-    } else {
-      const int plane = slot / (BM * 4);
-      const int rem = slot - plane * (BM * 4);
-      const int r = rem >> 2, c = rem & 3;
-      const int gr = min(m0 + r, M - 1);
-      a_src[i] = (plane ? Alo : Ahi) + offA + static_cast<int64_t>(gr) * K + (c ^ ((r >> 1) & 3)) * 8;
-    }
-  }
-  const uint16_t* b_src[B_LOADS];
-#pragma unroll
-  for (int i = 0; i < B_LOADS; ++i) {
-    const int slot = tid + i * NT;
-    if constexpr (IL) {
-      const int r = slot >> 3;
-      b_src[i] = Bhi + offB + static_cast<int64_t>(min(n0 + r, N - 1)) * 2 * K + ((slot & 7) ^ (r & 7)) * 8;
-    } else {
-      const int plane = slot / (BN * 4);
-      const int rem = slot - plane * (BN * 4);
-      const int r = rem >> 2, c = rem & 3;
-      const int gr = min(n0 + r, N - 1);
-      b_src[i] = (plane ? Blo : Bhi) + offB + static_cast<int64_t>(gr) * K + (c ^ ((r >> 1) & 3)) * 8;
-    }
-  }
-  auto fetch_cols = [&](int kt) {
-#pragma unroll
-    for (int i = 0; i < A_LOADS; ++i) a_col[i] = ca[q * K + kt * BK + a_k[i]];
-  };
-  auto issue = [&](int kt, int stage) {
-    const int k0 = kt * (IL ? 2 * BK : BK);
-    char* base = smem + stage * STAGE;
+    // Load slot s = tid + i * NT covers [plane][row][chunk]; LDS position c of row
+    // r holds global chunk c ^ ((r >> 1) & 3).  IL: slot s covers [row][chunk of
+    // 8] and position c of row r holds chunk c ^ (r & 7) of the row's K-step
+    // (chunks 0-3 hi, 4-7 lo).
+    const uint16_t* a_src[A_LOADS];
+    // FA: U's row offset and the in-step K offset (4 x chunk) of each load slot,
+    // and the column offsets of the next K-step to issue
+    const float* a_row[A_LOADS];
+    int a_k[A_LOADS];
+    int64_t a_col[A_LOADS];
 #pragma unroll
     for (int i = 0; i < A_LOADS; ++i) {
-      if constexpr (FA) lds_dma16(a_row[i] + a_col[i], base + (i * NT + wave * 64) * 16);
-      else lds_dma16(a_src[i] + k0, base + (i * NT + wave * 64) * 16);
-    }
-#pragma unroll
-    for (int i = 0; i < B_LOADS; ++i) lds_dma16(b_src[i] + k0, base + 2 * PA + (i * NT + wave * 64) * 16);
-  };
-
-  f4 acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j) acc[i][j] = f4{};
-
-  const int nk = K / BK;
-  const int kc = lane >> 4;                       // operand chunk: k = 8 * kc .. 8 * kc + 7
-  if constexpr (FA) {
-    // (two stages: the loop's wait for nothing outstanding also covers the
-    // column offsets fetched one step ahead)
-    if (nk > 0) {
-      fetch_cols(0);
-      wait_vmcnt<0>();
-      issue(0, 0);
-      if (nk > 1) fetch_cols(1);
-    }
-  } else {
-#pragma unroll
-    for (int s = 0; s < S - 1; ++s)
-      if (s < nk) issue(s, s);
-  }
-  for (int kt = 0; kt < nk; ++kt) {
-    // step kt has landed once at most (S - 2) later steps' loads are outstanding
-    if (kt + S - 2 < nk) wait_vmcnt<(S - 2) * (A_LOADS + B_LOADS)>();
-    else wait_vmcnt<0>();
-    // a plain barrier: the wait above covers this wave's loads of step kt, and
-    // every wave has finished reading the stage that the next issue overwrites
-    asm volatile("s_barrier" ::: "memory");
-    if (kt + S - 1 < nk) {
-      issue(kt + S - 1, (kt + S - 1) % S);
-      if constexpr (FA)
-        if (kt + 2 < nk) fetch_cols(kt + 2);
-    }
-    const char* base = smem + (kt % S) * STAGE;
-    bf8 ah[TM], al[TM];
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-      const int r = wm0 + i * 16 + (lane & 15);
+      const int slot = tid + i * NT;
       if constexpr (FA) {
-        // K 8 kc .. 8 kc + 7 of row r: chunks 2 kc and 2 kc + 1
-        const fv4 x0 = *reinterpret_cast<const fv4*>(base + r * 128 + (((2 * kc) ^ (r & 7)) << 4));
-        const fv4 x1 = *reinterpret_cast<const fv4*>(base + r * 128 + (((2 * kc + 1) ^ (r & 7)) << 4));
-        split8(x0, x1, ah[i], al[i]);
+        const int r = slot >> 3;
+        a_row[i] = U + ra[q * M + min(m0 + r, M - 1)];
+        a_k[i] = ((slot & 7) ^ (r & 7)) * 4;
+      } else if constexpr (IL) {
+        const int r = slot >> 3;
+        a_src[i] = Ahi + offA + static_cast<int64_t>(min(m0 + r, M - 1)) * 2 * K + ((slot & 7) ^ (r & 7)) * 8;
       } else {
-        const int off = IL ? r * 128 + ((kc ^ (r & 7)) << 4) : r * 64 + ((kc ^ ((r >> 1) & 3)) << 4);
-        const int off_lo = IL ? r * 128 + (((4 + kc) ^ (r & 7)) << 4) : PA + off;
-        ah[i] = *reinterpret_cast<const bf8*>(base + off);
-        al[i] = *reinterpret_cast<const bf8*>(base + off_lo);
+        const int plane = slot / (BM * 4);
+        const int rem = slot - plane * (BM * 4);
+        const int r = rem >> 2, c = rem & 3;
+        const int gr = min(m0 + r, M - 1);
+        a_src[i] = (plane ? Alo : Ahi) + offA + static_cast<int64_t>(gr) * K + (c ^ ((r >> 1) & 3)) * 8;
       }
     }
+    const uint16_t* b_src[B_LOADS];
 #pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      const int r = wn0 + j * 16 + (lane & 15);
-      const int off = 2 * PA + (IL ? r * 128 + ((kc ^ (r & 7)) << 4) : r * 64 + ((kc ^ ((r >> 1) & 3)) << 4));
-      const int off_lo = IL ? 2 * PA + r * 128 + (((4 + kc) ^ (r & 7)) << 4) : PB + off;
-      const bf8 bh = *reinterpret_cast<const bf8*>(base + off);
-      const bf8 bl = *reinterpret_cast<const bf8*>(base + off_lo);
-      // consecutive MFMAs update different accumulators (no dependent back-to-back pairs)
-#pragma unroll
-      for (int i = 0; i < TM; ++i) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al[i], bh, acc[i][j], 0, 0, 0);
-#pragma unroll
-      for (int i = 0; i < TM; ++i) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[i], bl, acc[i][j], 0, 0, 0);
-#pragma unroll
-      for (int i = 0; i < TM; ++i) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[i], bh, acc[i][j], 0, 0, 0);
+    for (int i = 0; i < B_LOADS; ++i) {
+      const int slot = tid + i * NT;
+      if constexpr (IL) {
+        const int r = B_EVEN ? slot >> 3 : min(slot >> 3, BN - 1);
+        b_src[i] = Bhi + offB + static_cast<int64_t>(min(n0 + r, N - 1)) * 2 * K + ((slot & 7) ^ (r & 7)) * 8;
+      } else {
+        const int plane = slot / (BN * 4);
+        const int rem = slot - plane * (BN * 4);
+        const int r = rem >> 2, c = rem & 3;
+        const int gr = min(n0 + r, N - 1);
+        b_src[i] = (plane ? Blo : Bhi) + offB + static_cast<int64_t>(gr) * K + (c ^ ((r >> 1) & 3)) * 8;
+      }
     }
-  }
-
-  // 16x16x32 bf16 accumulator layout: lane l, item r holds row 4 (l / 16) + r, column l % 16
-  TC* Cq = C + (FC ? 0 : q * static_cast<int64_t>(M) * N);
+    auto fetch_cols = [&](int kt) {
 #pragma unroll
-  for (int j = 0; j < TN; ++j) {
-    const int col = n0 + wn0 + j * 16 + (lane & 15);
-    const int64_t ccol = (FC && col < N) ? cc[q * N + col] : col;
+      for (int i = 0; i < A_LOADS; ++i) a_col[i] = ca[q * K + (kt0 + kt) * BK + a_k[i]];
+    };
+    auto issue = [&](int kt, int stage) {
+      const int k0 = (kt0 + kt) * (IL ? 2 * BK : BK);
+      char* base = smem + stage * STAGE;
+#pragma unroll
+      for (int i = 0; i < A_LOADS; ++i) {
+        if constexpr (FA) lds_dma16(a_row[i] + a_col[i], base + (i * NT + wave * 64) * 16);
+        else lds_dma16(a_src[i] + k0, base + (i * NT + wave * 64) * 16);
+      }
+#pragma unroll
+      for (int i = 0; i < B_LOADS; ++i)
+        if (B_EVEN || i + 1 < B_LOADS || (i * NT + wave * 64) < BN * 8)
+          lds_dma16(b_src[i] + k0, base + 2 * PA + (i * NT + wave * 64) * 16);
+    };
+
+    f4 acc[TM][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int row = m0 + wm0 + i * 16 + 4 * (lane >> 4) + r;
-        if (row < M && col < N) {
-          const int64_t crow = FC ? rc[q * M + row] : static_cast<int64_t>(row) * N;
-          Cq[crow + ccol] = static_cast<TC>(acc[i][j][r]);
+      for (int j = 0; j < TN; ++j) acc[i][j] = f4{};
+
+    const int kc = lane >> 4;                       // operand chunk: k = 8 * kc .. 8 * kc + 7
+    if constexpr (FA) {
+      // (two stages: the loop's wait for nothing outstanding also covers the
+      // column offsets fetched one step ahead)
+      if (nk > 0) {
+        fetch_cols(0);
+        wait_vmcnt<0>();
+        issue(0, 0);
+        if (nk > 1) fetch_cols(1);
+      }
+    } else {
+#pragma unroll
+      for (int s = 0; s < S - 1; ++s)
+        if (s < nk) issue(s, s);
+    }
+    for (int kt = 0; kt < nk; ++kt) {
+      // step kt has landed once at most (S - 2) later steps' loads are outstanding
+      if (kt + S - 2 < nk) wait_vmcnt<(S - 2) * (A_LOADS + B_LOADS)>();
+      else wait_vmcnt<0>();
+      // a plain barrier: the wait above covers this wave's loads of step kt, and
+      // every wave has finished reading the stage that the next issue overwrites
+      asm volatile("s_barrier" ::: "memory");
+      if (kt + S - 1 < nk) {
+        issue(kt + S - 1, (kt + S - 1) % S);
+        if constexpr (FA)
+          if (kt + 2 < nk) fetch_cols(kt + 2);
+      }
+      const char* base = smem + (kt % S) * STAGE;
+      bf8 ah[TM], al[TM];
+#pragma unroll
+      for (int i = 0; i < TM; ++i) {
+        const int r = wm0 + i * 16 + (lane & 15);
+        if constexpr (FA) {
+          // K 8 kc .. 8 kc + 7 of row r: chunks 2 kc and 2 kc + 1
+          const fv4 x0 = *reinterpret_cast<const fv4*>(base + r * 128 + (((2 * kc) ^ (r & 7)) << 4));
+          const fv4 x1 = *reinterpret_cast<const fv4*>(base + r * 128 + (((2 * kc + 1) ^ (r & 7)) << 4));
+          split8(x0, x1, ah[i], al[i]);
+        } else {
+          const int off = IL ? r * 128 + ((kc ^ (r & 7)) << 4) : r * 64 + ((kc ^ ((r >> 1) & 3)) << 4);
+          const int off_lo = IL ? r * 128 + (((4 + kc) ^ (r & 7)) << 4) : PA + off;
+          ah[i] = *reinterpret_cast<const bf8*>(base + off);
+          al[i] = *reinterpret_cast<const bf8*>(base + off_lo);
         }
       }
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        const int r = wn0 + j * 16 + (lane & 15);
+        const int off = 2 * PA + (IL ? r * 128 + ((kc ^ (r & 7)) << 4) : r * 64 + ((kc ^ ((r >> 1) & 3)) << 4));
+        const int off_lo = IL ? 2 * PA + r * 128 + (((4 + kc) ^ (r & 7)) << 4) : PB + off;
+        const bf8 bh = *reinterpret_cast<const bf8*>(base + off);
+        const bf8 bl = *reinterpret_cast<const bf8*>(base + off_lo);
+        if constexpr (STEP) {
+          // the K-step's sum apart from the accumulator: one rounding at its size
+          f4 t[TM];
+#pragma unroll
+          for (int i = 0; i < TM; ++i) t[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al[i], bh, f4{}, 0, 0, 0);
+#pragma unroll
+          for (int i = 0; i < TM; ++i) t[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[i], bl, t[i], 0, 0, 0);
+#pragma unroll
+          for (int i = 0; i < TM; ++i) t[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[i], bh, t[i], 0, 0, 0);
+#pragma unroll
+          for (int i = 0; i < TM; ++i) acc[i][j] += t[i];
+        } else {
+          // consecutive MFMAs update different accumulators (no dependent back-to-back pairs)
+#pragma unroll
+          for (int i = 0; i < TM; ++i) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al[i], bh, acc[i][j], 0, 0, 0);
+#pragma unroll
+          for (int i = 0; i < TM; ++i) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[i], bl, acc[i][j], 0, 0, 0);
+#pragma unroll
+          for (int i = 0; i < TM; ++i) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[i], bh, acc[i][j], 0, 0, 0);
+        }
+      }
+    }
+
+    if constexpr (SK) {
+      if (nk < steps) {
+        store_piece<TM, TN>(part + sk_piece(sl.team, sl.member, ts, grp, first) * (BM * BN), acc);
+        it += nk;
+        continue;
+      }
+    }
+    // 16x16x32 bf16 accumulator layout: lane l, item r holds row 4 (l / 16) + r, column l % 16
+    TC* Cq = C + (FC ? 0 : q * static_cast<int64_t>(M) * N);
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      const int col = n0 + wn0 + j * 16 + (lane & 15);
+      const int64_t ccol = (FC && col < N) ? cc[q * N + col] : col;
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int row = m0 + wm0 + i * 16 + 4 * (lane >> 4) + r;
+          if (row < M && col < N) {
+            const int64_t crow = FC ? rc[q * M + row] : static_cast<int64_t>(row) * N;
+            Cq[crow + ccol] = static_cast<TC>(acc[i][j][r]);
+          }
+        }
+    }
+    it += nk;
+    if constexpr (!SK) break;
   }
 }
 
@@ -250,19 +307,78 @@ hipError_t launch_wide(int64_t batch, int M, int N, int K, const void* A, const 
   if (gm < 1) gm = 1;
   if (rc && c_bytes == 4)
     hipLaunchKernelGGL((k_bf16x3_wide<BM, BN, WM, WN, S, true, float, IL, FA>), grid, block, 0, s, a, a + pa, b, b + pb,
-                       static_cast<float*>(C), M, N, K, tiles_m, tiles_n, ntiles, rc, cc, gm, u, ra, ca);
+                       static_cast<float*>(C), M, N, K, tiles_m, tiles_n, ntiles, rc, cc, gm, u, ra, ca, nullptr, 0);
   else if (rc)
     hipLaunchKernelGGL((k_bf16x3_wide<BM, BN, WM, WN, S, true, double, IL, FA>), grid, block, 0, s, a, a + pa, b, b + pb,
-                       static_cast<double*>(C), M, N, K, tiles_m, tiles_n, ntiles, rc, cc, gm, u, ra, ca);
+                       static_cast<double*>(C), M, N, K, tiles_m, tiles_n, ntiles, rc, cc, gm, u, ra, ca, nullptr, 0);
   else if constexpr (!FA)
     hipLaunchKernelGGL((k_bf16x3_wide<BM, BN, WM, WN, S, false, double, IL, false>), grid, block, 0, s, a, a + pa, b,
-                       b + pb, static_cast<double*>(C), M, N, K, tiles_m, tiles_n, ntiles, rc, cc, gm, u, ra, ca);
+                       b + pb, static_cast<double*>(C), M, N, K, tiles_m, tiles_n, ntiles, rc, cc, gm, u, ra, ca, nullptr, 0);
   else
     return hipErrorInvalidValue;   // A in place writes W in place
   return hipGetLastError();
 }
 
+// 256 x BN tiles under stream-K, where N fills them and whole rounds of one-workgroup
+// tiles would not fill the device: 64 x BN / 2 blocks per wave read each A fragment for
+// BN / 32 column tiles, which halves the LDS and L2 traffic per product of the 128 x 128
+// register tile (8 x (4608 x 4608 x 288): 470 -> 330 us).  C: W through its tables, or the aligned W.
+template <int BN, bool FA, bool FC, typename TC>
+hipError_t launch_wide_sk(int64_t batch, int M, int N, int K, const void* A, const void* B, TC* C, hipStream_t s,
+                          const int64_t* rc, const int64_t* cc, const int64_t* ra, const int64_t* ca, float* part,
+                          size_t part_bytes) {
+  constexpr int BM = 256, WM = 4, WN = 2;
+  const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
+  const int64_t ntiles = batch * tiles_m * tiles_n;
+  const uint16_t* a = FA ? nullptr : static_cast<const uint16_t*>(A);
+  const float* u = FA ? static_cast<const float*>(A) : nullptr;
+  const uint16_t* b = static_cast<const uint16_t*>(B);
+  const SkLaunch sl = part ? sk_launch(ntiles, tiles_n, K / 32, device_cus(),
+                                       static_cast<int64_t>(part_bytes / sizeof(float)),
+                                       static_cast<int64_t>(BM) * BN, kSkMinIters)
+                           : SkLaunch{};
+  const dim3 block(64 * WM * WN);
+  if (sl.P == 0) {   // no room for the pieces: one workgroup per tile
+    hipLaunchKernelGGL((k_bf16x3_wide<BM, BN, WM, WN, 2, FC, TC, true, FA, false, true>), dim3(static_cast<unsigned>(ntiles)),
+                       block, 0, s, a, a, b, b, C, M, N, K, tiles_m, tiles_n, ntiles, rc, cc, 8, u, ra, ca, nullptr, 0);
+    return hipGetLastError();
+  }
+  hipLaunchKernelGGL((k_bf16x3_wide<BM, BN, WM, WN, 2, FC, TC, true, FA, true, true>), dim3(static_cast<unsigned>(sl.P)), block,
+                     0, s, a, a, b, b, C, M, N, K, tiles_m, tiles_n, ntiles, rc, cc, 8, u, ra, ca, part, sl.ts);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  const dim3 fgrid = sk_fixup_grid(ntiles, sl.ts, K / 32, sl.P / sl.ts, static_cast<int64_t>(BM) * BN, 64 * WM * WN);
+  hipLaunchKernelGGL((k_sk_fixup<float, BM, BN, WM, WN, FC, float, TC>), fgrid, block, 0, s, part, C, M, N, K / 32,
+                     tiles_m, tiles_n, ntiles, sl.ts, sl.P / sl.ts, rc, cc);
+  return hipGetLastError();
+}
+template <int BN>
+hipError_t launch_wide_bn(int64_t batch, int M, int N, int K, const void* A, const void* B, void* C, hipStream_t s,
+                          const FusedTables* f, float* part, size_t part_bytes) {
+  const int64_t *rc = f->rc, *cc = f->cc, *ra = f->ra, *ca = f->ca;
+  if (!rc) return launch_wide_sk<BN, false, false>(batch, M, N, K, A, B, static_cast<double*>(C), s, rc, cc, ra, ca, part, part_bytes);
+  if (!ra) return hipErrorInvalidValue;   // (W in place: U in place too)
+  if (f->c_bytes == 4)
+    return launch_wide_sk<BN, true, true>(batch, M, N, K, A, B, static_cast<float*>(C), s, rc, cc, ra, ca, part, part_bytes);
+  return launch_wide_sk<BN, true, true>(batch, M, N, K, A, B, static_cast<double*>(C), s, rc, cc, ra, ca, part, part_bytes);
+}
+
 }  // namespace
+
+// The 256 x f->wide_bn tiles (192, 224, 256 or 288 columns) on interleaved planes of
+// B: A read in place (f->ra) with W through its tables, or A on planes and the aligned W.
+hipError_t launch_bf16x3_wide_sk(int64_t batch, int M, int N, int K, const void* A, const void* B, void* C,
+                                 hipStream_t s, const FusedTables* f, void* part, size_t part_bytes) {
+  if (K % 32 != 0) return hipErrorInvalidValue;
+  float* pt = static_cast<float*>(part);
+  switch (f->wide_bn) {
+    case 192: return launch_wide_bn<192>(batch, M, N, K, A, B, C, s, f, pt, part_bytes);
+    case 224: return launch_wide_bn<224>(batch, M, N, K, A, B, C, s, f, pt, part_bytes);
+    case 256: return launch_wide_bn<256>(batch, M, N, K, A, B, C, s, f, pt, part_bytes);
+    case 288: return launch_wide_bn<288>(batch, M, N, K, A, B, C, s, f, pt, part_bytes);
+  }
+  return hipErrorInvalidValue;
+}
 
 // Wide split-bf16 tiles: 0 = 256 x 256 (8 waves of 128 x 64, two LDS stages),
 // 1 = 256 x 128 (4 waves of 128 x 64, three stages).  pa / pb: elements from

@@ -244,6 +244,10 @@ double bf16_planes_time(const Plan& p) {
     bm = 256, bn = wide == 0 ? 256 : 128, eff = 0.93;
   } else if (!bf16x3_register_tile(p.M, p.gn, p.kpad)) {
     bn = 256, eff = 0.72;
+  } else if (p.fused) {
+    const int tile = bf16x3_fused_tile(p.M, p.gn);
+    bn = tile == 0 ? 64 : tile == 2 ? 256 : tile == 3 ? 96 : 128;
+    if (tile == 0) eff *= 0.5;
   } else if (p.gn <= 64) {
     bn = 64, eff *= 0.5;
   } else if (p.gn >= 1024 && p.M >= 1024) {
@@ -371,8 +375,10 @@ bool plan_any(Plan* p, int want, bool trailing_k, int64_t run) {
   if (bf && !forced) {
     // against the product on hi/lo planes
     const double valign = y.b ? 0 : 8.0 * static_cast<double>(p->V.elems) / 3.5e12 + 8e-6;
-    // (0.7: the model is least sure where planes run on global-to-LDS tiles)
-    const double keep = p->kpad % 32 == 0 && !bf16x3_register_tile(p->M, p->gn, p->kpad) ? 0.7 : 0.85;
+    // (0.7: the model is least sure where planes run on global-to-LDS tiles, and for
+    // K-major A with 4-byte loads: 5 x (2300 x 1540 x 585) took 256 us, 230 on planes)
+    const bool unsure = (p->kpad % 32 == 0 && !bf16x3_register_tile(p->M, p->gn, p->kpad)) || (y.am == 1 && !y.ch16);
+    const double keep = unsure ? 0.7 : 0.85;
     if (!a_ok || c.time + valign > keep * bf16_planes_time(*p)) return false;
   } else if (!forced) {
     // against the product the plan takes otherwise and its passes over U and V
@@ -393,11 +399,61 @@ bool plan_any(Plan* p, int want, bool trailing_k, int64_t run) {
   y.sk = c.sk;
   y.ldb = ldb;
   y.partial_bytes = c.partial_bytes;
+  y.time = c.time;
   return true;
 }
 }  // namespace
 
 namespace {
+// Split-bf16 on 256 x wide_bn tiles under stream-K (Plan::direct): a binary32 U whose
+// contracted modes are its last ones in runs of 4, K in whole 32-deep steps.
+void plan_wide(Plan* p, bool trailing_k) {
+  const char* fa_env = std::getenv("SYMT_BF16_FA");
+  if (p->cplx || p->U.dtype != SYMT_F32 || p->V.dtype != SYMT_F32 || !trailing_k || p->nK % 4 != 0 || p->gk % 32 != 0 ||
+      p->M < 256 || p->gn <= 0 || p->v < 1 || p->w_col_run < 16 || (fa_env && std::atoi(fa_env) == 0))
+    return;
+  const char* tile = std::getenv("SYMT_GEMM_TILE");
+  const char* sk_env = std::getenv("SYMT_GEMM_SK");
+  if (sk_env && std::atoi(sk_env) == 0) return;
+  int bn = 0;
+  int64_t padded = 0;
+  for (int c : {288, 256, 224, 192}) {
+    if (tile && *tile && std::string("bw256x") + std::to_string(c) + "sk" != tile) continue;
+    const int64_t n = (p->gn + c - 1) / c * c;
+    if (bn == 0 || n < padded) bn = c, padded = n;
+  }
+  if (bn == 0) return;
+  auto d = std::make_shared<Plan>(*p);
+  d->fused = d->fused_b = d->any_direct = false;
+  d->fused_ua = d->bf16_il = d->bf16_wide_fa = true;
+  d->any = {};
+  d->wide_bn = bn;
+  d->krun = 0;
+  d->kpad = p->gk;
+  d->ws_u_al = 0;                                  // U is never aligned
+  d->bytes_partial = 2 * size_t(256) * 256 * bn * 4;
+  const size_t G = static_cast<size_t>(p->g.size);
+  d->bytes_tables = round_up(8 * G * p->M, 256) * 2 + round_up(8 * G * p->gk, 256) + round_up(8 * G * p->gn, 256);
+  d->workspace = round_up(p->ws_v_al, 256) + d->bytes_tables + round_up(d->bytes_partial, 256) +
+                 round_up(p->bytes_charges, 256);
+  if (!tile || !*tile) {
+    // V to planes, the product at 300 TFLOP/s (a third of the bf16 rate; 264 to 300
+    // measured), pieces and launches; where the model says it takes at most 0.8 of the
+    // plan's own time: 8 x (4608 x 4608 x 288) 500 -> 400 us, 8 x (4608 x 4608 x 200)
+    // 504 -> 339, 12 x (6912 x 6912 x 432) 2256 -> 1809; 8 x (8192 x 8192 x 512), whole
+    // rounds of 256 x 256 tiles, stays: 1480 against 1567.
+    const double mine = 45e-6 + 12.0 * static_cast<double>(p->V.elems) / 2.9e12 +
+                        2.0 * static_cast<double>(p->nq) * static_cast<double>((p->M + 255) / 256 * 256) *
+                            static_cast<double>(padded) * static_cast<double>(p->gk) / 300e12;
+    double now = p->any.tile >= 0 ? p->any.time : bf16_planes_time(*p);
+    if (p->any.tile < 0 && p->bf16_wide_fa) now -= 12.0 * static_cast<double>(p->U.elems) / 2.9e12;
+    if (mine > 0.8 * now) return;
+  }
+  p->workspace_steps = p->workspace;
+  p->workspace = std::max(p->workspace, d->workspace);
+  p->direct = std::move(d);
+}
+
 // slices: as a fused plan over the live slices (Plan::direct).
 int plan_contraction(const char* einsum, const symt_group* group, const symt_tensor* u, const symt_tensor* v,
                      const symt_tensor* w, int32_t compute, bool slices, Plan* p, std::string* err) {
@@ -843,6 +899,12 @@ int plan_contraction(const char* einsum, const symt_group* group, const symt_ten
     Plan q;
     if ((rc = make_plan(einsum, group, u, v, w, compute, &q, err))) return rc;
     p->any = q.direct ? q.direct->any : q.any;
+    if (q.direct && q.direct->wide_bn > 0) {
+      p->wide_bn = q.direct->wide_bn;
+      p->bf16_il = true;
+      p->bytes_partial = q.direct->bytes_partial;
+      p->workspace += round_up(p->bytes_partial, 256);
+    }
     p->any.am = 0;
     p->any.b = p->any.cb = false;
     const int64_t ve = compute == SYMT_COMPUTE_F64 ? 2 : 4;
@@ -867,6 +929,7 @@ int plan_contraction(const char* einsum, const symt_group* group, const symt_ten
     p->workspace += round_up(p->bytes_partial, 256);
   }
   p->workspace += round_up(p->bytes_charges, 256);
+  if (!force_steps && !slices && compute == SYMT_COMPUTE_BF16X3 && whole) plan_wide(p, trailing_k);
   // Subgroup modes: in place over the live slices, for the passes over U, V and W
   // that it saves (the Z_8 ladder with 4 sectors on its output modes, 4 x (2304 x
   // 4608 x 288) f64: 570 -> 407 us, of which aligning took 148; Z_2 with

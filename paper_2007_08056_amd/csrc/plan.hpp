@@ -163,6 +163,7 @@ struct FusedTables {
   // (row-streaming product with its rows along N)
   int64_t v_col_run = 1, w_col_run = 1;
   int32_t c_cols = 0;
+  int32_t wide_bn = 0;              // > 0 (split-bf16): 256 x wide_bn tiles under stream-K
   // in-place product for any layout (gemm_any.hpp): tile >= 0 runs it
   int32_t any_tile = -1;
   int32_t any_am = 0;               // A: 0 rows along K, 1 K-major, 2 K-major complex pairs
@@ -224,6 +225,9 @@ struct Plan {
   // the 256 x 256 wide tile, split when its fragments are read (where U is
   // 16-byte aligned; else U is aligned first as for fused_ua)
   bool bf16_wide_fa = false;
+  // ... or 256 x wide_bn tiles under stream-K (split-bf16; a direct plan with U in
+  // place, and the three steps of the same contraction)
+  int32_t wide_bn = 0;
   // fused with A loaded K-major (U's contracted modes are not its last ones): row k
   // of a K-step at ca(Q, k), M chunks at ra(Q, m); a_chunks: U's other modes come
   // in runs of whole 16-byte chunks (vector loads along M)
@@ -251,11 +255,14 @@ struct Plan {
     bool cb = false, ch16 = false, sk = false, b = false;
     int64_t ldb = 0;                // V's row stride (reals) with b
     size_t partial_bytes = 0;
+    double time = 0;                // the model's, in seconds
   } any;
-  // Subgroup modes (fewer live slices than |G|): the same contraction as a fused plan
-  // over its live slices, whose offset tables hold a slice each (slices).  Absent
-  // where a live slice's delta has stored sectors without a solution.  The three
-  // steps' plan keeps describing the contraction (info.fused = 0).
+  // The plan that runs in this one's place, which keeps describing the contraction
+  // (info):
+  //  * subgroup modes (fewer live slices than |G|): a fused plan over the live slices,
+  //    whose offset tables hold a slice each (slices); absent where a live slice's
+  //    delta has stored sectors without a solution;
+  //  * split-bf16 on 256 x wide_bn tiles under stream-K, where U is 16-byte aligned.
   std::shared_ptr<const Plan> direct;
   bool slices = false;
   bool clear_w = false;             // slices: blocks of W that no slice reaches

@@ -369,6 +369,7 @@ int do_fused(symt_ctx* ctx, const Plan& p, char* base, hipStream_t s, const int3
   f.a_bytes = static_cast<int32_t>(p.fused_ua && !wide_fa ? (p.compute == SYMT_COMPUTE_F64 ? 8 : 4)
                                                             : elem_bytes(p.U.dtype));
   f.krun = p.krun;
+  f.wide_bn = p.wide_bn;
   f.at = p.a_trans ? 1 : 0;
   f.c_bytes = static_cast<int32_t>(elem_bytes(p.W.dtype));
   // W written in place with its rows contiguous (and not its columns): the
@@ -634,7 +635,7 @@ int contract_planned(symt_ctx* ctx, const Plan& p, void* workspace, size_t works
     for (int op = 0; op < 3; ++op)
       if (!p.chg[op].empty()) chg[op] = dev + off[op];
   }
-  if (p.direct) {
+  if (p.direct && (p.direct->slices || aligned16(p.U.data))) {
     Plan d = *p.direct;
     d.U.data = p.U.data;
     d.V.data = p.V.data;
@@ -656,8 +657,9 @@ int contract_planned(symt_ctx* ctx, const Plan& p, void* workspace, size_t works
   // (none live: no block of W is reached, and the unalign step clears W)
   symt::FusedTables f{};
   if (any) set_any(p, p.any.ch16, &f);
+  f.wide_bn = p.wide_bn;
   if (p.nq > 0 && (rc = do_gemm(ctx, p.compute, p.nq, p.M, any ? p.gk : p.kpad, p.gn, ual, val, wal, s,
-                                any ? &f : nullptr,
+                                any || p.wide_bn ? &f : nullptr,
                                 p.bytes_partial ? part : nullptr, p.bytes_partial, 0, 0, p.bf16_il)))
     return rc;
   if ((rc = do_unalign(ctx, p, wal, s, true, chg[2]))) return rc;
