@@ -25,7 +25,8 @@
 // (its align passes alone took 392); 9 x (500 x 500 x 500) f64 68.7 -> 62.9 us,
 // f32 44.8 -> 35.9 us; the Z_8 ladder in f32 (8 x (4608 x 4608 x 288)) 915 -> 818 us
 // (96 x 96 with three workgroups per CU against a 64 x 96 register tile); the
-// complex Z_8 ladder with blocks of 16 and 6, 1551 -> 1361 us.  4-byte loads run
+// complex ladder over Z_2 x Z_4 with blocks of 18 and 5 in f64 1985 -> 1722 us, over Z_8 with
+// 24 and 6 in f32 3457 -> 3125.  4-byte loads run
 // at about two thirds of 16-byte ones' rate (3 x (743 x 1113 x 1111) f64: 34.5
 // TFLOP/s), so odd real shapes mostly stay on the register tiles.
 //

@@ -390,7 +390,10 @@ bool plan_any(Plan* p, int want, bool trailing_k, int64_t run) {
     if (p->fused_ua) other += 2.0 * elem * pe * static_cast<double>(p->U.elems) / rate + 8e-6;
     if (!p->fused_b)
       other += 2.0 * elem * pe * pe * static_cast<double>(p->V.elems) / rate + (p->cplx ? 16e-6 : 8e-6);
-    double mine = c.time;
+    // (complex V in place on 96 x 96 in f64 reaches 0.80 of the rate, not 0.85, and V's
+    // passes are cheaper than U's: 8 x (4608 x 9216 x 576) took 6222 us, 5866 on V_al,
+    // 6 x (2400 x 4800 x 768) 1842 and 1745)
+    double mine = c.time * (p->cplx && y.cb && elem == 8 && c.tile == 0 ? 1.09 : 1.0);
     if (!y.b) mine += 2.0 * elem * pe * pe * static_cast<double>(p->V.elems) / rate + (p->cplx ? 16e-6 : 8e-6);
     // (a binary32 product that splits K keeps its shorter sums unless much is gained)
     if (mine > (g.splits > 1 && elem == 4 ? 0.8 : 0.95) * other) return false;
