@@ -390,13 +390,14 @@ bool plan_any(Plan* p, int want, bool trailing_k, int64_t run) {
     if (p->fused_ua) other += 2.0 * elem * pe * static_cast<double>(p->U.elems) / rate + 8e-6;
     if (!p->fused_b)
       other += 2.0 * elem * pe * pe * static_cast<double>(p->V.elems) / rate + (p->cplx ? 16e-6 : 8e-6);
-    // (complex V in place on 96 x 96 in f64 reaches 0.80 of the rate, not 0.85, and V's
-    // passes are cheaper than U's: 8 x (4608 x 9216 x 576) took 6222 us, 5866 on V_al,
-    // 6 x (2400 x 4800 x 768) 1842 and 1745)
-    double mine = c.time * (p->cplx && y.cb && elem == 8 && c.tile == 0 ? 1.09 : 1.0);
+    double mine = c.time;
     if (!y.b) mine += 2.0 * elem * pe * pe * static_cast<double>(p->V.elems) / rate + (p->cplx ? 16e-6 : 8e-6);
-    // (a binary32 product that splits K keeps its shorter sums unless much is gained)
-    if (mine > (g.splits > 1 && elem == 4 ? 0.8 : 0.95) * other) return false;
+    // (a binary32 product that splits K keeps its shorter sums unless much is gained; a
+    // complex f64 one whose U is read along K saves V's passes at most and multiplies at
+    // 0.80 of the rate: 8 x (4608 x 9216 x 576) took 6222 us, 5866 on V_al, at a ratio of
+    // 0.94; where U had to be aligned too it is 0.75 and less)
+    const double keep = g.splits > 1 && elem == 4 ? 0.8 : p->cplx && elem == 8 && y.am == 0 ? 0.85 : 0.95;
+    if (mine > keep * other) return false;
   }
   y.tile = c.tile;
   y.sk = c.sk;
