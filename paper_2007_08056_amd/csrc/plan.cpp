@@ -375,9 +375,12 @@ bool plan_any(Plan* p, int want, bool trailing_k, int64_t run) {
   if (bf && !forced) {
     // against the product on hi/lo planes
     const double valign = y.b ? 0 : 8.0 * static_cast<double>(p->V.elems) / 3.5e12 + 8e-6;
-    // (0.7: the model is least sure where planes run on global-to-LDS tiles, and for
-    // K-major A with 4-byte loads: 5 x (2300 x 1540 x 585) took 256 us, 230 on planes)
-    const bool unsure = (p->kpad % 32 == 0 && !bf16x3_register_tile(p->M, p->gn, p->kpad)) || (y.am == 1 && !y.ch16);
+    // (0.7: the model is least sure where planes run on global-to-LDS tiles, for K-major A
+    // with 4-byte loads -- 5 x (2300 x 1540 x 585) took 256 us, 230 on planes -- and for
+    // outputs much larger than the operands, whose stores bound both: 4 x (6192 x 40 x
+    // 8640) 507 and 456)
+    const bool unsure = (p->kpad % 32 == 0 && !bf16x3_register_tile(p->M, p->gn, p->kpad)) ||
+                        (y.am == 1 && !y.ch16) || (p->gk <= 64 && p->M > 64 && p->gn > 64);
     const double keep = unsure ? 0.7 : 0.85;
     if (!a_ok || c.time + valign > keep * bf16_planes_time(*p)) return false;
   } else if (!forced) {
