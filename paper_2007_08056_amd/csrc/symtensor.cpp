@@ -59,9 +59,16 @@ struct TableCache {
   }
 };
 
+// A plan's tables, and those of the plan that runs in its place (Plan::direct): which of
+// the two a call runs can depend on its data's alignment, and their tables can have the
+// same size with other contents (offsets into U_al and into U).
+struct PlanTables {
+  TableCache own, direct;
+};
+
 struct CachedPlan {
   Plan plan;
-  std::shared_ptr<TableCache> tables;
+  std::shared_ptr<PlanTables> tables;
 };
 
 struct symt_ctx {
@@ -82,7 +89,7 @@ struct symt_ctx {
 struct symt_prepared {
   symt_ctx* ctx;
   Plan plan;
-  std::shared_ptr<TableCache> tables;
+  std::shared_ptr<PlanTables> tables;
 };
 
 namespace {
@@ -467,10 +474,10 @@ std::string plan_key(const char* einsum, const symt_group* group, const symt_ten
   return k;
 }
 
-// `tables` (optional): the cached plan's device table slot.
+// `tables` (optional): the cached plan's device table slots.
 int plan_for(symt_ctx* ctx, const char* einsum, const symt_group* group, const symt_tensor* u,
              const symt_tensor* v, const symt_tensor* w, int32_t compute, Plan* p,
-             std::shared_ptr<TableCache>* tables = nullptr) {
+             std::shared_ptr<PlanTables>* tables = nullptr) {
   std::string key;
   if (ctx) {
     key = plan_key(einsum, group, u, v, w, compute);
@@ -497,7 +504,7 @@ int plan_for(symt_ctx* ctx, const char* einsum, const symt_group* group, const s
       // freeing device memory waits for the device)
       ctx->plans.clear();
     }
-    auto tc = std::make_shared<TableCache>();
+    auto tc = std::make_shared<PlanTables>();
     ctx->plans.emplace(std::move(key), CachedPlan{*p, tc});
     if (tables) *tables = tc;
   }
@@ -601,7 +608,7 @@ namespace {
 // Validation and launches of one planned contraction (symtensor_contract and
 // symtensor_contract_static): every check runs before the first launch.
 int contract_planned(symt_ctx* ctx, const Plan& p, void* workspace, size_t workspace_bytes, void* stream,
-                     TableCache* tables = nullptr) {
+                     PlanTables* tables = nullptr) {
   int rc;
   if ((rc = check_data(ctx, p.U, "u")) || (rc = check_data(ctx, p.V, "v")) ||
       (rc = check_data(ctx, p.W, "w")))
@@ -640,9 +647,9 @@ int contract_planned(symt_ctx* ctx, const Plan& p, void* workspace, size_t works
     d.U.data = p.U.data;
     d.V.data = p.V.data;
     d.W.data = p.W.data;
-    return do_fused(ctx, d, base, s, chg, tables);
+    return do_fused(ctx, d, base, s, chg, tables ? &tables->direct : nullptr);
   }
-  if (p.fused || p.fused_ua || p.any_direct) return do_fused(ctx, p, base, s, chg, tables);
+  if (p.fused || p.fused_ua || p.any_direct) return do_fused(ctx, p, base, s, chg, tables ? &tables->own : nullptr);
   void* ual = base;
   void* val = base + symt::round_up(p.ws_u_al, 256);
   void* wal = base + symt::round_up(p.ws_u_al, 256) + symt::round_up(p.ws_v_al, 256);
@@ -675,7 +682,7 @@ int symtensor_contract(symt_ctx* ctx, const char* einsum, const symt_group* grou
   if (!ctx) return ctx_fail(nullptr, SYMT_EINVAL, "context is NULL");
   if (!w) return ctx_fail(ctx, SYMT_EINVAL, "output descriptor is NULL");
   Plan p;
-  std::shared_ptr<TableCache> tables;
+  std::shared_ptr<PlanTables> tables;
   int rc = plan_for(ctx, einsum, group, u, v, w, compute, &p, &tables);
   if (rc) return rc;
   return contract_planned(ctx, p, workspace, workspace_bytes, stream, tables.get());
