@@ -274,6 +274,9 @@ class _Einsum:
 
     def __init__(self, subscripts, u, v, compute):
         info = plan(subscripts, u, v, compute)
+        # (data may have been set since the tensors were made, and a descriptor takes block sizes alone)
+        for x in (u, v):
+            SymTensor(x.data, x.signs, x.charge, x.group, x.mode_charges, x.sectors)
         tu, tv, tw = _swap(subscripts)
         dims = [u.dims[tu.index(m)] if m in tu else v.dims[tv.index(m)] for m in tw]
         G = group_size(u.group)
