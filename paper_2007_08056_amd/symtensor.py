@@ -290,7 +290,8 @@ class _Einsum:
         # the output as a descriptor: a tensor of its shape that holds nothing
         w = _wrap(torch.empty(self.shape, dtype=u.data.dtype, device="meta"), *self.meta_w)
         self.forward = _planned(subscripts, u, v, w, _code(compute, False))
-        self.grad_u = self.grad_v = None
+        # the gradient contraction of each operand and the fields of the tensors it was planned for
+        self.grads = [(None, None), (None, None)]
 
     def contract(self, ud, vd):
         _check_dense(ud)
@@ -303,16 +304,19 @@ class _Einsum:
         """out <- the gradient contraction of operand 0 (u) or 1 (v)."""
         for t in (gw, other, out):
             _check_dense(t)
-        call = self.grad_v if operand else self.grad_u
-        if call is None:
+        # (saved-tensor hooks may hand back another storage type than the forward pass had)
+        fields = (gw.shape, gw.dtype, other.shape, other.dtype, out.shape, out.dtype)
+        planned, call = self.grads[operand]
+        if planned != fields:
             tu, tv, tw = _swap(self.subscripts)
-            dw, x = _wrap(gw, *self.meta_w), _wrap(out, *(self.meta_v if operand else self.meta_u))
-            y = _wrap(other, *(self.meta_u if operand else self.meta_v))
+            dw, x = SymTensor(gw, *self.meta_w), SymTensor(out, *(self.meta_v if operand else self.meta_u))
+            y = SymTensor(other, *(self.meta_u if operand else self.meta_v))
             code = _code(self.compute, False)
             if operand:
-                call = self.grad_v = _planned(f"{tu},{tw}->{tv}", y, dw, x, code)
+                call = _planned(f"{tu},{tw}->{tv}", y, dw, x, code)
             else:
-                call = self.grad_u = _planned(f"{tw},{tv}->{tu}", dw, y, x, code)
+                call = _planned(f"{tw},{tv}->{tu}", dw, y, x, code)
+            self.grads[operand] = (fields, call)
         if operand:
             call.run(other, gw, out)
         else:
