@@ -325,14 +325,15 @@ bool v_in_place_layout(const Plan& p, int64_t* ldb, bool* chunks) {
 namespace {
 // The in-place product for any layout (gemm_any.hpp): whether it takes this
 // plan, and its loader and tile.  Binary64 and binary32 plans whose operands are
-// all stored in the compute type and whose W is written in place anyway;
+// all stored in the compute type (without a given W: one of that type) and whose W is
+// written in place anyway;
 // split-bf16 plans of real binary32 operands (W of either real type).
 bool plan_any(Plan* p, int want, bool trailing_k, int64_t run) {
   const bool bf = p->compute == SYMT_COMPUTE_BF16X3;
   if (p->U.dtype != want || p->V.dtype != want) return false;
   if (bf ? p->cplx || (!p->slices && (p->subgroups || p->nq != p->g.size)) || p->M <= 0 || p->N <= 0 || p->Kd <= 0 || p->U.elems <= 0 ||
                p->v < 1 || p->s < 1 || p->t < 1
-         : !(p->fused || p->fused_ua) || p->W.dtype != want)
+         : !(p->fused || p->fused_ua) || (p->has_w && p->W.dtype != want))
     return false;
   const int64_t nb = p->slices ? p->nq : p->g.size;
   const int elem = p->compute == SYMT_COMPUTE_F64 ? 8 : 4;
