@@ -5,8 +5,8 @@
 //
 // Each workgroup owns a BM x BN output tile with WM x WN waves; a wave owns a
 // (BM/WM) x (BN/WN) block of 16 x 16 MFMA tiles (v_mfma_f32_16x16x32_bf16) and
-// keeps ONE binary32 accumulator per output element, into which it adds
-// Ahi*Bhi, Ahi*Blo and Alo*Bhi.  One accumulator (rather than one for hi*hi and
+// keeps ONE binary32 accumulator per output element (two under stream-K: TWO below), into
+// which it adds Ahi*Bhi, Ahi*Blo and Alo*Bhi.  One accumulator (rather than one for hi*hi and
 // one for the cross terms) halves the accumulator registers, so a wave can hold
 // a 128 x 64 block in half a SIMD's registers: the 256 x 256 tile runs eight
 // waves, two per SIMD, so that one wave's MFMAs cover the other's wait at the
@@ -52,21 +52,18 @@ namespace symt {
 
 namespace {
 
-// STEP: a K-step's three products are summed apart and added to the accumulator once,
-// so that it rounds as often as the hi-hi accumulator of the two-accumulator tiles: on
-// the ladders' products 4.436e-6 rms against 4.453e-6 (two accumulators) and 4.461e-6
-// (one, three additions a step), for 9% of the time (366 -> 400 us on 8 x (4608 x 4608
-// x 288)).
+// TWO: two binary32 accumulators per output, the Ahi*Bhi sum and the cross terms' sum,
+// joined in binary64 when the tile is done, as the 128 x 128 tiles hold them.
 // SK: stream-K (sk_index.hpp): persistent workgroups share the K-steps of all
-// tiles evenly, the accumulators of cut tiles go to `part` for k_sk_fixup.
+// tiles evenly, the binary64 sums of cut tiles go to `part` for k_sk_fixup (TWO only).
 template <int BM, int BN, int WM, int WN, int S, bool FC, typename TC, bool IL, bool FA, bool SK = false,
-          bool STEP = false>
+          bool TWO = false>
 __global__ __launch_bounds__(64 * WM * WN, 1) void k_bf16x3_wide(
     const uint16_t* __restrict__ Ahi, const uint16_t* __restrict__ Alo, const uint16_t* __restrict__ Bhi,
     const uint16_t* __restrict__ Blo, TC* __restrict__ C, int M, int N, int K, int tiles_m, int tiles_n,
     int64_t ntiles, const int64_t* __restrict__ rc, const int64_t* __restrict__ cc, int group_m,
     const float* __restrict__ U, const int64_t* __restrict__ ra, const int64_t* __restrict__ ca,
-    float* __restrict__ part, int ts) {
+    double* __restrict__ part, int ts) {
   constexpr int NT = 64 * WM * WN;
   constexpr int BK = 32;
   constexpr int TM = BM / WM / 16;
@@ -81,6 +78,7 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void k_bf16x3_wide(
   static_assert(S >= 2 && S * STAGE <= 160 * 1024, "LDS ring");
   static_assert(FC || std::is_same<TC, double>::value, "aligned W is binary64");
   static_assert(!FA || (IL && S == 2), "A in place: interleaved B planes and two stages");
+  static_assert(!SK || TWO, "pieces are binary64 sums of two accumulators");
   __shared__ __attribute__((aligned(1024))) char smem[S * STAGE];
 
   const int tid = threadIdx.x;
@@ -179,11 +177,14 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void k_bf16x3_wide(
           lds_dma16(b_src[i] + k0, base + 2 * PA + (i * NT + wave * 64) * 16);
     };
 
-    f4 acc[TM][TN];
+    f4 acc[TM][TN], cross[TWO ? TM : 1][TWO ? TN : 1];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int j = 0; j < TN; ++j) acc[i][j] = f4{};
+      for (int j = 0; j < TN; ++j) {
+        acc[i][j] = f4{};
+        if constexpr (TWO) cross[i][j] = f4{};
+      }
 
     const int kc = lane >> 4;                       // operand chunk: k = 8 * kc .. 8 * kc + 7
     if constexpr (FA) {
@@ -236,17 +237,16 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void k_bf16x3_wide(
         const int off_lo = IL ? 2 * PA + r * 128 + (((4 + kc) ^ (r & 7)) << 4) : PB + off;
         const bf8 bh = *reinterpret_cast<const bf8*>(base + off);
         const bf8 bl = *reinterpret_cast<const bf8*>(base + off_lo);
-        if constexpr (STEP) {
-          // the K-step's sum apart from the accumulator: one rounding at its size
-          f4 t[TM];
+        if constexpr (TWO) {
+          // (the two updates of a cross accumulator are TM products apart)
 #pragma unroll
-          for (int i = 0; i < TM; ++i) t[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al[i], bh, f4{}, 0, 0, 0);
+          for (int i = 0; i < TM; ++i) {
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[i], bh, acc[i][j], 0, 0, 0);
+            cross[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[i], bl, cross[i][j], 0, 0, 0);
+          }
 #pragma unroll
-          for (int i = 0; i < TM; ++i) t[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[i], bl, t[i], 0, 0, 0);
-#pragma unroll
-          for (int i = 0; i < TM; ++i) t[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[i], bh, t[i], 0, 0, 0);
-#pragma unroll
-          for (int i = 0; i < TM; ++i) acc[i][j] += t[i];
+          for (int i = 0; i < TM; ++i)
+            cross[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al[i], bh, cross[i][j], 0, 0, 0);
         } else {
           // consecutive MFMAs update different accumulators (no dependent back-to-back pairs)
 #pragma unroll
@@ -259,9 +259,21 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void k_bf16x3_wide(
       }
     }
 
+    auto sum = [&](int i, int j, int r) {
+      if constexpr (TWO) return static_cast<double>(acc[i][j][r]) + static_cast<double>(cross[i][j][r]);
+      else return acc[i][j][r];
+    };
     if constexpr (SK) {
       if (nk < steps) {
-        store_piece<TM, TN>(part + sk_piece(sl.team, sl.member, ts, grp, first) * (BM * BN), acc);
+        // (accumulator order: store_piece)
+        double* pw = part + sk_piece(sl.team, sl.member, ts, grp, first) * (BM * BN) +
+                     (tid >> 6) * (TM * TN * 4 * 64) + lane;
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) pw[((i * TN + j) * 4 + r) * 64] = sum(i, j, r);
         it += nk;
         continue;
       }
@@ -279,7 +291,7 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void k_bf16x3_wide(
           const int row = m0 + wm0 + i * 16 + 4 * (lane >> 4) + r;
           if (row < M && col < N) {
             const int64_t crow = FC ? rc[q * M + row] : static_cast<int64_t>(row) * N;
-            Cq[crow + ccol] = static_cast<TC>(acc[i][j][r]);
+            Cq[crow + ccol] = static_cast<TC>(sum(i, j, r));
           }
         }
     }
@@ -319,22 +331,30 @@ hipError_t launch_wide(int64_t batch, int M, int N, int K, const void* A, const 
   return hipGetLastError();
 }
 
-// 256 x BN tiles under stream-K, where N fills them and whole rounds of one-workgroup
-// tiles would not fill the device: 64 x BN / 2 blocks per wave read each A fragment for
-// BN / 32 column tiles, which halves the LDS and L2 traffic per product of the 128 x 128
-// register tile (8 x (4608 x 4608 x 288): 470 -> 330 us).  C: W through its tables, or the aligned W.
+// 256 x (2 BN) tiles under stream-K, each as two workgroups of BN columns (a team of
+// stream-K walks its K-steps side by side, so both read A's lines from L2 once), where N
+// fills them and whole rounds of one-workgroup tiles would not fill the device.  C: W
+// through its tables, or the aligned W.
+// Bound by LDS: a 32 x 144 wave block reads 22 fragments for 54 MFMAs, 0.8 of the matrix
+// pipes' own time.  What it saves on the 128 x 128 register tile is that tile's staging
+// through registers, its padded columns (288 run as 384) and its last round.  Eight waves,
+// whose two accumulators (hi hi and the cross terms, joined in binary64, as that tile
+// holds them) take 144 registers each, two waves per SIMD: four waves of 64 x 144 read
+// 26 fragments for 108 MFMAs but spill 45 registers, 518 us against 412 on
+// 8 x (4608 x 4608 x 288), which is 553 on the register tile; 8 x (4608 x 4608 x 200)
+// 556 -> 352, 4 x (3136 x 3136 x 288) 227 -> 142 us.
 template <int BN, bool FA, bool FC, typename TC>
 hipError_t launch_wide_sk(int64_t batch, int M, int N, int K, const void* A, const void* B, TC* C, hipStream_t s,
-                          const int64_t* rc, const int64_t* cc, const int64_t* ra, const int64_t* ca, float* part,
+                          const int64_t* rc, const int64_t* cc, const int64_t* ra, const int64_t* ca, double* part,
                           size_t part_bytes) {
-  constexpr int BM = 256, WM = 4, WN = 2;
+  constexpr int BM = 256, WM = 8, WN = 1;
   const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
   const int64_t ntiles = batch * tiles_m * tiles_n;
   const uint16_t* a = FA ? nullptr : static_cast<const uint16_t*>(A);
   const float* u = FA ? static_cast<const float*>(A) : nullptr;
   const uint16_t* b = static_cast<const uint16_t*>(B);
   const SkLaunch sl = part ? sk_launch(ntiles, tiles_n, K / 32, device_cus(),
-                                       static_cast<int64_t>(part_bytes / sizeof(float)),
+                                       static_cast<int64_t>(part_bytes / sizeof(double)),
                                        static_cast<int64_t>(BM) * BN, kSkMinIters)
                            : SkLaunch{};
   const dim3 block(64 * WM * WN);
@@ -348,13 +368,13 @@ hipError_t launch_wide_sk(int64_t batch, int M, int N, int K, const void* A, con
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const dim3 fgrid = sk_fixup_grid(ntiles, sl.ts, K / 32, sl.P / sl.ts, static_cast<int64_t>(BM) * BN, 64 * WM * WN);
-  hipLaunchKernelGGL((k_sk_fixup<float, BM, BN, WM, WN, FC, float, TC>), fgrid, block, 0, s, part, C, M, N, K / 32,
+  hipLaunchKernelGGL((k_sk_fixup<float, BM, BN, WM, WN, FC, double, TC>), fgrid, block, 0, s, part, C, M, N, K / 32,
                      tiles_m, tiles_n, ntiles, sl.ts, sl.P / sl.ts, rc, cc);
   return hipGetLastError();
 }
 template <int BN>
 hipError_t launch_wide_bn(int64_t batch, int M, int N, int K, const void* A, const void* B, void* C, hipStream_t s,
-                          const FusedTables* f, float* part, size_t part_bytes) {
+                          const FusedTables* f, double* part, size_t part_bytes) {
   const int64_t *rc = f->rc, *cc = f->cc, *ra = f->ra, *ca = f->ca;
   if (!rc) return launch_wide_sk<BN, false, false>(batch, M, N, K, A, B, static_cast<double*>(C), s, rc, cc, ra, ca, part, part_bytes);
   if (!ra) return hipErrorInvalidValue;   // (W in place: U in place too)
@@ -365,17 +385,17 @@ hipError_t launch_wide_bn(int64_t batch, int M, int N, int K, const void* A, con
 
 }  // namespace
 
-// The 256 x f->wide_bn tiles (192, 224, 256 or 288 columns) on interleaved planes of
+// The 256 x f->wide_bn tiles (192, 224, 256 or 288 columns in two halves) on interleaved planes of
 // B: A read in place (f->ra) with W through its tables, or A on planes and the aligned W.
 hipError_t launch_bf16x3_wide_sk(int64_t batch, int M, int N, int K, const void* A, const void* B, void* C,
                                  hipStream_t s, const FusedTables* f, void* part, size_t part_bytes) {
   if (K % 32 != 0) return hipErrorInvalidValue;
-  float* pt = static_cast<float*>(part);
+  double* pt = static_cast<double*>(part);
   switch (f->wide_bn) {
-    case 192: return launch_wide_bn<192>(batch, M, N, K, A, B, C, s, f, pt, part_bytes);
-    case 224: return launch_wide_bn<224>(batch, M, N, K, A, B, C, s, f, pt, part_bytes);
-    case 256: return launch_wide_bn<256>(batch, M, N, K, A, B, C, s, f, pt, part_bytes);
-    case 288: return launch_wide_bn<288>(batch, M, N, K, A, B, C, s, f, pt, part_bytes);
+    case 192: return launch_wide_bn<96>(batch, M, N, K, A, B, C, s, f, pt, part_bytes);
+    case 224: return launch_wide_bn<112>(batch, M, N, K, A, B, C, s, f, pt, part_bytes);
+    case 256: return launch_wide_bn<128>(batch, M, N, K, A, B, C, s, f, pt, part_bytes);
+    case 288: return launch_wide_bn<144>(batch, M, N, K, A, B, C, s, f, pt, part_bytes);
   }
   return hipErrorInvalidValue;
 }

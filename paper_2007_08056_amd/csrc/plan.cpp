@@ -413,7 +413,8 @@ bool plan_any(Plan* p, int want, bool trailing_k, int64_t run) {
 }  // namespace
 
 namespace {
-// Split-bf16 on 256 x wide_bn tiles under stream-K (Plan::direct): a binary32 U whose
+// Split-bf16 on 256 x wide_bn tiles under stream-K (Plan::direct; two workgroups of
+// wide_bn / 2 columns each): a binary32 U whose
 // contracted modes are its last ones in runs of 4, K in whole 32-deep steps.
 void plan_wide(Plan* p, bool trailing_k) {
   const char* fa_env = std::getenv("SYMT_BF16_FA");
@@ -439,17 +440,17 @@ void plan_wide(Plan* p, bool trailing_k) {
   d->krun = 0;
   d->kpad = p->gk;
   d->ws_u_al = 0;                                  // U is never aligned
-  d->bytes_partial = 2 * size_t(256) * 256 * bn * 4;
+  d->bytes_partial = 2 * size_t(256) * 256 * (bn / 2) * 8;   // (binary64 pieces of half tiles)
   const size_t G = static_cast<size_t>(p->g.size);
   d->bytes_tables = round_up(8 * G * p->M, 256) * 2 + round_up(8 * G * p->gk, 256) + round_up(8 * G * p->gn, 256);
   d->workspace = round_up(p->ws_v_al, 256) + d->bytes_tables + round_up(d->bytes_partial, 256) +
                  round_up(p->bytes_charges, 256);
   if (!tile || !*tile) {
-    // V to planes, the product at 300 TFLOP/s (a third of the bf16 rate; 264 to 300
+    // V to planes, the product at 300 TFLOP/s (a third of the bf16 rate; 253 to 308
     // measured), pieces and launches; where the model says it takes at most 0.8 of the
-    // plan's own time: 8 x (4608 x 4608 x 288) 500 -> 400 us, 8 x (4608 x 4608 x 200)
-    // 504 -> 339, 12 x (6912 x 6912 x 432) 2256 -> 1809; 8 x (8192 x 8192 x 512), whole
-    // rounds of 256 x 256 tiles, stays: 1480 against 1567.
+    // plan's own time: 8 x (4608 x 4608 x 288) 553 -> 407 us, 8 x (4608 x 4608 x 200)
+    // 556 -> 348, 6 x (3456 x 3456 x 216) 232 -> 181; 8 x (8192 x 8192 x 512), whole
+    // rounds of 256 x 256 tiles, stays: 1555 against 1753.
     const double mine = 45e-6 + 12.0 * static_cast<double>(p->V.elems) / 2.9e12 +
                         2.0 * static_cast<double>(p->nq) * static_cast<double>((p->M + 255) / 256 * 256) *
                             static_cast<double>(padded) * static_cast<double>(p->gk) / 300e12;
