@@ -2,6 +2,7 @@
 // aligned shapes and the transform descriptors (Alg. 2: its coefficient
 // and delta steps, and the index maps of its aligned-operand and final steps).
 #include "plan.hpp"
+#include "sk_index.hpp"
 
 #include <algorithm>
 #include <cstdio>
@@ -413,23 +414,52 @@ bool plan_any(Plan* p, int want, bool trailing_k, int64_t run) {
 }  // namespace
 
 namespace {
+// Time of a split-bf16 product on 256 x bn tiles under stream-K, with V's pass to planes: a
+// K-step costs the same whatever it multiplies (its loads, splits and LDS reads), a cut
+// tile's pieces are written and read in binary64, and a short K leaves the stores of W in
+// sight.  A fit to 380 timings, 91 products of 0.2 to 930 GFLOP on each width: 6% off in the
+// mean.
+double wide_time(const Plan& p, int bn) {
+  const int64_t half = bn / 2, tm = (p.M + 255) / 256, tn = (p.gn + half - 1) / half, nk = p.gk / 32;
+  const int64_t ntiles = p.nq * tm * tn;
+  const SkLaunch sl = sk_launch(ntiles, static_cast<int>(tn), static_cast<int>(nk), 256, int64_t(1) << 60, 256 * half,
+                                kSkMinIters);
+  int64_t steps = (ntiles + 255) / 256 * nk, pieces = 0;   // of the fullest workgroup; of all cut tiles
+  if (sl.P > 0) {
+    const int nteam = sl.P / sl.ts;
+    const int64_t total = ntiles / sl.ts * nk;
+    int64_t cut = -1;
+    for (int t = 1; t < nteam; ++t) {
+      const int64_t at = sk_bound(t, total, nteam);
+      if (at % nk == 0) continue;
+      pieces += at / nk == cut ? sl.ts : 2 * sl.ts;
+      cut = at / nk;
+    }
+    steps = (total + nteam - 1) / nteam;
+  }
+  const double step = bn == 288 ? 1.60e-6 : bn == 256 ? 1.43e-6 : bn == 224 ? 1.345e-6 : 1.25e-6;
+  return 23e-6 + 12.0 * static_cast<double>(p.V.elems) / 7.4e12 + 4.0 * static_cast<double>(p.U.elems) / 11.4e12 +
+         4.0 * static_cast<double>(p.W.elems) / 1.9e12 + static_cast<double>(pieces) * 256 * half * 16 / 10.2e12 +
+         static_cast<double>(steps) * step;
+}
+
 // Split-bf16 on 256 x wide_bn tiles under stream-K (Plan::direct; two workgroups of
-// wide_bn / 2 columns each): a binary32 U whose
-// contracted modes are its last ones in runs of 4, K in whole 32-deep steps.
+// wide_bn / 2 columns each): a binary32 U whose contracted modes are its last ones in runs
+// of 4, K in whole 32-deep steps.
 void plan_wide(Plan* p, bool trailing_k) {
   const char* fa_env = std::getenv("SYMT_BF16_FA");
   if (p->cplx || p->U.dtype != SYMT_F32 || p->V.dtype != SYMT_F32 || !trailing_k || p->nK % 4 != 0 || p->gk % 32 != 0 ||
-      p->M < 256 || p->gn <= 0 || p->v < 1 || p->w_col_run < 16 || (fa_env && std::atoi(fa_env) == 0))
+      p->M < 256 || p->gn <= 0 || p->gk <= 0 || p->v < 1 || p->w_col_run < 16 || (fa_env && std::atoi(fa_env) == 0))
     return;
   const char* tile = std::getenv("SYMT_GEMM_TILE");
   const char* sk_env = std::getenv("SYMT_GEMM_SK");
   if (sk_env && std::atoi(sk_env) == 0) return;
   int bn = 0;
-  int64_t padded = 0;
+  double time = 0;
   for (int c : {288, 256, 224, 192}) {
     if (tile && *tile && std::string("bw256x") + std::to_string(c) + "sk" != tile) continue;
-    const int64_t n = (p->gn + c - 1) / c * c;
-    if (bn == 0 || n < padded) bn = c, padded = n;
+    const double t = wide_time(*p, c);
+    if (bn == 0 || t < time) bn = c, time = t;
   }
   if (bn == 0) return;
   auto d = std::make_shared<Plan>(*p);
@@ -446,17 +476,16 @@ void plan_wide(Plan* p, bool trailing_k) {
   d->workspace = round_up(p->ws_v_al, 256) + d->bytes_tables + round_up(d->bytes_partial, 256) +
                  round_up(p->bytes_charges, 256);
   if (!tile || !*tile) {
-    // V to planes, the product at 300 TFLOP/s (a third of the bf16 rate; 253 to 308
-    // measured), pieces and launches; where the model says it takes at most 0.8 of the
-    // plan's own time: 8 x (4608 x 4608 x 288) 553 -> 407 us, 8 x (4608 x 4608 x 200)
-    // 556 -> 348, 6 x (3456 x 3456 x 216) 232 -> 181; 8 x (8192 x 8192 x 512), whole
-    // rounds of 256 x 256 tiles, stays: 1555 against 1753.
-    const double mine = 45e-6 + 12.0 * static_cast<double>(p->V.elems) / 2.9e12 +
-                        2.0 * static_cast<double>(p->nq) * static_cast<double>((p->M + 255) / 256 * 256) *
-                            static_cast<double>(padded) * static_cast<double>(p->gk) / 300e12;
+    // Where the model says it takes at most 0.8 of the plan's own time: of 70 random
+    // products the 14 under it took 0.47 to 0.99 of that plan's measured time (the other
+    // plans' models are off by up to 1.6), the 12 at 0.8 to 0.9 took 0.71 to 1.34.
+    // 8 x (4608 x 4608 x 288) 553 -> 407 us, 12 x (6912 x 6912 x 432) 2284 -> 1779 and
+    // 8 x (4608 x 4608 x 200) 556 -> 348; 8 x (8192 x 8192 x 512), whole rounds of
+    // 256 x 256 tiles, stays (1555 against 1753), and so do short K with many rows
+    // (8 x (11840 x 768 x 224): 184 against 225).
     double now = p->any.tile >= 0 ? p->any.time : bf16_planes_time(*p);
     if (p->any.tile < 0 && p->bf16_wide_fa) now -= 12.0 * static_cast<double>(p->U.elems) / 2.9e12;
-    if (mine > 0.8 * now) return;
+    if (time > 0.8 * now) return;
   }
   p->workspace_steps = p->workspace;
   p->workspace = std::max(p->workspace, d->workspace);
