@@ -1298,7 +1298,8 @@ int launch_sector_gemm(int compute, int64_t batch, int64_t m, int64_t k, int64_t
   const int M = static_cast<int>(m), N = static_cast<int>(n), K = static_cast<int>(k);
   hipError_t e = hipSuccess;
   if (fused && fused->any_tile >= 0) {
-    const AnyLaunch l{fused->any_tile, fused->any_am, fused->any_ch, fused->any_cb != 0, fused->any_sk != 0};
+    const AnyLaunch l{fused->any_tile, fused->any_am, fused->any_ch, fused->any_cb != 0, fused->any_sk != 0,
+                      fused->any_chunk != 0};
     const auto launch = compute == SYMT_COMPUTE_F64   ? launch_gemm_any_f64
                         : compute == SYMT_COMPUTE_F32 ? launch_gemm_any_f32
                                                       : launch_gemm_any_bf16x3;

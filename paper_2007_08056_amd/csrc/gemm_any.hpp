@@ -43,7 +43,9 @@
 // 358 -> 142, 4 x (1156 x 1156 x 36) 118 -> 39, 6 x (16 x 186624 x 18) 5307 -> 203.
 //
 // Values and K order are the other tiles': K-steps of 128 bytes, four indices
-// per MFMA, tiles cut by stream-K summed in K order by k_sk_fixup.
+// per MFMA, tiles cut by stream-K summed in K order by k_sk_fixup.  Where K was cut
+// before, binary32 sums of 128 indices go to a second accumulator (kAnyChunk: 16 to 36
+// additions a chunk, up to 6% of the time on 96 x 96, whose registers it fills).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -70,6 +72,11 @@ __device__ __forceinline__ void lds_dma(const void* g, void* lds) {
   if constexpr (CH == 16) __builtin_amdgcn_global_load_lds((gptr_t)(g), (lptr_t)(lds), 16, 0, 0);
   else __builtin_amdgcn_global_load_lds((gptr_t)(g), (lptr_t)(lds), 4, 0, 0);
 }
+
+// K-steps that a binary32 accumulator sums before it starts over (128 indices), where these
+// tiles replace a product that cuts K: its sums hold at least 128 indices each, and one
+// accumulator over all of K is further off (CK; rms 6.9e-7 against 2.1e-7 at K = 744 complex).
+constexpr int kAnyChunk = 4;
 
 // AM, CB: the tile's layouts (any_index.hpp).  Null tables stand for the aligned
 // row-major forms (the three-step path, so that it sums in the same order).
@@ -116,7 +123,7 @@ constexpr int any_rows_per_load() {
   return (ROW - g + 64 * CH - 1) / ROW + 1;
 }
 
-template <typename T, int BM, int BN, int WM, int WN, int S, int CH, int AM, bool CB, bool BF>
+template <typename T, int BM, int BN, int WM, int WN, int S, int CH, int AM, bool CB, bool BF, bool CK>
 __device__ __forceinline__ void any_tile_accumulate(
     const T* __restrict__ A, const T* __restrict__ B, int M, int N, const AnySteps& st, int64_t q, int m0, int n0,
     int kt0, int kt1, const int64_t* __restrict__ ra, const int64_t* __restrict__ ca,
@@ -218,6 +225,15 @@ __device__ __forceinline__ void any_tile_accumulate(
   };
 
   const int nk = kt1 - kt0;
+  // CK: the sum of every kAnyChunk K-steps is added to `sum` and starts over
+  static_assert(!CK || (std::is_same<T, float>::value && !BF), "binary32 sums");
+  typename D::Acc sum[CK ? TM : 1][CK ? TN : 1];
+  if constexpr (CK) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) sum[i][j] = typename D::Acc{};
+  }
   if (nk > 0) fetch(kt0);
 #pragma unroll
   for (int s = 0; s < S - 1; ++s)
@@ -289,7 +305,23 @@ __device__ __forceinline__ void any_tile_accumulate(
 #pragma unroll
           for (int j = 0; j < TN; ++j) acc.v[i][j] = Mfma<T>::run(a[i], b[j], acc.v[i][j]);
       }
+      if constexpr (CK)
+        if (it % kAnyChunk == kAnyChunk - 1) {
+#pragma unroll
+          for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+              sum[i][j] += acc.v[i][j];
+              acc.v[i][j] = typename D::Acc{};
+            }
+        }
     }
+  }
+  if constexpr (CK) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) acc.v[i][j] += sum[i][j];
   }
 }
 
@@ -344,7 +376,7 @@ __device__ __forceinline__ void store_any_piece(double* __restrict__ piece, cons
 // One workgroup per tile (ts = 0, XCD-aware order), or stream-K (ts > 0:
 // persistent workgroups, pieces of cut tiles to `part` for k_sk_fixup).
 template <typename T, int BM, int BN, int WM, int WN, int S, int CH, int AM, bool CB, bool BF = false,
-          typename TC = T>
+          typename TC = T, bool CK = false>
 __global__ __launch_bounds__(64 * WM * WN, (kAnyWavesPerSimd<BM, BN, CH, BF>)) void k_gemm_any(
     const T* __restrict__ A, const T* __restrict__ B, TC* __restrict__ C, int M, int N, AnySteps st, int tiles_m,
     int tiles_n, int64_t ntiles, const int64_t* __restrict__ ra, const int64_t* __restrict__ ca,
@@ -389,8 +421,8 @@ __global__ __launch_bounds__(64 * WM * WN, (kAnyWavesPerSimd<BM, BN, CH, BF>)) v
         acc.v[i][j] = typename D::Acc{};
         if constexpr (BF) acc.x[i][j] = typename D::Acc{};
       }
-    any_tile_accumulate<T, BM, BN, WM, WN, S, CH, AM, CB, BF>(A, B, M, N, st, q, tm * BM, tn * BN, kt0, kt1, ra, ca,
-                                                              rb, cb, ldb, smem, acc);
+    any_tile_accumulate<T, BM, BN, WM, WN, S, CH, AM, CB, BF, CK>(A, B, M, N, st, q, tm * BM, tn * BN, kt0, kt1, ra,
+                                                                  ca, rb, cb, ldb, smem, acc);
     if (kt0 == 0 && kt1 == st.nk) {
       // W's table entries all requested before the first store
       CTab<TM, TN> ct;
@@ -410,7 +442,7 @@ __global__ __launch_bounds__(64 * WM * WN, (kAnyWavesPerSimd<BM, BN, CH, BF>)) v
 }
 
 template <typename T, int BM, int BN, int WM, int WN, int S, int CH, int AM, bool CB, bool BF = false,
-          typename TC = T>
+          typename TC = T, bool CK = false>
 hipError_t launch_any_kernel(int64_t batch, int M, int N, const AnySteps& st, const void* A, const void* B, void* C,
                              hipStream_t s, const FusedTables* f, void* part, size_t part_bytes, bool sk) {
   const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
@@ -422,7 +454,7 @@ hipError_t launch_any_kernel(int64_t batch, int M, int N, const AnySteps& st, co
   TC* c = static_cast<TC*>(C);
   TP* pt = static_cast<TP*>(part);
   const int rows4 = f->c_rows4 && (reinterpret_cast<uintptr_t>(c) & 15) == 0 ? 1 : 0;
-  auto kern = k_gemm_any<T, BM, BN, WM, WN, S, CH, AM, CB, BF, TC>;
+  auto kern = k_gemm_any<T, BM, BN, WM, WN, S, CH, AM, CB, BF, TC, CK>;
   int P = 0, ts = 0;
   if (sk && part) {
     // resident workgroups per CU of this instantiation, cached
@@ -454,26 +486,29 @@ hipError_t launch_any_kernel(int64_t batch, int M, int N, const AnySteps& st, co
 
 // Tiles in the order of the planner's table (the 96 x 96 one takes 16-byte loads
 // only: with 4-byte loads its sources and accumulators exceed two waves' registers).
-template <typename T, int CH, int AM, bool CB>
-hipError_t launch_any_tile(int tile, int64_t batch, int M, int N, const AnySteps& st, const void* A, const void* B,
-                           void* C, hipStream_t s, const FusedTables* f, void* part, size_t part_bytes, bool sk) {
+template <typename T, int CH, int AM, bool CB, bool CK>
+hipError_t launch_any_tile(const AnyLaunch& l, int64_t batch, int M, int N, const AnySteps& st, const void* A,
+                           const void* B, void* C, hipStream_t s, const FusedTables* f, void* part, size_t part_bytes) {
   if constexpr (CH == 16)
-    if (tile == 0)
-      return launch_any_kernel<T, 96, 96, 2, 2, 2, CH, AM, CB>(batch, M, N, st, A, B, C, s, f, part, part_bytes, sk);
-  if (tile <= 1)
-    return launch_any_kernel<T, 128, 64, 2, 2, 2, CH, AM, CB>(batch, M, N, st, A, B, C, s, f, part, part_bytes, sk);
-  return launch_any_kernel<T, 64, 64, 2, 2, 2, CH, AM, CB>(batch, M, N, st, A, B, C, s, f, part, part_bytes, sk);
+    if (l.tile == 0)
+      return launch_any_kernel<T, 96, 96, 2, 2, 2, CH, AM, CB, false, T, CK>(batch, M, N, st, A, B, C, s, f, part,
+                                                                           part_bytes, l.sk);
+  if (l.tile <= 1)
+    return launch_any_kernel<T, 128, 64, 2, 2, 2, CH, AM, CB, false, T, CK>(batch, M, N, st, A, B, C, s, f, part,
+                                                                          part_bytes, l.sk);
+  return launch_any_kernel<T, 64, 64, 2, 2, 2, CH, AM, CB, false, T, CK>(batch, M, N, st, A, B, C, s, f, part,
+                                                                       part_bytes, l.sk);
 }
 
-template <typename T, int CH>
-hipError_t launch_any_typed(int tile, int am, bool cb, int64_t batch, int M, int N, const AnySteps& st, const void* A,
+template <typename T, int CH, bool CK>
+hipError_t launch_any_typed(const AnyLaunch& l, int64_t batch, int M, int N, const AnySteps& st, const void* A,
                             const void* B, void* C, hipStream_t s, const FusedTables* f, void* part,
-                            size_t part_bytes, bool sk) {
-  if (cb)
-    return am == 0 ? launch_any_tile<T, CH, 0, true>(tile, batch, M, N, st, A, B, C, s, f, part, part_bytes, sk)
-                   : launch_any_tile<T, CH, 2, true>(tile, batch, M, N, st, A, B, C, s, f, part, part_bytes, sk);
-  return am == 0 ? launch_any_tile<T, CH, 0, false>(tile, batch, M, N, st, A, B, C, s, f, part, part_bytes, sk)
-                 : launch_any_tile<T, CH, 1, false>(tile, batch, M, N, st, A, B, C, s, f, part, part_bytes, sk);
+                            size_t part_bytes) {
+  if (l.cb)
+    return l.am == 0 ? launch_any_tile<T, CH, 0, true, CK>(l, batch, M, N, st, A, B, C, s, f, part, part_bytes)
+                     : launch_any_tile<T, CH, 2, true, CK>(l, batch, M, N, st, A, B, C, s, f, part, part_bytes);
+  return l.am == 0 ? launch_any_tile<T, CH, 0, false, CK>(l, batch, M, N, st, A, B, C, s, f, part, part_bytes)
+                   : launch_any_tile<T, CH, 1, false, CK>(l, batch, M, N, st, A, B, C, s, f, part, part_bytes);
 }
 
 }  // namespace

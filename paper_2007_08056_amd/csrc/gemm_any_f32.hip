@@ -6,9 +6,11 @@ namespace symt {
 hipError_t launch_gemm_any_f32(const AnyLaunch& l, int64_t batch, int M, int N, int K, const void* A, const void* B,
                                void* C, hipStream_t s, const FusedTables* f, void* part, size_t part_bytes) {
   const AnySteps st = any_steps(K, f->any_krun, 32);
-  return l.ch == 16
-             ? launch_any_typed<float, 16>(l.tile, l.am, l.cb, batch, M, N, st, A, B, C, s, f, part, part_bytes, l.sk)
-             : launch_any_typed<float, 4>(l.tile, l.am, l.cb, batch, M, N, st, A, B, C, s, f, part, part_bytes, l.sk);
+  if (l.chunk)
+    return l.ch == 16 ? launch_any_typed<float, 16, true>(l, batch, M, N, st, A, B, C, s, f, part, part_bytes)
+                      : launch_any_typed<float, 4, true>(l, batch, M, N, st, A, B, C, s, f, part, part_bytes);
+  return l.ch == 16 ? launch_any_typed<float, 16, false>(l, batch, M, N, st, A, B, C, s, f, part, part_bytes)
+                    : launch_any_typed<float, 4, false>(l, batch, M, N, st, A, B, C, s, f, part, part_bytes);
 }
 
 }  // namespace symt

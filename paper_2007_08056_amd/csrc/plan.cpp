@@ -324,6 +324,26 @@ bool v_in_place_layout(const Plan& p, int64_t* ldb, bool* chunks) {
 }
 
 namespace {
+// Most K indices that one accumulator of a product on bm x bn tiles sums: all of K, or the
+// share of a stream-K workgroup.
+int64_t longest_share(int64_t batch, int64_t M, int64_t N, int64_t K, int64_t nk, int bm, int bn, int wgs) {
+  const int64_t tn = (N + bn - 1) / bn, ntiles = batch * ((M + bm - 1) / bm) * tn;
+  const SkLaunch sl = sk_launch(ntiles, static_cast<int>(tn), static_cast<int>(nk), std::min(kSkSlots, 256 * wgs),
+                                int64_t(1) << 60, static_cast<int64_t>(bm) * bn, kSkMinIters);
+  if (sl.P == 0) return K;
+  const int64_t total = ntiles / sl.ts * nk, nteam = sl.P / sl.ts;
+  return std::min(K, std::min(nk, (total + nteam - 1) / nteam) * ((K + nk - 1) / nk));
+}
+// The same of the product that a plan takes by itself.
+int64_t longest_sum(const GemmChoice& g, int64_t batch, int64_t M, int64_t N, int64_t K, int elem) {
+  const int64_t bk = 128 / elem;
+  if (g.tile == kTallKTile || g.splits > 1) {
+    const int64_t steps = (K + 15) / 16;
+    return std::min(K, (steps + g.splits - 1) / g.splits * 16);
+  }
+  return g.sk ? longest_share(batch, M, N, K, (K + bk - 1) / bk, g.bm, g.bn, g.wgs) : K;
+}
+
 // The in-place product for any layout (gemm_any.hpp): whether it takes this
 // plan, and its loader and tile.  Binary64 and binary32 plans whose operands are
 // all stored in the compute type (without a given W: one of that type) and whose W is
@@ -397,12 +417,22 @@ bool plan_any(Plan* p, int want, bool trailing_k, int64_t run) {
       other += 2.0 * elem * pe * pe * static_cast<double>(p->V.elems) / rate + (p->cplx ? 16e-6 : 8e-6);
     double mine = c.time;
     if (!y.b) mine += 2.0 * elem * pe * pe * static_cast<double>(p->V.elems) / rate + (p->cplx ? 16e-6 : 8e-6);
-    // (a binary32 product that splits K keeps its shorter sums unless much is gained; a
-    // complex f64 one whose U is read along K saves V's passes at most and multiplies at
-    // 0.80 of the rate: 8 x (4608 x 9216 x 576) took 6222 us, 5866 on V_al, at a ratio of
-    // 0.94; where U had to be aligned too it is 0.75 and less)
+    // (0.8 where binary32 splits K: the model is too fast there -- 6 x (1536 x 768 x 64)
+    // takes 56 us on the tile it picks, 27 on 128 x 64 with K split; a complex f64 product
+    // whose U is read along K saves V's passes at most and multiplies at 0.80 of the rate:
+    // 8 x (4608 x 9216 x 576) took 6222 us, 5866 on V_al, at a ratio of 0.94; where U had
+    // to be aligned too it is 0.75 and less)
     const double keep = g.splits > 1 && elem == 4 ? 0.8 : p->cplx && elem == 8 && y.am == 0 ? 0.85 : 0.95;
     if (mine > keep * other) return false;
+  }
+  if (!bf && elem == 4) {
+    // binary32 sums no longer than those of the product it replaces, on aligned data or not
+    const int64_t own = c.sk ? longest_share(nb, p->M, p->gn, p->gk, ksteps, kAnyTiles[c.tile].bm, kAnyTiles[c.tile].bn,
+                                             kAnyTiles[c.tile].wgs)
+                             : p->gk;
+    for (bool aligned : {true, false})
+      y.chunk = y.chunk || own > longest_sum(choose_fp_gemm(nb, p->M, p->gn, p->gk, elem, aligned, p->a_trans && aligned), nb,
+                                             p->M, p->gn, p->gk, elem);
   }
   y.tile = c.tile;
   y.sk = c.sk;
@@ -1118,7 +1148,7 @@ GemmChoice choose_among(int64_t batch, int64_t M, int64_t N, int64_t K, int elem
                2 * 1.5e-6 + 5e-6;
       }
       if (best.tile < 0 || time < best_t) {
-        best.tile = i; best.bm = t.bm; best.bn = t.bn; best.dma = t.dma; best.sk = sk;
+        best.tile = i; best.bm = t.bm; best.bn = t.bn; best.dma = t.dma; best.sk = sk; best.wgs = t.wgs;
         best.splits = 1;
         best.partial_bytes = partial;
         best.time = best_t = time;

@@ -171,12 +171,13 @@ struct FusedTables {
   int32_t any_ch = 4;               // bytes per lane load: 16 (aligned whole chunks) or 4
   int32_t any_krun = 0;             // > 0: K stepped run by run
   int32_t any_sk = 0;               // 1: stream-K
+  int32_t any_chunk = 0;            // 1: binary32 sums of 128 indices (the replaced product cuts K)
 };
 
 // One launch of the in-place product for any layout.
 struct AnyLaunch {
   int tile, am, ch;
-  bool cb, sk;
+  bool cb, sk, chunk;
 };
 
 struct OperandDesc {
@@ -253,6 +254,7 @@ struct Plan {
   struct {
     int32_t tile = -1, am = 0, krun = 0;
     bool cb = false, ch16 = false, sk = false, b = false;
+    bool chunk = false;             // binary32: sums of 128 indices
     int64_t ldb = 0;                // V's row stride (reals) with b
     size_t partial_bytes = 0;
     double time = 0;                // the model's, in seconds
@@ -303,6 +305,7 @@ struct GemmChoice {
   bool dma = false;           // global-to-LDS tile
   bool sk = false;            // stream-K: persistent workgroups split the K-iterations of all
                               // tiles evenly; tiles cut between two of them are summed after
+  int wgs = 0;                // global-to-LDS tiles: resident workgroups per CU
   int splits = 1;             // register tiles: each tile's K-steps in this many runs, summed after
   size_t partial_bytes = 0;   // workspace for stream-K pieces or split partial tiles
   double time = 0;            // the model's time in seconds (0: not a tile of the table)

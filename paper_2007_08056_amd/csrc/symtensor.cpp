@@ -238,6 +238,7 @@ void set_any(const Plan& p, bool chunks, symt::FusedTables* f) {
   f->any_cb = p.any.cb ? 1 : 0;
   f->any_krun = p.any.krun;
   f->any_sk = p.any.sk ? 1 : 0;
+  f->any_chunk = p.any.chunk ? 1 : 0;
   f->any_ch = chunks ? 16 : 4;
 }
 

@@ -66,9 +66,9 @@ int main() {
     const GemmChoice c = p.compute == SYMT_COMPUTE_BF16X3
                              ? GemmChoice{}
                              : choose_fp_gemm(d.nq, d.M, d.gn, d.gk, p.compute == SYMT_COMPUTE_F64 ? 8 : 4, true, d.a_trans);
-    std::printf("fused=%d fused_ua=%d any=%d am=%d ch16=%d sk=%d cb=%d any_direct=%d direct=%d slices=%d wide_bn=%d "
+    std::printf("fused=%d fused_ua=%d any=%d am=%d ch16=%d sk=%d chunk=%d cb=%d any_direct=%d direct=%d slices=%d wide_bn=%d "
                 "tile=%d splits=%d tile_sk=%d workspace=%zu partial=%zu nq=%lld m=%lld k=%lld n=%lld\n",
-                p.fused, p.fused_ua, d.any.tile, d.any.am, d.any.ch16, d.any.sk, d.any.cb, d.any_direct, p.direct != nullptr,
+                p.fused, p.fused_ua, d.any.tile, d.any.am, d.any.ch16, d.any.sk, d.any.chunk, d.any.cb, d.any_direct, p.direct != nullptr,
                 d.slices, d.wide_bn, c.tile, c.splits, c.sk, p.workspace, d.bytes_partial, static_cast<long long>(d.nq),
                 static_cast<long long>(d.M), static_cast<long long>(d.gk), static_cast<long long>(d.gn));
   }
