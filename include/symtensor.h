@@ -141,7 +141,9 @@
  * run, complex v not expanded; info.fused and info.fused_v are then those of the
  * product it replaces), and so do BF16X3 products of real binary32 operands (w of
  * either real type), which then split both in registers; the three-step path multiplies its aligned forms on the
- * same tile, in the same K-steps and stream-K shares.  The workspace holds
+ * same tile, in the same K-steps and stream-K shares (where u's or v's layout would take 16-byte loads and its
+ * data is not 16-byte aligned, 4-byte loads may take another tile and stream-K then groups its sums otherwise,
+ * within the same bound).  The workspace holds
  * U_al in that case (left unused when u is read in place), then V_al (used when
  * v is not read in place) and the tables.  Where K-steps are the three-step path's, results are identical in
  * value to it: the product sums in the same order.

@@ -51,7 +51,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <atomic>
 #include <cstdint>
 #include <type_traits>
 
@@ -457,14 +456,10 @@ hipError_t launch_any_kernel(int64_t batch, int M, int N, const AnySteps& st, co
   auto kern = k_gemm_any<T, BM, BN, WM, WN, S, CH, AM, CB, BF, TC, CK>;
   int P = 0, ts = 0;
   if (sk && part) {
-    // resident workgroups per CU of this instantiation, cached
-    static std::atomic<int> occupancy{0};
-    int occ = occupancy.load(std::memory_order_relaxed);
-    if (occ == 0) {
-      if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kern, 64 * WM * WN, 0) != hipSuccess || occ < 1) occ = 1;
-      occupancy.store(occ, std::memory_order_relaxed);
-    }
-    const SkLaunch sl = sk_launch(ntiles, tiles_n, st.nk, std::min<int64_t>(kSkSlots, static_cast<int64_t>(device_cus()) * occ),
+    // (as many per CU as every layout of this tile and load width admits: the in-place
+    // product and the three steps share K out alike)
+    constexpr int wgs = kAnyWavesPerSimd<BM, BN, CH, BF>;
+    const SkLaunch sl = sk_launch(ntiles, tiles_n, st.nk, std::min<int64_t>(kSkSlots, static_cast<int64_t>(device_cus()) * wgs),
                                   static_cast<int64_t>(part_bytes / sizeof(TP)), static_cast<int64_t>(BM) * BN,
                                   kSkMinIters);
     P = sl.P;

@@ -158,27 +158,39 @@ struct AnyChoice {
 };
 // Tiles of the in-place product for any layout (launch order), their efficiency
 // with 16-byte and with 4-byte loads (measured on 8 x (4608 x 4608 x 288): f64 0.86,
-// 0.80, 0.75; 4-byte loads on 3 x (743 x 1113 x 1111): 0.5), and resident workgroups
-// per CU.
+// 0.80, 0.75; 4-byte loads on 3 x (743 x 1113 x 1111): 0.5; 0: no such kernel), and
+// stream-K workgroups per CU with each.
 struct AnyTileDesc {
   const char* name;
   int bm, bn;
   double eff16, eff4;
-  int wgs;
+  int wgs, wgs4;
 };
 constexpr AnyTileDesc kAnyTiles[] = {
-    {"a96x96s2", 96, 96, 0.85, 0.5, 3}, {"a128x64s2", 128, 64, 0.80, 0.5, 3}, {"a64x64s2", 64, 64, 0.75, 0.5, 3}};
-AnyChoice choose_any(int64_t batch, int64_t M, int64_t N, int64_t kpad, int elem, bool ch16, const char* forced,
-                     int sk_mode) {
+    {"a96x96s2", 96, 96, 0.85, 0, 3, 0}, {"a128x64s2", 128, 64, 0.80, 0.5, 3, 2}, {"a64x64s2", 64, 64, 0.75, 0.5, 3, 3}};
+// Whether a choice may take tile i (of a table of AnyTileDesc): the one that is named, or
+// the second where the named first one has no kernel for these loads (as its launch does).
+bool any_usable(const AnyTileDesc* tiles, int i, bool ch16, const char* forced) {
+  if (forced && std::strcmp(forced, tiles[i].name) != 0)
+    return i == 1 && !ch16 && tiles[0].eff4 == 0 && std::strcmp(forced, tiles[0].name) == 0;
+  return ch16 || tiles[i].eff4 != 0;
+}
+// steps16: the three-step path's aligned forms take 16-byte loads as well.  Where it must
+// load otherwise, stream-K needs a tile that shares K out the same way with both.
+bool any_sk_usable(const AnyTileDesc& t, bool ch16, bool steps16) {
+  return ch16 == steps16 || (t.eff4 != 0 && t.wgs == t.wgs4);
+}
+AnyChoice choose_any(int64_t batch, int64_t M, int64_t N, int64_t kpad, int elem, bool ch16, bool steps16,
+                     const char* forced, int sk_mode) {
   AnyChoice best;
   const double per_cu = (elem == 8 ? 78.6e12 : 157.3e12) / 256.0;
   for (int i = 0; i < static_cast<int>(sizeof(kAnyTiles) / sizeof(kAnyTiles[0])); ++i) {
     const AnyTileDesc& t = kAnyTiles[i];
-    if (forced && std::strcmp(forced, t.name) != 0) continue;
+    if (!any_usable(kAnyTiles, i, ch16, forced)) continue;
     const int64_t tiles = batch * ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
     const double t_tile = 2.0 * t.bm * t.bn * static_cast<double>(kpad) / ((ch16 ? t.eff16 : t.eff4) * per_cu);
     for (int sk = 0; sk < 2; ++sk) {
-      if (sk ? sk_mode == 0 : sk_mode == 1) continue;
+      if (sk ? sk_mode == 0 || !any_sk_usable(t, ch16, steps16) : sk_mode == 1 && any_sk_usable(t, ch16, steps16)) continue;
       const size_t partial = sk ? 2 * static_cast<size_t>(std::min(kSkSlots, 256 * t.wgs)) * t.bm * t.bn * elem : 0;
       double time;
       if (sk) {
@@ -203,21 +215,21 @@ AnyChoice choose_any(int64_t batch, int64_t M, int64_t N, int64_t kpad, int elem
 // with 16- and 4-byte loads, stream-K and not (its own choice is 7% from the best
 // of them in the mean, planes alone 2.4 times).
 constexpr AnyTileDesc kAnyTilesBf16[] = {
-    {"a128x128s2", 128, 128, 0.31, 0, 2}, {"a128x64s2", 128, 64, 0.22, 0.17, 2}, {"a64x64s2", 64, 64, 0.19, 0.14, 3}};
+    {"a128x128s2", 128, 128, 0.31, 0, 2, 0}, {"a128x64s2", 128, 64, 0.22, 0.17, 2, 2},
+    {"a64x64s2", 64, 64, 0.19, 0.14, 3, 3}};
 constexpr double kBf16PerCu = 2500e12 / 3 / 256;
 AnyChoice choose_any_bf16(int64_t batch, int64_t M, int64_t N, int64_t kpad, double bytes, bool ch16,
-                          const char* forced, int sk_mode) {
+                          bool steps16, const char* forced, int sk_mode) {
   AnyChoice best;
   const double mem = bytes / 1.9e12;
   for (int i = 0; i < static_cast<int>(sizeof(kAnyTilesBf16) / sizeof(kAnyTilesBf16[0])); ++i) {
     const AnyTileDesc& t = kAnyTilesBf16[i];
-    if (forced && std::strcmp(forced, t.name) != 0) continue;
-    if (!forced && !ch16 && t.eff4 == 0) continue;
+    if (!any_usable(kAnyTilesBf16, i, ch16, forced)) continue;
     const int64_t tiles = batch * ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
-    const double eff = ch16 || t.eff4 == 0 ? t.eff16 : t.eff4;
+    const double eff = ch16 ? t.eff16 : t.eff4;
     const double t_tile = 2.0 * t.bm * t.bn * static_cast<double>(kpad) / (eff * kBf16PerCu);
     for (int sk = 0; sk < 2; ++sk) {
-      if (sk ? sk_mode == 0 : sk_mode == 1) continue;
+      if (sk ? sk_mode == 0 || !any_sk_usable(t, ch16, steps16) : sk_mode == 1 && any_sk_usable(t, ch16, steps16)) continue;
       // (pieces are binary64)
       const size_t partial = sk ? 2 * static_cast<size_t>(std::min(kSkSlots, 256 * t.wgs)) * t.bm * t.bn * 8 : 0;
       const int64_t rounds = (tiles + 255) / 256;
@@ -385,14 +397,15 @@ bool plan_any(Plan* p, int want, bool trailing_k, int64_t run) {
                                                          : i_run % ve == 0 && (pe * p->M) % ve == 0;
   const bool b16 = (y.b ? j_run % ve == 0 : true) && p->gn % ve == 0;
   y.ch16 = a16 && b16;
+  y.steps16 = p->gk % ve == 0 && p->gn % ve == 0 && y.krun % ve == 0;
   const int64_t ksteps = y.krun > 0 ? p->gk / y.krun * ((y.krun + bk - 1) / bk) : (p->gk + bk - 1) / bk;
   const char* forced = std::getenv("SYMT_GEMM_TILE");
   const char* sk_env = std::getenv("SYMT_GEMM_SK");
   const int sk_mode = sk_env ? std::atoi(sk_env) : -1;
   const AnyChoice c =
       bf ? choose_any_bf16(nb, p->M, p->gn, ksteps * bk,
-                           4.0 * static_cast<double>(p->U.elems + p->V.elems + p->W.elems), y.ch16, forced, sk_mode)
-         : choose_any(nb, p->M, p->gn, ksteps * bk, elem, y.ch16, forced, sk_mode);
+                           4.0 * static_cast<double>(p->U.elems + p->V.elems + p->W.elems), y.ch16, y.steps16, forced, sk_mode)
+         : choose_any(nb, p->M, p->gn, ksteps * bk, elem, y.ch16, y.steps16, forced, sk_mode);
   if (c.tile < 0) return false;
   if (bf && !forced) {
     // against the product on hi/lo planes
@@ -427,9 +440,9 @@ bool plan_any(Plan* p, int want, bool trailing_k, int64_t run) {
   }
   if (!bf && elem == 4) {
     // binary32 sums no longer than those of the product it replaces, on aligned data or not
-    const int64_t own = c.sk ? longest_share(nb, p->M, p->gn, p->gk, ksteps, kAnyTiles[c.tile].bm, kAnyTiles[c.tile].bn,
-                                             kAnyTiles[c.tile].wgs)
-                             : p->gk;
+    const AnyTileDesc& t = kAnyTiles[c.tile];
+    const int64_t own =
+        c.sk ? longest_share(nb, p->M, p->gn, p->gk, ksteps, t.bm, t.bn, y.ch16 ? t.wgs : t.wgs4) : p->gk;
     for (bool aligned : {true, false})
       y.chunk = y.chunk || own > longest_sum(choose_fp_gemm(nb, p->M, p->gn, p->gk, elem, aligned, p->a_trans && aligned), nb,
                                              p->M, p->gn, p->gk, elem);
@@ -975,8 +988,7 @@ int plan_contraction(const char* einsum, const symt_group* group, const symt_ten
     }
     p->any.am = 0;
     p->any.b = p->any.cb = false;
-    const int64_t ve = compute == SYMT_COMPUTE_F64 ? 2 : 4;
-    p->any.ch16 = p->gk % ve == 0 && p->gn % ve == 0 && p->any.krun % ve == 0;
+    p->any.ch16 = p->any.steps16;
   } else if (p->any.tile >= 0) {
     // U is not aligned then, nor V where it has tables of its own (4-byte loads take any alignment)
     const size_t G = static_cast<size_t>(nb);

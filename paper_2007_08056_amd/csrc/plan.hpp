@@ -255,6 +255,7 @@ struct Plan {
     int32_t tile = -1, am = 0, krun = 0;
     bool cb = false, ch16 = false, sk = false, b = false;
     bool chunk = false;             // binary32: sums of 128 indices
+    bool steps16 = false;           // the aligned forms (three steps) hold whole 16-byte chunks
     int64_t ldb = 0;                // V's row stride (reals) with b
     size_t partial_bytes = 0;
     double time = 0;                // the model's, in seconds

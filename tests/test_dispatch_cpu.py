@@ -1,4 +1,6 @@
 """Which product the planner takes, by default and with its tuning variables (host only)."""
+import random
+
 from tests import planner as PL
 
 
@@ -20,3 +22,39 @@ def test_wide_split_bf16_tiles_where_they_were_measured_faster():
              (ladder(8, 24, 0, (6, 6)), 0)]               # no contracted index at all
     got = PL.plans([ln for ln, _ in cases])
     assert [p["wide_bn"] for p in got] == [bn for _, bn in cases]
+
+
+def test_in_place_and_steps_share_k_out_alike():
+    # stream-K cuts K where its tile, its loads' width and its workgroups per CU say: the three
+    # steps must have the in-place product's, so that both sum the same ranges
+    rng = random.Random(11)
+    forms = [("abcd,cdij->abij", "++--", "++--"), ("klab,klij->abij", "--++", "++--"), ("ak,kb->ab", "+-", "+-"),
+             ("ka,kb->ab", "-+", "+-"), ("abk,ki->abi", "++-", "+-"), ("ak,ik->ai", "+-", "-+")]
+    # (two that ran 128 x 64 in place against 96 x 96 in steps, then random ones)
+    cases = [("abcd,cdij->abij", (8,), "++--", (25, 9, 15, 20), "++--", (15, 20, 3, 3), PL.F64, "f64"),
+             ("abcd,cdij->abij", (8,), "++--", (3, 4, 16, 14), "++--", (16, 14, 29, 6), PL.F32, "f32")]
+    for _ in range(3000):
+        sub, su, sv = rng.choice(forms)
+        tu, tv = sub.split("->")[0].split(",")
+        pair = len(tu) == 2
+        d = {c: rng.randint(1, 900) if pair and rng.random() < .7 else 4 * rng.randint(1, 250) if pair
+             else rng.choice([rng.randint(1, 40), 2 * rng.randint(1, 20)]) for c in dict.fromkeys(tu + tv)}
+        dt, comp = rng.choice([(PL.F64, "f64"), (PL.F32, "f32"), (PL.C128, "f64"), (PL.C64, "f32"), (PL.F32, "bf16x3")])
+        cases.append((sub, (rng.choice([1, 2, 3, 4, 6, 8]),), su, tuple(d[c] for c in tu), sv, tuple(d[c] for c in tv), dt,
+                      comp))
+    got = PL.plans([PL.line(*c) for c in cases] + [PL.line(*c, steps=True) for c in cases])
+    cut = 0
+    for c, a, b in zip(cases, got, got[len(cases):]):
+        if a["any"] < 0 or a["wide_bn"]:
+            continue
+        # a tile's launch takes 128 x 64 where the first one has no kernel for 4-byte loads
+        def runs(p):
+            tile = p["any"] if p["ch16"] else max(p["any"], 1)
+            wgs = 3 if tile == 2 else 2 if c[-1] == "bf16x3" or (tile == 1 and not p["ch16"]) else 3
+            return tile, wgs
+        assert a["ch16"] or a["any"] > 0, c               # the planner's choice is the tile that runs
+        assert a["sk"] == b["sk"] and a["chunk"] == b["chunk"] and a["any"] == b["any"], c
+        if a["sk"]:
+            cut += 1
+            assert runs(a) == runs(b), c
+    assert cut > 100
