@@ -176,8 +176,10 @@
  * Return values: SYMT_OK (0) or one of the negative codes below; the detail of
  * the last failure on a context is in symtensor_last_error().
  *
- * Environment (read at planning and launch time; for tuning and tests only,
- * never needed for correctness: every tile meets the same accuracy bound):
+ * Environment (read at planning, and by symtensor_sector_gemm at launch; a
+ * contraction is launched with the values it was planned under; for tuning and
+ * tests only, never needed for correctness: every tile meets the same accuracy
+ * bound):
  *   SYMT_GEMM_TILE=<name>  restricts the sector product to one tile where that
  *                          tile applies (F64/F32: "128x96", "d96x96s2", ...,
  *                          "rows" = the row-streaming product taken by default
@@ -195,7 +197,7 @@
  *                          the global-to-LDS tiles.
  *   SYMT_FUSED_V=0         keeps V aligned in the fused product (info.fused_v = 0).
  *   SYMT_GEMM_GROUP_M=<n>  M-panels per group in the tile order of the wide
- *                          split-bf16 tiles (default 8).
+ *                          split-bf16 tiles (default 8; read at launch).
  *   SYMT_BF16_IL=0         keeps the wide split-bf16 tiles' planes one after the
  *                          other (not interleaved by K-steps).
  *   SYMT_BF16_FA=0         keeps u on planes for the 256 x 256 wide split-bf16

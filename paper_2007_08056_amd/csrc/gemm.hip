@@ -1311,7 +1311,7 @@ int launch_sector_gemm(int compute, int64_t batch, int64_t m, int64_t k, int64_t
       if (err) *err = "split-bf16 product needs the contracted extent to be a multiple of 8";
       return SYMT_EUNSUPPORTED;
     }
-    const char* forced = std::getenv("SYMT_GEMM_TILE");
+    const char* forced = tuned(kTuneTile);
     const std::string f = forced ? forced : "";
     const bool dma_ok = K % 32 == 0;
     const int64_t pa = plane_a > 0 ? plane_a : batch * static_cast<int64_t>(M) * K;

@@ -381,7 +381,7 @@ bool plan_any(Plan* p, int want, bool trailing_k, int64_t run) {
   auto& y = p->any;
   y.am = trailing_k ? 0 : p->cplx ? 2 : 1;
   int64_t ldb = 0;
-  const char* vip = std::getenv("SYMT_FUSED_V");
+  const char* vip = tuned(kTuneFusedV);
   y.b = !(vip && std::atoi(vip) == 0) && v_rows_affine(*p, &ldb);
   y.cb = y.b && p->cplx;
   if (y.am == 2 && !y.cb) return false;
@@ -399,8 +399,8 @@ bool plan_any(Plan* p, int want, bool trailing_k, int64_t run) {
   y.ch16 = a16 && b16;
   y.steps16 = p->gk % ve == 0 && p->gn % ve == 0 && y.krun % ve == 0;
   const int64_t ksteps = y.krun > 0 ? p->gk / y.krun * ((y.krun + bk - 1) / bk) : (p->gk + bk - 1) / bk;
-  const char* forced = std::getenv("SYMT_GEMM_TILE");
-  const char* sk_env = std::getenv("SYMT_GEMM_SK");
+  const char* forced = tuned(kTuneTile);
+  const char* sk_env = tuned(kTuneSk);
   const int sk_mode = sk_env ? std::atoi(sk_env) : -1;
   const AnyChoice c =
       bf ? choose_any_bf16(nb, p->M, p->gn, ksteps * bk,
@@ -490,12 +490,12 @@ double wide_time(const Plan& p, int bn) {
 // wide_bn / 2 columns each): a binary32 U whose contracted modes are its last ones in runs
 // of 4, K in whole 32-deep steps.
 void plan_wide(Plan* p, bool trailing_k) {
-  const char* fa_env = std::getenv("SYMT_BF16_FA");
+  const char* fa_env = tuned(kTuneFa);
   if (p->cplx || p->U.dtype != SYMT_F32 || p->V.dtype != SYMT_F32 || !trailing_k || p->nK % 4 != 0 || p->gk % 32 != 0 ||
       p->M < 256 || p->gn <= 0 || p->gk <= 0 || p->v < 1 || p->w_col_run < 16 || (fa_env && std::atoi(fa_env) == 0))
     return;
-  const char* tile = std::getenv("SYMT_GEMM_TILE");
-  const char* sk_env = std::getenv("SYMT_GEMM_SK");
+  const char* tile = tuned(kTuneTile);
+  const char* sk_env = tuned(kTuneSk);
   if (sk_env && std::atoi(sk_env) == 0) return;
   int bn = 0;
   double time = 0;
@@ -787,7 +787,7 @@ int plan_contraction(const char* einsum, const symt_group* group, const symt_ten
   // ... and up to a multiple of 32 where a wide tile multiplies them (32-deep
   // K-steps), if that adds at most an eighth of K
   if (compute == SYMT_COMPUTE_BF16X3 && p->kpad % 32 != 0 && p->nq > 0 && p->M > 0 && p->gn > 0) {
-    const char* tile_env = std::getenv("SYMT_GEMM_TILE");
+    const char* tile_env = tuned(kTuneTile);
     const std::string tile = tile_env ? tile_env : "";
     const int64_t k32 = (p->gk + 31) / 32 * 32;
     const bool wide = tile.empty() ? bf16x3_wide_tile(p->nq, p->M, p->gn) >= 0
@@ -942,7 +942,7 @@ int plan_contraction(const char* einsum, const symt_group* group, const symt_ten
   // ---- V read in place as well (see v_in_place_layout); V_al keeps its place in
   // the workspace: a V that is not 16-byte aligned is aligned as before.
   int64_t ldb = 0;
-  const char* vip_env = std::getenv("SYMT_FUSED_V");
+  const char* vip_env = tuned(kTuneFusedV);
   const bool vip_off = vip_env && std::atoi(vip_env) == 0;
   bool chunks = false;
   if (!vip_off && (p->fused || p->fused_ua) && !p->cplx && p->V.dtype == want &&
@@ -959,13 +959,13 @@ int plan_contraction(const char* einsum, const symt_group* group, const symt_ten
   // SYMT_BF16_IL=0 keeps the plane-after-plane layout (tuning and tests)
   if (compute == SYMT_COMPUTE_BF16X3 && !p->cplx && !p->fused && !p->fused_b && p->nq > 0 && p->M > 0 &&
       p->gn > 0 && p->kpad % 32 == 0) {
-    const char* tile_env = std::getenv("SYMT_GEMM_TILE");
+    const char* tile_env = tuned(kTuneTile);
     const std::string tile = tile_env ? tile_env : "";
-    const char* il_env = std::getenv("SYMT_BF16_IL");
+    const char* il_env = tuned(kTuneIl);
     const bool wide = tile.empty() ? bf16x3_wide_tile(p->nq, p->M, p->gn) >= 0
                                    : tile == "bw256x256s2" || tile == "bw256x128s3";
     p->bf16_il = wide && !(il_env && std::atoi(il_env) == 0);
-    const char* fa_env = std::getenv("SYMT_BF16_FA");
+    const char* fa_env = tuned(kTuneFa);
     const bool wide256 = tile.empty() ? bf16x3_wide_tile(p->nq, p->M, p->gn) == 0 : tile == "bw256x256s2";
     p->bf16_wide_fa = p->bf16_il && wide256 && p->fused_ua && p->U.dtype == SYMT_F32 && trailing_k &&
                       p->nK % 4 == 0 && p->gk == p->kpad && !(fa_env && std::atoi(fa_env) == 0);
@@ -1028,8 +1028,26 @@ int plan_contraction(const char* einsum, const symt_group* group, const symt_ten
 }
 }  // namespace
 
+namespace {
+thread_local const Tuning* t_tuning = nullptr;
+}  // namespace
+
+const char* tuned(TuningVar v) {
+  static constexpr const char* kNames[kTuningVars] = {"SYMT_FUSED_V", "SYMT_GEMM_TILE", "SYMT_GEMM_SK", "SYMT_BF16_IL",
+                                                      "SYMT_BF16_FA"};
+  if (t_tuning) return t_tuning->set[v] ? t_tuning->value[v].c_str() : nullptr;
+  return std::getenv(kNames[v]);
+}
+TuningScope::TuningScope(const Tuning* t) : outer_(t_tuning) { t_tuning = t; }
+TuningScope::~TuningScope() { t_tuning = outer_; }
+
 int make_plan(const char* einsum, const symt_group* group, const symt_tensor* u, const symt_tensor* v,
               const symt_tensor* w, int32_t compute, Plan* p, std::string* err) {
+  auto t = std::make_shared<Tuning>();
+  for (int i = 0; i < kTuningVars; ++i)
+    if (const char* x = tuned(static_cast<TuningVar>(i))) t->set[i] = true, t->value[i] = x;
+  TuningScope scope(t.get());
+  if (p) p->tuning = t;
   return plan_contraction(einsum, group, u, v, w, compute, false, p, err);
 }
 
@@ -1207,8 +1225,8 @@ bool tallk_groups(const Plan& p) {
 // the DMA tiles.
 GemmChoice choose_fp_gemm(int64_t batch, int64_t M, int64_t N, int64_t K, int elem, bool aligned,
                           bool a_kmajor) {
-  const char* forced = std::getenv("SYMT_GEMM_TILE");
-  const char* sk_env = std::getenv("SYMT_GEMM_SK");
+  const char* forced = tuned(kTuneTile);
+  const char* sk_env = tuned(kTuneSk);
   const int sk_mode = sk_env ? std::atoi(sk_env) : -1;
   GemmChoice g = choose_among(batch, M, N, K, elem, aligned, forced, sk_mode, a_kmajor);
   if (g.tile < 0) g = choose_among(batch, M, N, K, elem, aligned, nullptr, sk_mode, a_kmajor);
@@ -1219,7 +1237,7 @@ GemmChoice choose_fp_gemm(int64_t batch, int64_t M, int64_t N, int64_t K, int el
 // by default global-to-LDS tiles where K holds whole 32-deep steps and the
 // product is at least 256 x 512.
 bool bf16x3_register_tile(int64_t M, int64_t N, int64_t K) {
-  const char* forced = std::getenv("SYMT_GEMM_TILE");
+  const char* forced = tuned(kTuneTile);
   const std::string f = forced ? forced : "";
   const bool dma_ok = K % 32 == 0;
   if ((f == "bd256x128s3" || f == "bd128x256s3" || f == "bw256x256s2" || f == "bw256x128s3") && dma_ok)
@@ -1244,7 +1262,7 @@ int bf16x3_wide_tile(int64_t batch, int64_t M, int64_t N) {
 }
 
 int bf16x3_fused_tile(int64_t M, int64_t N) {
-  const char* forced = std::getenv("SYMT_GEMM_TILE");
+  const char* forced = tuned(kTuneTile);
   const std::string f = forced ? forced : "";
   if (f == "b128x64k32") return 0;
   if (f == "b128x256k32") return 2;

@@ -174,6 +174,27 @@ struct FusedTables {
   int32_t any_chunk = 0;            // 1: binary32 sums of 128 indices (the replaced product cuts K)
 };
 
+// The tuning variables that plans and launches read (include/symtensor.h).  A plan keeps the
+// values it was made under, and its launches read those (TuningScope), whatever the
+// environment holds by then: tile and stream-K choices made at both times agree.
+enum TuningVar { kTuneFusedV, kTuneTile, kTuneSk, kTuneIl, kTuneFa, kTuningVars };
+struct Tuning {
+  bool set[kTuningVars] = {};
+  std::string value[kTuningVars];
+};
+// A variable's value: of this thread's innermost TuningScope, else the environment's; nullptr if unset.
+const char* tuned(TuningVar v);
+class TuningScope {
+ public:
+  explicit TuningScope(const Tuning* t);
+  ~TuningScope();
+  TuningScope(const TuningScope&) = delete;
+  TuningScope& operator=(const TuningScope&) = delete;
+
+ private:
+  const Tuning* outer_;
+};
+
 // One launch of the in-place product for any layout.
 struct AnyLaunch {
   int tile, am, ch;
@@ -192,6 +213,7 @@ struct OperandDesc {
 };
 
 struct Plan {
+  std::shared_ptr<const Tuning> tuning;   // the variables' values when it was made
   GroupDesc g;
   std::string tu, tv, tw;
   int32_t s = 0, t = 0, v = 0, sigma = 0;

@@ -610,6 +610,7 @@ namespace {
 // symtensor_contract_static): every check runs before the first launch.
 int contract_planned(symt_ctx* ctx, const Plan& p, void* workspace, size_t workspace_bytes, void* stream,
                      PlanTables* tables = nullptr) {
+  symt::TuningScope tuning(p.tuning.get());
   int rc;
   if ((rc = check_data(ctx, p.U, "u")) || (rc = check_data(ctx, p.V, "v")) ||
       (rc = check_data(ctx, p.W, "w")))
