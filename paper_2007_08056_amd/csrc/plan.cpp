@@ -336,6 +336,10 @@ bool v_in_place_layout(const Plan& p, int64_t* ldb, bool* chunks) {
 }
 
 namespace {
+// SYMT_GEMM_TILE where it names a tile of a split-bf16 product (bf) or of the others; an
+// empty value or any other name restricts nothing (nullptr).
+const char* forced_tile(bool bf);
+
 // Most K indices that one accumulator of a product on bm x bn tiles sums: all of K, or the
 // share of a stream-K workgroup.
 int64_t longest_share(int64_t batch, int64_t M, int64_t N, int64_t K, int64_t nk, int bm, int bn, int wgs) {
@@ -399,7 +403,7 @@ bool plan_any(Plan* p, int want, bool trailing_k, int64_t run) {
   y.ch16 = a16 && b16;
   y.steps16 = p->gk % ve == 0 && p->gn % ve == 0 && y.krun % ve == 0;
   const int64_t ksteps = y.krun > 0 ? p->gk / y.krun * ((y.krun + bk - 1) / bk) : (p->gk + bk - 1) / bk;
-  const char* forced = tuned(kTuneTile);
+  const char* forced = forced_tile(bf);
   const char* sk_env = tuned(kTuneSk);
   const int sk_mode = sk_env ? std::atoi(sk_env) : -1;
   const AnyChoice c =
@@ -494,13 +498,13 @@ void plan_wide(Plan* p, bool trailing_k) {
   if (p->cplx || p->U.dtype != SYMT_F32 || p->V.dtype != SYMT_F32 || !trailing_k || p->nK % 4 != 0 || p->gk % 32 != 0 ||
       p->M < 256 || p->gn <= 0 || p->gk <= 0 || p->v < 1 || p->w_col_run < 16 || (fa_env && std::atoi(fa_env) == 0))
     return;
-  const char* tile = tuned(kTuneTile);
+  const char* tile = forced_tile(true);
   const char* sk_env = tuned(kTuneSk);
   if (sk_env && std::atoi(sk_env) == 0) return;
   int bn = 0;
   double time = 0;
   for (int c : {288, 256, 224, 192}) {
-    if (tile && *tile && std::string("bw256x") + std::to_string(c) + "sk" != tile) continue;
+    if (tile && std::string("bw256x") + std::to_string(c) + "sk" != tile) continue;
     const double t = wide_time(*p, c);
     if (bn == 0 || t < time) bn = c, time = t;
   }
@@ -518,7 +522,7 @@ void plan_wide(Plan* p, bool trailing_k) {
   d->bytes_tables = round_up(8 * G * p->M, 256) * 2 + round_up(8 * G * p->gk, 256) + round_up(8 * G * p->gn, 256);
   d->workspace = round_up(p->ws_v_al, 256) + d->bytes_tables + round_up(d->bytes_partial, 256) +
                  round_up(p->bytes_charges, 256);
-  if (!tile || !*tile) {
+  if (!tile) {
     // Where the model says it takes at most 0.8 of the plan's own time: of 70 random
     // products the 14 under it took 0.47 to 0.99 of that plan's measured time (the other
     // plans' models are off by up to 1.6), the 12 at 0.8 to 0.9 took 0.71 to 1.34.
@@ -1097,6 +1101,28 @@ constexpr double kSkEff64 = 0.965, kSkEff32 = 0.80;
 // efficiency (the efficiencies above come from launches of many tiles per CU).
 constexpr int64_t kRegSaturation = 3;
 constexpr int kNumFpTiles = sizeof(kFpTiles) / sizeof(kFpTiles[0]);
+}  // namespace
+
+namespace {
+const char* forced_tile(bool bf) {
+  const char* name = tuned(kTuneTile);
+  if (!name) return nullptr;
+  auto is = [&](const char* x) { return std::strcmp(name, x) == 0; };
+  if (bf) {
+    for (const AnyTileDesc& t : kAnyTilesBf16)
+      if (is(t.name)) return name;
+    for (const char* x : {"b128x128k64", "b128x128k32", "b256x128k32", "b128x256k32", "b128x64k32", "b128x96k32",
+                          "b64x64k32", "bd256x128s3", "bd128x256s3", "bw256x256s2", "bw256x128s3", "bw256x192sk",
+                          "bw256x224sk", "bw256x256sk", "bw256x288sk"})
+      if (is(x)) return name;
+    return nullptr;
+  }
+  for (const FpTile& t : kFpTiles)
+    if (is(t.name)) return name;
+  for (const AnyTileDesc& t : kAnyTiles)
+    if (is(t.name)) return name;
+  return is("rows") || is("tallk") ? name : nullptr;
+}
 }  // namespace
 
 // Time model: a tile costs 2*bm*bn*K flops at its measured efficiency of one

@@ -58,3 +58,22 @@ def test_in_place_and_steps_share_k_out_alike():
             cut += 1
             assert runs(a) == runs(b), c
     assert cut > 100
+
+
+def test_tile_names_that_restrict_nothing():
+    # an unknown or empty name, or one of another compute mode's tiles, leaves the default choice
+    mm = lambda dt, comp, G=8, M=500, K=1000, N=600: PL.line("ak,kb->ab", (G,), "+-", (M, K), "++", (K, N), dt, comp)
+    f64 = [mm(PL.F64, "f64", 9, 500, 500, 500), mm(PL.C128, "f64"), mm(PL.C64, "f32")]
+    bf = [ladder(8, 24, 24, (6, 6)), mm(PL.F32, "bf16x3"), ladder(2, 9, 5, (3, 4))]
+    want, want_bf = PL.plans(f64), PL.plans(bf)
+    assert all(p["any"] >= 0 for p in want) and want_bf[0]["wide_bn"] and all(p["any"] >= 0 for p in want_bf[1:])
+    for name in ("", "no-such-tile", "bw256x288sk", "a128x128s2"):
+        assert PL.plans(f64, SYMT_GEMM_TILE=name) == want, name
+    for name in ("", "no-such-tile", "a96x96s2", "d96x96s2", "tallk"):
+        assert [(p["any"], p["wide_bn"]) for p in PL.plans(bf, SYMT_GEMM_TILE=name)] == \
+            [(p["any"], p["wide_bn"]) for p in want_bf], name
+    # names of other tiles of the same compute mode keep these products out
+    for name in ("96x96", "d128x128s2", "rows", "tallk"):
+        assert all(p["any"] < 0 for p in PL.plans(f64, SYMT_GEMM_TILE=name)), name
+    for name in ("b128x128k32", "bd128x256s3", "bw256x256s2"):
+        assert all(p["any"] < 0 and not p["wide_bn"] for p in PL.plans(bf, SYMT_GEMM_TILE=name)), name
