@@ -153,7 +153,6 @@ int read_operand(const symt_tensor* t, const GroupDesc& g, OperandDesc* o, const
 struct AnyChoice {
   int tile = -1;
   bool sk = false;
-  size_t partial_bytes = 0;
   double time = 0;
 };
 // Tiles of the in-place product for any layout (launch order), their efficiency
@@ -203,7 +202,7 @@ AnyChoice choose_any(int64_t batch, int64_t M, int64_t N, int64_t kpad, int elem
         const int64_t rounds = (tiles + 255) / 256;
         time = static_cast<double>(rounds) * t_tile / (rounds == 1 ? 0.57 : rounds == 2 ? 0.87 : 1.0);
       }
-      if (best.tile < 0 || time < best.time) best = AnyChoice{i, sk != 0, partial, time};
+      if (best.tile < 0 || time < best.time) best = AnyChoice{i, sk != 0, time};
     }
   }
   return best;
@@ -237,10 +236,24 @@ AnyChoice choose_any_bf16(int64_t batch, int64_t M, int64_t N, int64_t kpad, dou
                              : static_cast<double>(rounds) * t_tile / (rounds == 1 ? 0.57 : rounds == 2 ? 0.96 : 1.0);
       const double time = std::max(busy, mem) + 0.2 * std::min(busy, mem) +
                           (sk ? 0.7 * static_cast<double>(partial) / 5e12 + 15e-6 : 13e-6);
-      if (best.tile < 0 || time < best.time) best = AnyChoice{i, sk != 0, partial, time};
+      if (best.tile < 0 || time < best.time) best = AnyChoice{i, sk != 0, time};
     }
   }
   return best;
+}
+
+// Bytes of the pieces that a choice's launch can leave, with either load width (data that is
+// not 16-byte aligned takes 4-byte loads): two per workgroup that the K-steps can fill.
+size_t any_pieces(const AnyTileDesc* tiles, int tile, int64_t batch, int64_t M, int64_t N, int64_t nk, size_t elem) {
+  size_t most = 0;
+  for (bool ch16 : {true, false}) {
+    const AnyTileDesc& t = tiles[ch16 || tiles[tile].eff4 != 0 ? tile : 1];
+    const int64_t tn = (N + t.bn - 1) / t.bn, area = static_cast<int64_t>(t.bm) * t.bn;
+    const SkLaunch sl = sk_launch(batch * ((M + t.bm - 1) / t.bm) * tn, static_cast<int>(tn), static_cast<int>(nk),
+                                  std::min(kSkSlots, 256 * (ch16 ? t.wgs : t.wgs4)), int64_t(1) << 60, area, kSkMinIters);
+    most = std::max(most, 2 * static_cast<size_t>(sl.P) * static_cast<size_t>(area) * elem);
+  }
+  return most;
 }
 
 // The time of a split-bf16 plan on hi/lo planes: its passes over U, V and W (12
@@ -454,7 +467,8 @@ bool plan_any(Plan* p, int want, bool trailing_k, int64_t run) {
   y.tile = c.tile;
   y.sk = c.sk;
   y.ldb = ldb;
-  y.partial_bytes = c.partial_bytes;
+  // (split-bf16 pieces are binary64)
+  if (c.sk) y.partial_bytes = any_pieces(bf ? kAnyTilesBf16 : kAnyTiles, c.tile, nb, p->M, p->gn, ksteps, bf ? 8 : elem);
   y.time = c.time;
   return true;
 }
@@ -466,11 +480,15 @@ namespace {
 // tile's pieces are written and read in binary64, and a short K leaves the stores of W in
 // sight.  A fit to 380 timings, 91 products of 0.2 to 930 GFLOP on each width: 6% off in the
 // mean.
+SkLaunch wide_launch(const Plan& p, int bn) {
+  const int64_t half = bn / 2, tm = (p.M + 255) / 256, tn = (p.gn + half - 1) / half;
+  return sk_launch(p.nq * tm * tn, static_cast<int>(tn), static_cast<int>(p.gk / 32), 256, int64_t(1) << 60, 256 * half,
+                   kSkMinIters);
+}
 double wide_time(const Plan& p, int bn) {
   const int64_t half = bn / 2, tm = (p.M + 255) / 256, tn = (p.gn + half - 1) / half, nk = p.gk / 32;
   const int64_t ntiles = p.nq * tm * tn;
-  const SkLaunch sl = sk_launch(ntiles, static_cast<int>(tn), static_cast<int>(nk), 256, int64_t(1) << 60, 256 * half,
-                                kSkMinIters);
+  const SkLaunch sl = wide_launch(p, bn);
   int64_t steps = (ntiles + 255) / 256 * nk, pieces = 0;   // of the fullest workgroup; of all cut tiles
   if (sl.P > 0) {
     const int nteam = sl.P / sl.ts;
@@ -517,7 +535,7 @@ void plan_wide(Plan* p, bool trailing_k) {
   d->krun = 0;
   d->kpad = p->gk;
   d->ws_u_al = 0;                                  // U is never aligned
-  d->bytes_partial = 2 * size_t(256) * 256 * (bn / 2) * 8;   // (binary64 pieces of half tiles)
+  d->bytes_partial = 2 * static_cast<size_t>(wide_launch(*p, bn).P) * 256 * (bn / 2) * 8;   // (binary64 pieces of half tiles)
   const size_t G = static_cast<size_t>(p->g.size);
   d->bytes_tables = round_up(8 * G * p->M, 256) * 2 + round_up(8 * G * p->gk, 256) + round_up(8 * G * p->gn, 256);
   d->workspace = round_up(p->ws_v_al, 256) + d->bytes_tables + round_up(d->bytes_partial, 256) +
@@ -1006,7 +1024,7 @@ int plan_contraction(const char* einsum, const symt_group* group, const symt_ten
   if (compute != SYMT_COMPUTE_BF16X3 && p->nq > 0 && p->M > 0 && p->gn > 0 && p->gk > 0) {
     const GemmChoice gc = choose_fp_gemm(p->nq, p->M, p->gn, p->gk,
                                          compute == SYMT_COMPUTE_F64 ? 8 : 4, true, p->a_trans);
-    p->bytes_partial = std::max(gc.partial_bytes, p->any.partial_bytes);
+    p->bytes_partial = p->any.tile >= 0 ? p->any.partial_bytes : gc.partial_bytes;
     p->workspace += round_up(p->bytes_partial, 256);
   } else if (p->any.tile >= 0) {
     p->bytes_partial = p->any.partial_bytes;
