@@ -448,11 +448,17 @@ bool plan_any(Plan* p, int want, bool trailing_k, int64_t run) {
     double mine = c.time;
     if (!y.b) mine += 2.0 * elem * pe * pe * static_cast<double>(p->V.elems) / rate + (p->cplx ? 16e-6 : 8e-6);
     // (0.8 where binary32 splits K: the model is too fast there -- 6 x (1536 x 768 x 64)
-    // takes 56 us on the tile it picks, 27 on 128 x 64 with K split; a complex f64 product
-    // whose U is read along K saves V's passes at most and multiplies at 0.80 of the rate:
-    // 8 x (4608 x 9216 x 576) took 6222 us, 5866 on V_al, at a ratio of 0.94; where U had
-    // to be aligned too it is 0.75 and less)
-    const double keep = g.splits > 1 && elem == 4 ? 0.8 : p->cplx && elem == 8 && y.am == 0 ? 0.85 : 0.95;
+    // takes 56 us on the tile it picks, 27 on 128 x 64 with K split.  Complex products that
+    // would run on global-to-LDS tiles save their align passes and multiply at 0.80 of
+    // those tiles' rate, less with K-major pairs: of 100 products, K-major ones took 1.02 to
+    // 1.14 of the other's time at ratios of 0.79 to 0.9 -- 4 x (4200 x 512 x 10080) f32
+    // 1521 against 1730 us, 8 x (3136 x 2048 x 3872) f64 6407 and 6771 -- and 0.63 to 1.02
+    // below; f64 ones whose U is read along K up to 1.03 from 0.82 on, 0.69 to 1.02 below)
+    const bool gdma = p->cplx && g.dma;
+    const double keep = gdma && y.am == 2                ? 0.78
+                        : gdma && elem == 8 && y.am == 0 ? 0.82
+                        : g.splits > 1 && elem == 4      ? 0.8
+                                                         : 0.95;
     if (mine > keep * other) return false;
   }
   if (!bf && elem == 4) {

@@ -77,3 +77,18 @@ def test_tile_names_that_restrict_nothing():
         assert all(p["any"] < 0 for p in PL.plans(f64, SYMT_GEMM_TILE=name)), name
     for name in ("b128x128k32", "bd128x256s3", "bw256x256s2"):
         assert all(p["any"] < 0 and not p["wide_bn"] for p in PL.plans(bf, SYMT_GEMM_TILE=name)), name
+
+
+def test_complex_products_stay_where_in_place_was_measured_slower():
+    # (G, contracted blocks, u's other blocks, v's other blocks): the in-place product, or not
+    km = lambda G, kl, ab, ij, dt: PL.line("klab,klij->abij", (G,), "--++", kl + ab, "++--", kl + ij, dt,
+                                           "f32" if dt == PL.C64 else "f64")
+    ak = lambda G, kl, ab, ij, dt: PL.line("abkl,klij->abij", (G,), "++--", ab + kl, "++--", kl + ij, dt,
+                                           "f32" if dt == PL.C64 else "f64")
+    slower = [km(6, (2, 16), (44, 36), (8, 38), PL.C64),      # 1471 us before, 1616 in place
+              km(4, (4, 8), (38, 32), (48, 37), PL.C64),      # 1383, 1533
+              km(4, (16, 20), (39, 20), (24, 40), PL.C128)]   # 7782, 8283
+    faster = [km(3, (16, 20), (20, 12), (13, 10), PL.C64),    # 3 x (720 x 1920 x 780): 156, 112
+              ak(2, (4, 8), (27, 11), (26, 43), PL.C64),      # 2 x (594 x 128 x 4472): 47, 26
+              ak(2, (4, 8), (27, 11), (26, 43), PL.C128)]     # 56, 38
+    assert [p["any"] >= 0 for p in PL.plans(slower + faster)] == [False] * 3 + [True] * 3
