@@ -256,34 +256,39 @@ size_t any_pieces(const AnyTileDesc* tiles, int tile, int64_t batch, int64_t M, 
   return most;
 }
 
-// The time of a split-bf16 plan on hi/lo planes: its passes over U, V and W (12
-// bytes read and written per element that goes to planes) and the tile the launcher takes.
+// The time of a split-bf16 plan on the product that it takes by itself: its passes over U
+// and V to planes (12 bytes read and written per element that goes there), the stores of
+// W, and whole rounds of its tiles.  A fit for each product to the times of 510
+// contractions of 0.2 to 550 GFLOP with binary32 W: 7 to 12% off (standard deviation).
 double bf16_planes_time(const Plan& p) {
-  const double rate = 2.9e12;
-  double t = 36e-6 + (12.0 * static_cast<double>(p.V.elems) + 8.0 * static_cast<double>(p.W.elems)) / rate;
-  if (!p.fused) t += 12.0 * static_cast<double>(p.U.elems) / rate + 4e-6;
-  if (!p.fused && !p.fused_ua) t += 24.0 * static_cast<double>(p.W.elems) / rate + 4e-6;
-  const int wide = p.kpad % 32 == 0 ? bf16x3_wide_tile(p.nq, p.M, p.gn) : -1;
-  int64_t bm = 128, bn = 128;
-  double eff = 0.39;
-  if (wide >= 0) {
-    bm = 256, bn = wide == 0 ? 256 : 128, eff = 0.93;
-  } else if (!bf16x3_register_tile(p.M, p.gn, p.kpad)) {
-    bn = 256, eff = 0.72;
-  } else if (p.fused) {
-    const int tile = bf16x3_fused_tile(p.M, p.gn);
-    bn = tile == 0 ? 64 : tile == 2 ? 256 : tile == 3 ? 96 : 128;
-    if (tile == 0) eff *= 0.5;
-  } else if (p.gn <= 64) {
-    bn = 64, eff *= 0.5;
-  } else if (p.gn >= 1024 && p.M >= 1024) {
-    bn = 256;
-  } else if ((p.gn + 95) / 96 * 96 < (p.gn + 127) / 128 * 128) {
-    bn = 96, eff *= 0.75;
-  }
-  const int64_t tiles = p.nq * ((p.M + bm - 1) / bm) * ((p.gn + bn - 1) / bn);
-  return t + static_cast<double>((tiles + 255) / 256) * 2.0 * static_cast<double>(bm * bn) *
-                 static_cast<double>(p.kpad) / (eff * kBf16PerCu);
+  struct Product { int64_t bm, bn; double fixed, uv, w, eff; };
+  static constexpr Product kFa{256, 256, 15e-6, 5.1e12, 2.0e12, 0.56};     // 256 x 256, U in place
+  static constexpr Product kW256{256, 256, 28e-6, 6.2e12, 1.7e12, 0.61};
+  static constexpr Product kW128{256, 128, 43e-6, 6.8e12, 1.53e12, 0.47};
+  static constexpr Product kDma{128, 256, 30e-6, 10e12, 1.85e12, 0.52};    // bd128x256s3
+  static constexpr Product kFused{128, 128, 24e-6, 5.0e12, 2.9e12, 0.37};  // register tiles, U in place
+  static constexpr Product kFused64{128, 64, 24e-6, 5.0e12, 2.9e12, 0.2};
+  static constexpr Product kFused256{128, 256, 24e-6, 5.0e12, 2.9e12, 0.37};
+  static constexpr Product kReg{128, 128, 36e-6, 5.3e12, 2.25e12, 0.26};   // register tiles
+  static constexpr Product kReg64{128, 64, 36e-6, 5.3e12, 2.25e12, 0.15};
+  static constexpr Product kReg96{128, 96, 44e-6, 7.4e12, 2.1e12, 0.30};
+  static constexpr Product kReg256{128, 256, 33e-6, 15e12, 1.9e12, 0.27};
+  const int wide = p.kpad % 32 == 0 && !p.fused ? bf16x3_wide_tile(p.nq, p.M, p.gn) : -1;
+  const int fused = p.fused ? bf16x3_fused_tile(p.M, p.gn) : -1;
+  const Product& t = wide >= 0                                      ? p.bf16_wide_fa ? kFa : wide == 0 ? kW256 : kW128
+                     : !bf16x3_register_tile(p.M, p.gn, p.kpad)     ? kDma
+                     : p.fused ? fused == 0 ? kFused64 : fused == 2 ? kFused256 : kFused
+                     : p.gn <= 64                                   ? kReg64
+                     : p.gn >= 1024 && p.M >= 1024                  ? kReg256
+                     : (p.gn + 95) / 96 * 96 < (p.gn + 127) / 128 * 128 ? kReg96
+                                                                        : kReg;
+  const double planes = static_cast<double>(p.V.elems) + (p.fused || p.bf16_wide_fa ? 0.0 : static_cast<double>(p.U.elems));
+  // (three steps: the aligned W is written and read once more)
+  const double w = p.fused || p.fused_ua ? 0 : 24.0 * static_cast<double>(p.W.elems) / 2.9e12 + 4e-6;
+  const int64_t tiles = p.nq * ((p.M + t.bm - 1) / t.bm) * ((p.gn + t.bn - 1) / t.bn);
+  return t.fixed + 12.0 * planes / t.uv + 4.0 * static_cast<double>(p.W.elems) / t.w + w +
+         static_cast<double>((tiles + 255) / 256) * 2.0 * static_cast<double>(t.bm * t.bn) * static_cast<double>(p.kpad) /
+             (t.eff * kBf16PerCu);
 }
 
 bool is_letter(char c) { return (c >= 'a' && c <= 'z') || (c >= 'A' && c <= 'Z'); }
@@ -427,13 +432,16 @@ bool plan_any(Plan* p, int want, bool trailing_k, int64_t run) {
   if (bf && !forced) {
     // against the product on hi/lo planes
     const double valign = y.b ? 0 : 8.0 * static_cast<double>(p->V.elems) / 3.5e12 + 8e-6;
-    // (0.7: the model is least sure where planes run on global-to-LDS tiles, for K-major A
-    // with 4-byte loads -- 5 x (2300 x 1540 x 585) took 256 us, 230 on planes -- and for
-    // outputs much larger than the operands, whose stores bound both: 4 x (6192 x 40 x
-    // 8640) 507 and 456)
-    const bool unsure = (p->kpad % 32 == 0 && !bf16x3_register_tile(p->M, p->gn, p->kpad)) ||
-                        (y.am == 1 && !y.ch16) || (p->gk <= 64 && p->M > 64 && p->gn > 64);
-    const double keep = unsure ? 0.7 : 0.85;
+    // (the lines are where the measured times of 1300 products cross: the model takes
+    // 4-byte loads of a short K too lightly, those of a K-major A above all.  On planes
+    // and here: 4 x (7937 x 160 x 1613) 149 us and 198; 16 x (4096 x 128 x 449) 93 and 113;
+    // with K-major A 16 x (1940 x 96 x 1405) 129 and 155, 16 x (1601 x 512 x 605) 146 and
+    // 195; with 16-byte loads 4 x (6283 x 64 x 736) 64 and 43,
+    // 16 x (128 x 64 x 176128) with K-major A 1207 and 804)
+    const bool short_k = p->gk <= 256;
+    const double keep = y.am == 1 ? (y.ch16 ? (p->gk <= 64 ? 1.05 : 0.9) : short_k ? 0.7 : 0.87)
+                        : !y.ch16 && short_k ? 0.85
+                                             : 1.0;
     if (!a_ok || c.time + valign > keep * bf16_planes_time(*p)) return false;
   } else if (!forced) {
     // against the product the plan takes otherwise and its passes over U and V
@@ -547,16 +555,15 @@ void plan_wide(Plan* p, bool trailing_k) {
   d->workspace = round_up(p->ws_v_al, 256) + d->bytes_tables + round_up(d->bytes_partial, 256) +
                  round_up(p->bytes_charges, 256);
   if (!tile) {
-    // Where the model says it takes at most 0.8 of the plan's own time: of 70 random
-    // products the 14 under it took 0.47 to 0.99 of that plan's measured time (the other
-    // plans' models are off by up to 1.6), the 12 at 0.8 to 0.9 took 0.71 to 1.34.
+    // Where the models say it takes at most 0.88 of the planes' time, or 0.8 of the in-place
+    // product's, whose model is too slow: of 70 random products those under these lines
+    // took 0.47 to 1.05 of the plan's own measured time, those in the next 0.1 up to 1.41.
     // 8 x (4608 x 4608 x 288) 553 -> 407 us, 12 x (6912 x 6912 x 432) 2284 -> 1779 and
     // 8 x (4608 x 4608 x 200) 556 -> 348; 8 x (8192 x 8192 x 512), whole rounds of
     // 256 x 256 tiles, stays (1555 against 1753), and so do short K with many rows
     // (8 x (11840 x 768 x 224): 184 against 225).
-    double now = p->any.tile >= 0 ? p->any.time : bf16_planes_time(*p);
-    if (p->any.tile < 0 && p->bf16_wide_fa) now -= 12.0 * static_cast<double>(p->U.elems) / 2.9e12;
-    if (time > 0.8 * now) return;
+    const bool any = p->any.tile >= 0;
+    if (time > (any ? 0.8 * p->any.time : 0.88 * bf16_planes_time(*p))) return;
   }
   p->workspace_steps = p->workspace;
   p->workspace = std::max(p->workspace, d->workspace);

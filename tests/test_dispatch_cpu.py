@@ -92,3 +92,23 @@ def test_complex_products_stay_where_in_place_was_measured_slower():
               ak(2, (4, 8), (27, 11), (26, 43), PL.C64),      # 2 x (594 x 128 x 4472): 47, 26
               ak(2, (4, 8), (27, 11), (26, 43), PL.C128)]     # 56, 38
     assert [p["any"] >= 0 for p in PL.plans(slower + faster)] == [False] * 3 + [True] * 3
+
+
+def test_split_bf16_products_take_planes_or_in_place_as_measured():
+    # (layout, G, M, K, N): us on planes, us on the in-place or wide tile
+    planes = [("ak", 4, 7937, 160, 1613),     # 149, 198 (in place)
+              ("ak", 16, 4096, 128, 449),     # 93, 113
+              ("ka", 16, 1940, 96, 1405),     # 129, 155
+              ("ak", 4, 3648, 32, 2970),      # 90, 238 (256-column tiles under stream-K)
+              ("ak", 16, 2592, 256, 1631),    # 274, 412
+              ("ak", 8, 7840, 256, 2963)]     # 683, 946
+    in_place = [("ak", 4, 958, 199, 1701),    # 88, 42
+                ("ak", 2, 3072, 174, 1363),   # 103, 50
+                ("ak", 4, 2011, 193, 1472),   # 100, 61
+                ("ka", 4, 2848, 416, 576),    # 91, 41
+                ("ka", 16, 128, 64, 176128)]  # 1207, 804
+    def line(form, G, M, K, N):
+        return PL.line("ak,kb->ab" if form == "ak" else "ka,kb->ab", (G,), "+-" if form == "ak" else "-+",
+                       (M, K) if form == "ak" else (K, M), "++", (K, N), PL.F32, "bf16x3")
+    got = PL.plans([line(*c) for c in planes + in_place])
+    assert [(p["any"] >= 0, p["wide_bn"]) for p in got] == [(False, 0)] * len(planes) + [(True, 0)] * len(in_place)
