@@ -1285,11 +1285,11 @@ hipError_t launch_bf16x3_wide_sk(int64_t batch, int M, int N, int K, const void*
 // plane_a / plane_b (split-bf16 only): elements from a hi plane to its lo
 // plane, 0 for the packed layout (batch * m * k, batch * n * k).  il
 // (split-bf16 only): both operands' planes interleaved by 32-deep K-steps, which
-// only the wide tiles read.
+// only the wide tiles read.  long_cols: Plan::long_cols (true for the standalone product).
 int launch_sector_gemm(int compute, int64_t batch, int64_t m, int64_t k, int64_t n, const void* A,
                        const void* B, void* C, hipStream_t stream, std::string* err,
                        const FusedTables* fused, void* part, size_t part_bytes, int64_t plane_a,
-                       int64_t plane_b, bool il) {
+                       int64_t plane_b, bool il, bool long_cols) {
   if (batch == 0 || m == 0 || n == 0) return SYMT_OK;
   if (m > INT32_MAX || n > INT32_MAX || k > INT32_MAX) {
     if (err) *err = "sector product dimension above 2^31-1";
@@ -1375,7 +1375,7 @@ int launch_sector_gemm(int compute, int64_t batch, int64_t m, int64_t k, int64_t
     const bool aligned = (reinterpret_cast<uintptr_t>(A) & 15) == 0 &&
                          (reinterpret_cast<uintptr_t>(B) & 15) == 0 &&
                          (!fused || (fused->vec > 1 && fused->krun == 0));
-    const GemmChoice gc = choose_fp_gemm(batch, M, N, K, f64 ? 8 : 4, aligned, a_kmajor);
+    const GemmChoice gc = choose_fp_gemm(batch, M, N, K, f64 ? 8 : 4, aligned, a_kmajor, long_cols);
     if (gc.tile == kTallKTile) {
       // without room for the partials (the allocation-free entry point may drop
       // them) the 128 x 48 register tile runs instead, one workgroup per tile

@@ -445,8 +445,12 @@ bool plan_any(Plan* p, int want, bool trailing_k, int64_t run) {
     if (!a_ok || c.time + valign > keep * bf16_planes_time(*p)) return false;
   } else if (!forced) {
     // against the product the plan takes otherwise and its passes over U and V
-    const GemmChoice g = choose_fp_gemm(nb, p->M, p->gn, p->gk, elem, true, p->a_trans);
+    const GemmChoice g = choose_fp_gemm(nb, p->M, p->gn, p->gk, elem, true, p->a_trans, p->long_cols);
     if (!a_ok || g.tile == kRowsTile || g.tile == kTallKTile) return false;
+    // (many columns of few rows: a workgroup per 64 columns that multiplies padding --
+    // 6 x (7 x 16 x 5340600) complex f32 2916 us against 4493, 3 x (3 x 6 x 2122416) f64
+    // 647 against 684)
+    if (p->cplx && p->M <= 16 && nb * p->gn >= (int64_t(1) << 20)) return false;
     // an aligned form is read and written once, complex rows of V once more
     const double rate = p->cplx ? 1.3e12 : 3.5e12;
     double other = g.time;
@@ -475,8 +479,9 @@ bool plan_any(Plan* p, int want, bool trailing_k, int64_t run) {
     const int64_t own =
         c.sk ? longest_share(nb, p->M, p->gn, p->gk, ksteps, t.bm, t.bn, y.ch16 ? t.wgs : t.wgs4) : p->gk;
     for (bool aligned : {true, false})
-      y.chunk = y.chunk || own > longest_sum(choose_fp_gemm(nb, p->M, p->gn, p->gk, elem, aligned, p->a_trans && aligned), nb,
-                                             p->M, p->gn, p->gk, elem);
+      y.chunk = y.chunk || own > longest_sum(choose_fp_gemm(nb, p->M, p->gn, p->gk, elem, aligned, p->a_trans && aligned,
+                                                            p->long_cols),
+                                             nb, p->M, p->gn, p->gk, elem);
   }
   y.tile = c.tile;
   y.sk = c.sk;
@@ -901,6 +906,30 @@ int plan_contraction(const char* einsum, const symt_group* group, const symt_ten
                      (p->U.dtype == SYMT_F64 || p->U.dtype == SYMT_F32) &&
                      (!w || p->W.dtype == SYMT_F64 || p->W.dtype == SYMT_F32) &&
                      run % 32 == 0 && bf16x3_register_tile(p->M, p->gn, p->gk);
+  // W's aligned columns: the contiguous run of its output modes from V (the
+  // split-bf16 epilogue only pays off where its column stores coalesce; with
+  // W's columns transposed, the W transform's LDS-tiled transpose is cheaper)
+  int64_t w_run = 1;
+  {
+    int64_t st[kMaxOrder];
+    int64_t a = 1;
+    for (int m = p->W.n - 1; m >= 0; --m) { st[m] = a; a *= p->W.dims[m]; }
+    for (int i = p->t - 1; i >= 0 && st[p->posJ_w[i]] == w_run; --i) w_run *= p->W.dims[p->posJ_w[i]];
+    int64_t r_run = 1;
+    for (int i = p->s - 1; i >= 0 && st[p->posI_w[i]] == r_run; --i) r_run *= p->W.dims[p->posI_w[i]];
+    p->w_col_run = w_run;
+    p->w_row_run = r_run;
+    a = 1;
+    for (int m = p->V.n - 1; m >= 0; --m) { st[m] = a; a *= p->V.dims[m]; }
+    for (int i = p->t - 1; i >= 0 && st[p->posJ_v[i]] == p->v_col_run; --i) p->v_col_run *= p->V.dims[p->posJ_v[i]];
+  }
+  // rows of the row-streaming product along N (rows_swapped): real operands whose W has its
+  // columns or its rows contiguous; elsewhere its lanes scatter W and V's pairs.  On tiles
+  // and there: 8 x (63 x 63 x 194112) f32 with neither contiguous 969 us and 1441,
+  // 4 x (47 x 52 x 415710) complex 448 and 700, 3 x (53 x 44 x 157080) complex f64 302 and
+  // 340; W's rows contiguous 6 x (29 x 55 x 381895) f64 786 and 354, but f32 with both M
+  // and K large spends its registers: 4 x (51 x 57 x 168664) 154 and 193
+  p->long_cols = !p->cplx && (p->w_col_run >= 16 || (p->w_row_run > 1 && (ea == 8 || p->M <= 48 || p->gk <= 32)));
   // K runs that do not hold whole K-steps: where the product runs on register
   // tiles anyway, they step each run on their own (masking its last step), so A
   // is still read in place (and V, with one-element loads); global-to-LDS shapes
@@ -908,7 +937,7 @@ int plan_contraction(const char* einsum, const symt_group* group, const symt_ten
   const bool stepped = !whole_aligned && compute != SYMT_COMPUTE_BF16X3 && !p->cplx && p->U.dtype == want &&
                        (!w || p->W.dtype == want) && p->nK <= INT32_MAX && p->nK > 0 &&
                        p->gk % p->nK == 0 &&
-                       !choose_fp_gemm(nb, p->M, p->gn, p->gk, static_cast<int>(ea), true).dma;
+                       !choose_fp_gemm(nb, p->M, p->gn, p->gk, static_cast<int>(ea), true, false, p->long_cols).dma;
   // U's contracted modes are not its last ones: A is loaded K-major straight from U
   // (row k of a K-step at its own column-table entry, M chunks along U's other
   // modes), as B is from V: on register tiles, and on the 128-row global-to-LDS
@@ -927,8 +956,8 @@ int plan_contraction(const char* einsum, const symt_group* group, const symt_ten
   // (where the model's global-to-LDS tile is a 96-row one, which cannot read
   // K-major A, a 128-row one replaces it only for a U large enough that aligning
   // it would cost more than the other tile: 64 MiB; else U is aligned first)
-  const GemmChoice g_any = choose_fp_gemm(nb, p->M, p->gn, p->gk, static_cast<int>(ea), true);
-  const GemmChoice g_at = choose_fp_gemm(nb, p->M, p->gn, p->gk, static_cast<int>(ea), true, true);
+  const GemmChoice g_any = choose_fp_gemm(nb, p->M, p->gn, p->gk, static_cast<int>(ea), true, false, p->long_cols);
+  const GemmChoice g_at = choose_fp_gemm(nb, p->M, p->gn, p->gk, static_cast<int>(ea), true, true, p->long_cols);
   const bool at_dma = g_at.dma && a_chunks &&
                       (g_at.tile == g_any.tile || static_cast<double>(ea) * p->U.elems >= 64.0 * (1 << 20));
   const bool at_ok = !trailing_k && compute != SYMT_COMPUTE_BF16X3 && p->U.dtype == want &&
@@ -946,23 +975,6 @@ int plan_contraction(const char* einsum, const symt_group* group, const symt_ten
   // (split-bf16: U and V go to hi/lo planes as in three steps, and the product
   // writes its binary64 sums straight into W)
   const int w_want = compute == SYMT_COMPUTE_F32 ? SYMT_F32 : SYMT_F64;
-  // W's aligned columns: the contiguous run of its output modes from V (the
-  // split-bf16 epilogue only pays off where its column stores coalesce; with
-  // W's columns transposed, the W transform's LDS-tiled transpose is cheaper)
-  int64_t w_run = 1;
-  {
-    int64_t st[kMaxOrder];
-    int64_t a = 1;
-    for (int m = p->W.n - 1; m >= 0; --m) { st[m] = a; a *= p->W.dims[m]; }
-    for (int i = p->t - 1; i >= 0 && st[p->posJ_w[i]] == w_run; --i) w_run *= p->W.dims[p->posJ_w[i]];
-    int64_t r_run = 1;
-    for (int i = p->s - 1; i >= 0 && st[p->posI_w[i]] == r_run; --i) r_run *= p->W.dims[p->posI_w[i]];
-    p->w_col_run = w_run;
-    p->w_row_run = r_run;
-    a = 1;
-    for (int m = p->V.n - 1; m >= 0; --m) { st[m] = a; a *= p->V.dims[m]; }
-    for (int i = p->t - 1; i >= 0 && st[p->posJ_v[i]] == p->v_col_run; --i) p->v_col_run *= p->V.dims[p->posJ_v[i]];
-  }
   p->fused_ua = !p->fused && !force_steps && whole &&
                 (!w || p->W.dtype == (p->cplx ? want : w_want) ||
                  (compute == SYMT_COMPUTE_BF16X3 && p->W.dtype == SYMT_F32)) &&
@@ -1036,7 +1048,7 @@ int plan_contraction(const char* einsum, const symt_group* group, const symt_ten
   // Room for stream-K pieces when the model would pick it on 16-byte aligned operands.
   if (compute != SYMT_COMPUTE_BF16X3 && p->nq > 0 && p->M > 0 && p->gn > 0 && p->gk > 0) {
     const GemmChoice gc = choose_fp_gemm(p->nq, p->M, p->gn, p->gk,
-                                         compute == SYMT_COMPUTE_F64 ? 8 : 4, true, p->a_trans);
+                                         compute == SYMT_COMPUTE_F64 ? 8 : 4, true, p->a_trans, p->long_cols);
     p->bytes_partial = p->any.tile >= 0 ? p->any.partial_bytes : gc.partial_bytes;
     p->workspace += round_up(p->bytes_partial, 256);
   } else if (p->any.tile >= 0) {
@@ -1163,7 +1175,7 @@ const char* forced_tile(bool bf) {
 // fills (~1.5 us each), and one more launch (~5 us).
 namespace {
 GemmChoice choose_among(int64_t batch, int64_t M, int64_t N, int64_t K, int elem, bool aligned,
-                        const char* forced, int sk_mode, bool a_kmajor) {
+                        const char* forced, int sk_mode, bool a_kmajor, bool long_cols) {
   auto usable = [&](const FpTile& t) {
     if (!t.dma) return true;
     return aligned && K % (128 / elem) == 0 && N % (16 / elem) == 0 && (t.bn * elem / 16) % 16 == 0 &&
@@ -1203,7 +1215,7 @@ GemmChoice choose_among(int64_t batch, int64_t M, int64_t N, int64_t K, int elem
   // 14.3 us on register tiles, 15.3 here; at 4 x (57 x 57 x 16640) 18.1 and 16.8).
   const int64_t rows_min = elem == 4 && K > 32 ? 49152 : 16384;
   if (K >= 1 && K <= 64 && rows_swapped(M, N) && M >= 1 && batch >= 1 && batch <= 65535 &&
-      (rows_forced || (!forced && batch * N >= rows_min))) {
+      (rows_forced || (!forced && long_cols && batch * N >= rows_min))) {
     best.tile = kRowsTile;
     best.bm = static_cast<int>(M);
     best.bn = 32;
@@ -1281,12 +1293,12 @@ bool tallk_groups(const Plan& p) {
 // not apply); SYMT_GEMM_SK=0 forbids stream-K and split K, 1 forces stream-K on
 // the DMA tiles.
 GemmChoice choose_fp_gemm(int64_t batch, int64_t M, int64_t N, int64_t K, int elem, bool aligned,
-                          bool a_kmajor) {
+                          bool a_kmajor, bool long_cols) {
   const char* forced = tuned(kTuneTile);
   const char* sk_env = tuned(kTuneSk);
   const int sk_mode = sk_env ? std::atoi(sk_env) : -1;
-  GemmChoice g = choose_among(batch, M, N, K, elem, aligned, forced, sk_mode, a_kmajor);
-  if (g.tile < 0) g = choose_among(batch, M, N, K, elem, aligned, nullptr, sk_mode, a_kmajor);
+  GemmChoice g = choose_among(batch, M, N, K, elem, aligned, forced, sk_mode, a_kmajor, long_cols);
+  if (g.tile < 0) g = choose_among(batch, M, N, K, elem, aligned, nullptr, sk_mode, a_kmajor, long_cols);
   return g;
 }
 

@@ -266,6 +266,7 @@ struct Plan {
   // product) and of those from U (rows); one of them is 1
   int64_t w_col_run = 1, w_row_run = 1;
   int64_t v_col_run = 1;            // V's contiguous run of its output modes
+  bool long_cols = false;           // columns in long runs: rows_swapped products may run
   int64_t u_k_run = 1;              // U's contiguous run of its contracted index (in elements)
   // fused with K runs that do not hold whole K-steps: the register tiles step each
   // run on its own (krun = the run length; 0 = plain K-steps)
@@ -368,8 +369,9 @@ bool tallk_groups(const Plan& p);
 // Fewest K-iterations a stream-K workgroup takes on (bounds the pieces per tile).
 constexpr int kSkMinIters = 4;
 // a_kmajor: A is read K-major from U (global-to-LDS tiles of 128 rows only).
+// long_cols: Plan::long_cols, true for aligned operands.
 GemmChoice choose_fp_gemm(int64_t batch, int64_t M, int64_t N, int64_t K, int elem, bool aligned,
-                          bool a_kmajor = false);
+                          bool a_kmajor = false, bool long_cols = true);
 // Split-bf16 product: whether the launcher runs register-staged tiles on this
 // shape (else global-to-LDS ones), and which of the fused product's three
 // register tiles it takes (0: 128 x 64, 1: 128 x 128, 2: 128 x 256, 3: 128 x 96).

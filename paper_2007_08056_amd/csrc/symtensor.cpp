@@ -23,7 +23,8 @@ int launch_xform(const XformParams& p, bool in_f64, int out, const void* src, vo
 int launch_sector_gemm(int compute, int64_t batch, int64_t m, int64_t k, int64_t n, const void* A,
                        const void* B, void* C, hipStream_t stream, std::string* err,
                        const FusedTables* fused = nullptr, void* part = nullptr,
-                       size_t part_bytes = 0, int64_t plane_a = 0, int64_t plane_b = 0, bool il = false);
+                       size_t part_bytes = 0, int64_t plane_a = 0, int64_t plane_b = 0, bool il = false,
+                       bool long_cols = true);
 int launch_offsets(const OffsetBatch& batch, hipStream_t stream, std::string* err);
 int launch_put_i32(int32_t* dst, const int32_t* src, int64_t n, hipStream_t stream, std::string* err);
 int launch_zero(void* ptr, size_t bytes, hipStream_t stream, std::string* err);
@@ -221,11 +222,11 @@ int clear_k_pad(symt_ctx* ctx, const Plan& p, void* ual, void* val, hipStream_t 
 int do_gemm(symt_ctx* ctx, int compute, int64_t batch, int64_t m, int64_t k, int64_t n,
             const void* a, const void* b, void* c, hipStream_t s,
             const symt::FusedTables* fused = nullptr, void* part = nullptr, size_t part_bytes = 0,
-            int64_t plane_a = 0, int64_t plane_b = 0, bool il = false) {
+            int64_t plane_a = 0, int64_t plane_b = 0, bool il = false, bool long_cols = true) {
   std::string err;
   const int rc = timed(ctx, 2, s, [&] {
     return symt::launch_sector_gemm(compute, batch, m, k, n, a, b, c, s, &err, fused, part, part_bytes,
-                                    plane_a, plane_b, il);
+                                    plane_a, plane_b, il, long_cols);
   });
   return rc ? ctx_fail(ctx, rc, err) : SYMT_OK;
 }
@@ -418,7 +419,7 @@ int do_fused(symt_ctx* ctx, const Plan& p, char* base, hipStream_t s, const int3
                  ua && !wide_fa ? ual : p.U.data,
                  fb ? p.V.data : val,
                  p.W.data, s, &f,
-                 p.bytes_partial ? part : nullptr, p.bytes_partial, 0, 0, p.bf16_il);
+                 p.bytes_partial ? part : nullptr, p.bytes_partial, 0, 0, p.bf16_il, p.long_cols);
 }
 
 // Cache key of a planning request: the einsum, group, compute mode, every
@@ -669,7 +670,7 @@ int contract_planned(symt_ctx* ctx, const Plan& p, void* workspace, size_t works
   f.wide_bn = p.wide_bn;
   if (p.nq > 0 && (rc = do_gemm(ctx, p.compute, p.nq, p.M, any ? p.gk : p.kpad, p.gn, ual, val, wal, s,
                                 any || p.wide_bn ? &f : nullptr,
-                                p.bytes_partial ? part : nullptr, p.bytes_partial, 0, 0, p.bf16_il)))
+                                p.bytes_partial ? part : nullptr, p.bytes_partial, 0, 0, p.bf16_il, p.long_cols)))
     return rc;
   if ((rc = do_unalign(ctx, p, wal, s, true, chg[2]))) return rc;
   return SYMT_OK;

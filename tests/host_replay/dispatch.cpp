@@ -65,7 +65,7 @@ int main() {
     const Plan& d = p.direct ? *p.direct : p;
     const GemmChoice c = p.compute == SYMT_COMPUTE_BF16X3
                              ? GemmChoice{}
-                             : choose_fp_gemm(d.nq, d.M, d.gn, d.gk, p.compute == SYMT_COMPUTE_F64 ? 8 : 4, true, d.a_trans);
+                             : choose_fp_gemm(d.nq, d.M, d.gn, d.gk, p.compute == SYMT_COMPUTE_F64 ? 8 : 4, true, d.a_trans, d.long_cols);
     std::printf("fused=%d fused_ua=%d any=%d am=%d ch16=%d sk=%d chunk=%d cb=%d any_direct=%d direct=%d slices=%d wide_bn=%d "
                 "tile=%d splits=%d tile_sk=%d workspace=%zu partial=%zu nq=%lld m=%lld k=%lld n=%lld\n",
                 p.fused, p.fused_ua, d.any.tile, d.any.am, d.any.ch16, d.any.sk, d.any.chunk, d.any.cb, d.any_direct, p.direct != nullptr,

@@ -112,3 +112,29 @@ def test_split_bf16_products_take_planes_or_in_place_as_measured():
                        (M, K) if form == "ak" else (K, M), "++", (K, N), PL.F32, "bf16x3")
     got = PL.plans([line(*c) for c in planes + in_place])
     assert [(p["any"] >= 0, p["wide_bn"]) for p in got] == [(False, 0)] * len(planes) + [(True, 0)] * len(in_place)
+
+
+ROWS = 64     # GemmChoice::tile of the row-streaming product
+
+
+def test_rows_along_n_where_w_is_contiguous():
+    def line(sub, su, sv, G, d, dt):
+        tu, tv = sub.split("->")[0].split(",")
+        return PL.line(sub, (G,), su, [d[c] for c in tu], sv, [d[c] for c in tv], dt, "f64" if dt in (PL.F64, PL.C128) else "f32")
+    # (us on tiles, us on rows)
+    rows = [line("ak,kb->ab", "+-", "++", 4, dict(a=32, k=32, b=524288), PL.F32),           # 255, 111
+            line("ka,bk->ba", "-+", "++", 6, dict(a=29, k=55, b=381895), PL.F64),           # 786, 354
+            line("ak,kb->ba", "+-", "++", 1, dict(a=23, k=7, b=361591), PL.F32)]            # 42, 18
+    tiles = [line("ka,ijk->jai", "-+", "+++", 8, dict(a=63, k=63, i=337, j=72), PL.F32),    # 969, 1441
+             line("ka,ijk->jai", "-+", "+++", 6, dict(a=32, k=33, i=172, j=45), PL.F64),    # 94, 121
+             line("ak,kb->ba", "+-", "++", 4, dict(a=51, k=57, b=168664), PL.F32),          # 154, 193
+             line("ak,kb->ab", "+-", "++", 4, dict(a=47, k=26, b=207855), PL.C64),          # 448, 700
+             line("ak,kb->ab", "+-", "++", 6, dict(a=62, k=16, b=389338), PL.C128)]         # 1691, 1897
+    got = PL.plans(rows + tiles)
+    assert [p["tile"] == ROWS for p in got] == [True] * len(rows) + [False] * len(tiles)
+    # the three steps take the same product
+    steps = PL.plans([ln.rsplit(" ", 1)[0] + " " + str(int(ln.rsplit(" ", 1)[1]) | PL.STEPS) for ln in rows + tiles])
+    assert [p["tile"] for p in steps] == [p["tile"] for p in got]
+    # (many columns of few rows stay off the in-place tiles as well: 2916 us, 4493)
+    few, = PL.plans([line("ak,ijkl->aijl", "+-", "++++", 6, dict(a=7, k=8, i=25, j=129, l=23), PL.C64)])
+    assert few["tile"] != ROWS and few["any"] < 0
