@@ -138,3 +138,43 @@ def test_rows_along_n_where_w_is_contiguous():
     # (many columns of few rows stay off the in-place tiles as well: 2916 us, 4493)
     few, = PL.plans([line("ak,ijkl->aijl", "+-", "++++", 6, dict(a=7, k=8, i=25, j=129, l=23), PL.C64)])
     assert few["tile"] != ROWS and few["any"] < 0
+
+
+TALLK = 65    # GemmChoice::tile of the long-K product
+
+
+def test_the_gpu_tests_reach_their_kernels():
+    """Forced names that do not apply are ignored, and the GPU tests of a kernel then pass on
+    another: the planner takes each of their cases as they mean it."""
+    from tests import test_gpu_any as any_layout
+    from tests import test_gpu_rows_swapped as rows
+    from tests import test_gpu_subgroup_direct as subgroup
+    from tests import test_gpu_tallk_vec as tallk
+    from tests import test_gpu_wide_sk as wide
+    real, every = ((PL.F64, "f64"), (PL.F32, "f32")), ((PL.F64, "f64"), (PL.F32, "f32"), (PL.C128, "f64"), (PL.C64, "f32"))
+
+    def lines(cases, dt, comp):
+        return [PL.line(sub, g, cu, du, cv, dv, dt, comp) for sub, g, cu, cv, du, dv in cases]
+    for sk in ("0", "1"):
+        layouts = set()
+        for i, tile in enumerate(("a96x96s2", "a128x64s2", "a64x64s2")):
+            for dt, comp in every:
+                got = PL.plans(lines(any_layout.CASES, dt, comp), SYMT_GEMM_TILE=tile, SYMT_GEMM_SK=sk)
+                # (without whole 16-byte chunks the first tile's launch runs the second)
+                assert [p["any"] for p in got] == [i if p["ch16"] else max(i, 1) for p in got], (tile, dt, sk)
+                layouts |= {(p["am"], p["cb"], p["ch16"]) for p in got}
+        assert layouts >= {(0, 0, 0), (0, 0, 1), (1, 0, 0), (1, 0, 1), (0, 1, 1), (2, 1, 0), (2, 1, 1)}
+        for i, tile in enumerate(("a128x128s2", "a128x64s2", "a64x64s2")):
+            got = PL.plans(lines(any_layout.CASES, PL.F32, "bf16x3"), SYMT_GEMM_TILE=tile, SYMT_GEMM_SK=sk)
+            assert [p["any"] for p in got] == [i if p["ch16"] else max(i, 1) for p in got], (tile, sk)
+            assert all(p["sk"] == int(sk) for p in got)
+    for bn in (192, 224, 256, 288):
+        got = PL.plans(lines(wide.CASES, PL.F32, "bf16x3"), SYMT_GEMM_TILE=f"bw256x{bn}sk")
+        assert [p["wide_bn"] for p in got] == [bn] * len(got)
+    for dt, comp in every + ((PL.F32, "bf16x3"),):
+        got = PL.plans([PL.line(sub, (G,), cu, du, cv, dv, dt, comp, cv=2, hu=hu, hv=hv)
+                        for sub, G, cu, cv, du, dv, hu, hv in subgroup.CASES])
+        assert all(p["direct"] and p["slices"] for p in got), (dt, comp)
+    for dt, comp in real:
+        assert all(p["tile"] == ROWS for p in PL.plans(lines(rows.CASES, dt, comp), SYMT_GEMM_TILE="rows"))
+        assert all(p["tile"] == TALLK for p in PL.plans(lines(tallk.CASES, dt, comp), SYMT_GEMM_TILE="tallk"))
