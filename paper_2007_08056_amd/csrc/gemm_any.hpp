@@ -79,7 +79,7 @@ constexpr int kAnyChunk = 4;
 
 // AM, CB: the tile's layouts (any_index.hpp).  Null tables stand for the aligned
 // row-major forms (the three-step path, so that it sums in the same order).
-template <typename T, int BM, int BN, int WM, int WN, int S, int CH, int AM, bool CB>
+template <typename T, int BM, int BN, int WM, int WN, int CH, int AM, bool CB>
 struct AnyTile {
   static constexpr int ES = static_cast<int>(sizeof(T));
   static constexpr int NW = WM * WN, NT = 64 * NW;
@@ -92,10 +92,8 @@ struct AnyTile {
   static constexpr int B_BYTES = (CB ? BK / 2 : BK) * B_ROW;
   static constexpr int STAGE = A_BYTES + B_BYTES;
   static constexpr int A_LOADS = (A_BYTES / CH + NT - 1) / NT, B_LOADS = (B_BYTES / CH + NT - 1) / NT;
-  static constexpr bool WHOLE = A_BYTES % (CH * NT) == 0 && B_BYTES % (CH * NT) == 0;
   static_assert(A_BYTES % (64 * CH) == 0 && B_BYTES % (64 * CH) == 0, "loads must fill whole waves");
   static_assert(TM * WM * 16 == BM && TN * WN * 16 == BN, "tile shape");
-  static_assert(S == 2 || (WHOLE && (S - 2) * (A_LOADS + B_LOADS) < 64), "every wave counts the same loads");
   using Acc = typename Mfma<T>::Acc;
 };
 
@@ -122,13 +120,13 @@ constexpr int any_rows_per_load() {
   return (ROW - g + 64 * CH - 1) / ROW + 1;
 }
 
-template <typename T, int BM, int BN, int WM, int WN, int S, int CH, int AM, bool CB, bool BF, bool CK>
+template <typename T, int BM, int BN, int WM, int WN, int CH, int AM, bool CB, bool BF, bool CK>
 __device__ __forceinline__ void any_tile_accumulate(
     const T* __restrict__ A, const T* __restrict__ B, int M, int N, const AnySteps& st, int64_t q, int m0, int n0,
     int kt0, int kt1, const int64_t* __restrict__ ra, const int64_t* __restrict__ ca,
     const int64_t* __restrict__ rb, const int64_t* __restrict__ cb, int64_t ldb, char* smem,
     AnyAcc<T, BM / WM / 16, BN / WN / 16, BF>& acc) {
-  using D = AnyTile<T, BM, BN, WM, WN, S, CH, AM, CB>;
+  using D = AnyTile<T, BM, BN, WM, WN, CH, AM, CB>;
   constexpr int ES = D::ES, NT = D::NT, NW = D::NW, BK = D::BK, TM = D::TM, TN = D::TN;
   constexpr int A_LOADS = D::A_LOADS, B_LOADS = D::B_LOADS, STAGE = D::STAGE, A_BYTES = D::A_BYTES;
   constexpr int A_ROW = D::A_ROW;
@@ -233,17 +231,17 @@ __device__ __forceinline__ void any_tile_accumulate(
 #pragma unroll
       for (int j = 0; j < TN; ++j) sum[i][j] = typename D::Acc{};
   }
-  if (nk > 0) fetch(kt0);
-#pragma unroll
-  for (int s = 0; s < S - 1; ++s)
-    if (s < nk) issue(kt0 + s, s);
+  if (nk > 0) {
+    fetch(kt0);
+    issue(kt0, 0);
+  }
   for (int it = 0; it < nk; ++it) {
-    // step it has landed once at most (S-2) later steps' loads are outstanding
-    if (it + S - 2 < nk) wait_vmcnt<(S - 2) * (A_LOADS + B_LOADS)>();
-    else wait_vmcnt<0>();
+    // this wave's loads of step it have landed; past the barrier every wave's have, and
+    // every wave is done with the other stage
+    wait_vmcnt<0>();
     asm volatile("s_barrier" ::: "memory");
-    if (it + S - 1 < nk) issue(kt0 + it + S - 1, (it + S - 1) % S);
-    const char* As = smem + (it % S) * STAGE;
+    if (it + 1 < nk) issue(kt0 + it + 1, (it + 1) % 2);
+    const char* As = smem + (it % 2) * STAGE;
     const char* Bs = As + A_BYTES;
     if constexpr (BF) {
       const int g = lane >> 4;
@@ -374,7 +372,7 @@ __device__ __forceinline__ void store_any_piece(double* __restrict__ piece, cons
 
 // One workgroup per tile (ts = 0, XCD-aware order), or stream-K (ts > 0:
 // persistent workgroups, pieces of cut tiles to `part` for k_sk_fixup).
-template <typename T, int BM, int BN, int WM, int WN, int S, int CH, int AM, bool CB, bool BF = false,
+template <typename T, int BM, int BN, int WM, int WN, int CH, int AM, bool CB, bool BF = false,
           typename TC = T, bool CK = false>
 __global__ __launch_bounds__(64 * WM * WN, (kAnyWavesPerSimd<BM, BN, CH, BF>)) void k_gemm_any(
     const T* __restrict__ A, const T* __restrict__ B, TC* __restrict__ C, int M, int N, AnySteps st, int tiles_m,
@@ -382,9 +380,9 @@ __global__ __launch_bounds__(64 * WM * WN, (kAnyWavesPerSimd<BM, BN, CH, BF>)) v
     const int64_t* __restrict__ rc, const int64_t* __restrict__ cc, const int64_t* __restrict__ rb,
     const int64_t* __restrict__ cb, int64_t ldb,
     typename std::conditional<BF, double, T>::type* __restrict__ part, int ts, int c_rows4) {
-  using D = AnyTile<T, BM, BN, WM, WN, S, CH, AM, CB>;
+  using D = AnyTile<T, BM, BN, WM, WN, CH, AM, CB>;
   constexpr int TM = D::TM, TN = D::TN;
-  __shared__ __attribute__((aligned(1024))) char smem[S * D::STAGE];
+  __shared__ __attribute__((aligned(1024))) char smem[2 * D::STAGE];
   AnyAcc<T, TM, TN, BF> acc;
   SkSlot sl{0, 0, 1};
   int64_t it = 0, end = st.nk, first = 0, tile = 0;
@@ -420,7 +418,7 @@ __global__ __launch_bounds__(64 * WM * WN, (kAnyWavesPerSimd<BM, BN, CH, BF>)) v
         acc.v[i][j] = typename D::Acc{};
         if constexpr (BF) acc.x[i][j] = typename D::Acc{};
       }
-    any_tile_accumulate<T, BM, BN, WM, WN, S, CH, AM, CB, BF, CK>(A, B, M, N, st, q, tm * BM, tn * BN, kt0, kt1, ra,
+    any_tile_accumulate<T, BM, BN, WM, WN, CH, AM, CB, BF, CK>(A, B, M, N, st, q, tm * BM, tn * BN, kt0, kt1, ra,
                                                                   ca, rb, cb, ldb, smem, acc);
     if (kt0 == 0 && kt1 == st.nk) {
       // W's table entries all requested before the first store
@@ -440,7 +438,7 @@ __global__ __launch_bounds__(64 * WM * WN, (kAnyWavesPerSimd<BM, BN, CH, BF>)) v
   }
 }
 
-template <typename T, int BM, int BN, int WM, int WN, int S, int CH, int AM, bool CB, bool BF = false,
+template <typename T, int BM, int BN, int WM, int WN, int CH, int AM, bool CB, bool BF = false,
           typename TC = T, bool CK = false>
 hipError_t launch_any_kernel(int64_t batch, int M, int N, const AnySteps& st, const void* A, const void* B, void* C,
                              hipStream_t s, const FusedTables* f, void* part, size_t part_bytes, bool sk) {
@@ -453,7 +451,7 @@ hipError_t launch_any_kernel(int64_t batch, int M, int N, const AnySteps& st, co
   TC* c = static_cast<TC*>(C);
   TP* pt = static_cast<TP*>(part);
   const int rows4 = f->c_rows4 && (reinterpret_cast<uintptr_t>(c) & 15) == 0 ? 1 : 0;
-  auto kern = k_gemm_any<T, BM, BN, WM, WN, S, CH, AM, CB, BF, TC, CK>;
+  auto kern = k_gemm_any<T, BM, BN, WM, WN, CH, AM, CB, BF, TC, CK>;
   int P = 0, ts = 0;
   if (sk && part) {
     // (as many per CU as every layout of this tile and load width admits: the in-place
@@ -486,12 +484,12 @@ hipError_t launch_any_tile(const AnyLaunch& l, int64_t batch, int M, int N, cons
                            const void* B, void* C, hipStream_t s, const FusedTables* f, void* part, size_t part_bytes) {
   if constexpr (CH == 16)
     if (l.tile == 0)
-      return launch_any_kernel<T, 96, 96, 2, 2, 2, CH, AM, CB, false, T, CK>(batch, M, N, st, A, B, C, s, f, part,
+      return launch_any_kernel<T, 96, 96, 2, 2, CH, AM, CB, false, T, CK>(batch, M, N, st, A, B, C, s, f, part,
                                                                            part_bytes, l.sk);
   if (l.tile <= 1)
-    return launch_any_kernel<T, 128, 64, 2, 2, 2, CH, AM, CB, false, T, CK>(batch, M, N, st, A, B, C, s, f, part,
+    return launch_any_kernel<T, 128, 64, 2, 2, CH, AM, CB, false, T, CK>(batch, M, N, st, A, B, C, s, f, part,
                                                                           part_bytes, l.sk);
-  return launch_any_kernel<T, 64, 64, 2, 2, 2, CH, AM, CB, false, T, CK>(batch, M, N, st, A, B, C, s, f, part,
+  return launch_any_kernel<T, 64, 64, 2, 2, CH, AM, CB, false, T, CK>(batch, M, N, st, A, B, C, s, f, part,
                                                                        part_bytes, l.sk);
 }
 

@@ -10,12 +10,12 @@ hipError_t launch_tile(int tile, int64_t batch, int M, int N, const AnySteps& st
   // (128 x 128 with 4-byte loads: their sources and two accumulators exceed the registers)
   if constexpr (CH == 16)
     if (tile == 0)
-      return launch_any_kernel<float, 128, 128, 2, 2, 2, CH, AM, false, true, TC>(batch, M, N, st, A, B, C, s, f, part,
+      return launch_any_kernel<float, 128, 128, 2, 2, CH, AM, false, true, TC>(batch, M, N, st, A, B, C, s, f, part,
                                                                                 part_bytes, sk);
   if (tile <= 1)
-    return launch_any_kernel<float, 128, 64, 2, 2, 2, CH, AM, false, true, TC>(batch, M, N, st, A, B, C, s, f, part,
+    return launch_any_kernel<float, 128, 64, 2, 2, CH, AM, false, true, TC>(batch, M, N, st, A, B, C, s, f, part,
                                                                              part_bytes, sk);
-  return launch_any_kernel<float, 64, 64, 2, 2, 2, CH, AM, false, true, TC>(batch, M, N, st, A, B, C, s, f, part,
+  return launch_any_kernel<float, 64, 64, 2, 2, CH, AM, false, true, TC>(batch, M, N, st, A, B, C, s, f, part,
                                                                           part_bytes, sk);
 }
 
