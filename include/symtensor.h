@@ -54,7 +54,8 @@
  *                       W_al f64 (|G|,M,N).
  *   hi = bf16(x), lo = bf16(x - hi), x taken in binary32, both rounded to
  *   nearest even; the product is hi*hi + hi*lo + lo*hi with binary32
- *   accumulation (two accumulators) and a binary64 sum of the two at the end.
+ *   accumulation and a binary64 sum at the end (an accumulator for hi*hi and one
+ *   for the cross terms; the wide tiles that hold whole tiles add all three in one).
  *
  * COMPLEX OPERANDS (Sec. 2.2 allows tensors over C).  u, v and w are all
  * complex (SYMT_C128 / SYMT_C64) or all real, else SYMT_EDTYPE; any compute
@@ -132,8 +133,9 @@
  * contracted modes are its last ones, in runs of 4 or more elements per block,
  * 16-byte aligned, is read in place by the 256 x 256 tile and split in
  * registers (same bits as its planes).  Such a u also runs on 256-row tiles of 192
- * to 288 columns under stream-K where those fit N and the time model prefers them
- * (info stays that of the product they replace; the three-step path then multiplies
+ * to 288 columns (two workgroups of half the columns each) under stream-K where those
+ * fit N and the time model prefers them, with two accumulators and the cut tiles' sums
+ * in binary64 (info stays that of the product they replace; the three-step path then multiplies
  * on the same tiles; a u that is not 16-byte aligned takes the replaced product).  F64 and F32 products that would
  * otherwise align an operand, expand a complex v, or run on register-staged
  * tiles take a product that reads u and v in place in any layout and at any
@@ -275,7 +277,7 @@ typedef struct {
  * mode needs the same count in u and v, w's counts must be the derived ones
  * (u's on I modes, v's on J modes) -- else SYMT_ESYM; a count that does not
  * divide |G| is SYMT_EINVAL.  Counts below |G| need a cyclic group and no
- * charge tables (SYMT_EUNSUPPORTED), and disable the fused product. */
+ * charge tables (SYMT_EUNSUPPORTED); see FUSED PRODUCT for their products. */
 typedef struct {
   int32_t nmodes;
   const char* signs;
@@ -301,7 +303,9 @@ typedef struct {
   char w_signs[SYMT_MAX_ORDER + 1];/* derived output sign string (tw order), NUL-terminated */
   int32_t w_charge;                /* derived output charge */
   int32_t fused;                   /* 1 if symtensor_contract's product reads u in place (and
-                                      writes w in place): see FUSED PRODUCT */
+                                      writes w in place): see FUSED PRODUCT (where a plan
+                                      replaces its product, these three fields stay those
+                                      of the product it replaces) */
   int32_t fused_v;                 /* 1 if the product also reads v in place (no V_al), given
                                       16-byte aligned v data */
   int32_t fused_w;                 /* 1 if the product writes w in place (fused = 1, or u

@@ -21,12 +21,12 @@
 // and the odd real rows (-im, re) are formed as fragments are read; A is read as
 // interleaved reals (its contracted modes last) or K-major as pairs.
 //
-// Measured (before -> after): the complex bond-64 environment chain 648 -> 245 us
-// (its align passes alone took 392); 9 x (500 x 500 x 500) f64 68.7 -> 62.9 us,
-// f32 44.8 -> 35.9 us; the Z_8 ladder in f32 (8 x (4608 x 4608 x 288)) 915 -> 818 us
+// Measured (before -> after): the complex bond-64 environment chain 648 -> 247 us
+// (its align passes alone took 392); 9 x (500 x 500 x 500) f64 71.7 -> 64.5 us,
+// f32 47.3 -> 37.0 us; the Z_8 ladder in f32 (8 x (4608 x 4608 x 288)) 918 -> 844 us
 // (96 x 96 with three workgroups per CU against a 64 x 96 register tile); the
 // complex ladder over Z_2 x Z_4 with blocks of 18 and 5 in f64 1985 -> 1722 us, over Z_8 with
-// 24 and 6 in f32 3457 -> 3125.  4-byte loads run
+// 24 and 6 in f32 3491 -> 3138.  4-byte loads run
 // at about two thirds of 16-byte ones' rate (3 x (743 x 1113 x 1111) f64: 34.5
 // TFLOP/s), so odd real shapes mostly stay on the register tiles.
 //
@@ -39,8 +39,9 @@
 // large products with whole 32-deep K-steps stay on planes, whose tiles reach 0.9;
 // what it saves is the planes' write and reads (12 bytes per element), three or
 // four launches, and the single pass over a long K that those tiles make.
-// Before -> after: 5 x (120 x 320 x 90) 41 -> 17 us, 8 x (3200 x 3200 x 128)
-// 358 -> 142, 4 x (1156 x 1156 x 36) 118 -> 39, 6 x (16 x 186624 x 18) 5307 -> 203.
+// Before -> after, whole contractions: 5 x (120 x 320 x 90) 41 -> 20 us, 4 x (1156 x
+// 1156 x 36) 110 -> 32, 6 x (16 x 186624 x 18) 5233 -> 133, 8 x (3200 x 3200 x 128) 343 ->
+// 153 (195 before the wide tiles were timed as they run; those take it now, at 164).
 //
 // Values and K order are the other tiles': K-steps of 128 bytes, four indices
 // per MFMA, tiles cut by stream-K summed in K order by k_sk_fixup.  Where K was cut

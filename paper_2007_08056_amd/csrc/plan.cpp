@@ -209,10 +209,9 @@ AnyChoice choose_any(int64_t batch, int64_t M, int64_t N, int64_t kpad, int elem
 }
 
 // The split-bf16 tiles of the in-place product.  Efficiencies (of a third of the
-// bf16 peak), rates and launch costs here and in bf16_planes_time are a fit to the
-// times of 130 contractions of 0.00002 to 300 GFLOP on each tile and on planes,
-// with 16- and 4-byte loads, stream-K and not (its own choice is 7% from the best
-// of them in the mean, planes alone 2.4 times).
+// bf16 peak), rates and launch costs are a fit to the times of 130 contractions of
+// 0.00002 to 300 GFLOP on each tile, with 16- and 4-byte loads, stream-K and not (its
+// own choice is 7% from the best of them in the mean, planes alone 2.4 times).
 constexpr AnyTileDesc kAnyTilesBf16[] = {
     {"a128x128s2", 128, 128, 0.31, 0, 2, 0}, {"a128x64s2", 128, 64, 0.22, 0.17, 2, 2},
     {"a64x64s2", 64, 64, 0.19, 0.14, 3, 3}};
